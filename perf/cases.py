@@ -1,0 +1,460 @@
+"""Performance cases: the attribution work a user of the library has it do.
+
+Each case is one pass through the public entry points (``session.py`` over the
+C ABI) on seeded synthetic inputs that are already on the GPU, as captured
+factor blocks and stored feature rows are in a real run:
+
+* ``project``    projected per-example gradients of a stack of linear layers
+* ``attribute``  K-FAC / EK-FAC attribution of one training batch: projection
+                 with the factor sums, eigendecompositions, the eigenvalue
+                 correction, preconditioned queries, scores
+* ``score``      stored feature rows of queries against training rows, top-k
+* ``crossgram``  unprojected cross-Gram of a training batch and queries
+* ``tokens``     token-level scores of a training batch against queries
+* ``masks``      random-mask gradients (ten disjoint masks per layer)
+
+``listed`` names the cases, ``draw`` makes more from the same ranges,
+``exact`` is the same computation in float64 with torch alone.
+"""
+import math
+
+import numpy as np
+import torch
+
+from paper_2609_38767_amd.session import Curvature, ProjectionSession, cross_gram, feature_rows, score
+
+DEV = "cuda"
+TORCH = {"f32": torch.float32, "bf16": torch.bfloat16}
+ELT = {"f32": 4, "bf16": 2}
+
+# One transformer block per family: (d_in, d_out, index of the input block it
+# reads; layers with the same index share it, as q/k/v and gate/up do).
+BLOCKS = {
+    "gpt2": [(768, 2304, 0), (768, 768, 1), (768, 3072, 2), (3072, 768, 3)],
+    "pythia410m": [(1024, 3072, 0), (1024, 1024, 1), (1024, 4096, 2), (4096, 1024, 3)],
+    "llama8b": [(4096, 4096, 0), (4096, 1024, 0), (4096, 1024, 0), (4096, 4096, 1), (4096, 14336, 2),
+                (4096, 14336, 2), (14336, 4096, 3)],
+    "qwen7b": [(3584, 3584, 0), (3584, 512, 0), (3584, 512, 0), (3584, 3584, 1), (3584, 18944, 2),
+               (3584, 18944, 2), (18944, 3584, 3)],
+}
+HEAVY_TAILED = ("llama8b", "qwen7b")  # Student-t factors, as real activations and gradients have
+
+
+def listed():
+    return [
+        # The smallest call: one 64 -> 64 layer, 12 short float32 examples; what is left is the call itself.
+        {"name": "project one small layer f32", "op": "project", "family": "plain", "d_in": 64, "d_out": 64,
+         "blocks": 1, "n": 12, "T": 16, "k": 8, "dtype": "f32", "ragged": False},
+        # The capture of a training batch of an 8B model: long sequences, bf16, full length.
+        {"name": "project llama blocks bf16", "op": "project", "family": "llama8b", "blocks": 4, "n": 8, "T": 2048,
+         "k": 32, "dtype": "bf16", "ragged": False},
+        # A training batch of a small model in float32 with examples of every length, the precision of fidelity runs.
+        {"name": "project pythia f32 ragged", "op": "project", "family": "pythia410m", "blocks": 24, "n": 8, "T": 512,
+         "k": 64, "dtype": "f32", "ragged": True},
+        # The single query of an attribution run: one example, latency and an idle chip count.
+        {"name": "project one query bf16", "op": "project", "family": "qwen7b", "blocks": 8, "n": 1, "T": 512,
+         "k": 64, "dtype": "bf16", "ragged": False},
+        # EK-FAC attribution of one training batch against one query, end to end.
+        {"name": "attribute ekfac bf16", "op": "attribute", "family": "qwen7b", "blocks": 4, "n": 32, "T": 512,
+         "k": 64, "dtype": "bf16", "ragged": False, "kind": "ekfac", "n_q": 1},
+        # One query against stored rows of a whole model (long rows, one read of the training rows).
+        {"name": "score one query bf16", "op": "score", "n_q": 1, "n_train": 4096, "F": 229376, "dtype": "bf16",
+         "precond": False, "cosine": False, "topk": 100},
+        # Many queries against a large training set: the score matrix product.
+        {"name": "score 2048x200000 bf16", "op": "score", "n_q": 2048, "n_train": 200000, "F": 8192, "dtype": "bf16",
+         "precond": True, "cosine": False, "topk": 100},
+        # Cosine scores in float32, as the fidelity and data-selection runs take them.
+        {"name": "score cosine f32", "op": "score", "n_q": 256, "n_train": 8192, "F": 12288, "dtype": "f32",
+         "precond": False, "cosine": True, "topk": 100},
+        # Full-dimensional GradDot in float32 (the routing ablation's precision), ragged examples.
+        {"name": "crossgram T512 f32", "op": "crossgram", "family": "pythia410m", "blocks": 12, "n": 8, "n_q": 1,
+         "T": 512, "dtype": "f32", "ragged": True},
+        # The same in bf16 at long sequences, where dense gradients are the cheaper route.
+        {"name": "crossgram T2048 bf16", "op": "crossgram", "family": "pythia410m", "blocks": 12, "n": 8, "n_q": 1,
+         "T": 2048, "dtype": "bf16", "ragged": False},
+        # Which tokens of the training examples a few queries respond to.
+        {"name": "token scores bf16", "op": "tokens", "family": "qwen7b", "blocks": 4, "n": 16, "T": 512, "k": 64,
+         "dtype": "bf16", "ragged": True, "n_q": 4},
+        # AdamW-influence's ten random masks of 512 entries per layer.
+        {"name": "masks 10x512 bf16", "op": "masks", "family": "llama8b", "blocks": 2, "n": 4, "T": 2048, "m": 512,
+         "dtype": "bf16", "ragged": False},
+    ]
+
+
+# ------------------------------------------------------------------- drawing
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def _draw_stack(rng, budget_bytes, dtypes=("f32", "bf16")):
+    """A stack, batch and sequence length whose factor blocks take at most budget_bytes."""
+    c = {"family": rng.choice(["plain", "gpt2", "pythia410m", "llama8b", "qwen7b"]), "dtype": rng.choice(dtypes),
+         "ragged": rng.random() < 0.5}
+    if c["family"] == "plain":  # adapter- and projection-shaped layers of any width
+        c["d_in"], c["d_out"] = _log_int(rng, 8, 4096), _log_int(rng, 64, 4096)
+        if rng.random() < 0.7:  # most models' widths are multiples of 8
+            c["d_in"], c["d_out"] = (c["d_in"] + 7) // 8 * 8, (c["d_out"] + 7) // 8 * 8
+    c["blocks"] = _log_int(rng, 1, 24)
+    c["n"], c["T"] = _log_int(rng, 1, 32), _log_int(rng, 16, 2048)
+    while _factor_bytes(dict(c, ragged=False)) > budget_bytes:
+        key = max(("blocks", "n", "T"), key=lambda k: c[k] / {"blocks": 4, "n": 8, "T": 256}[k])
+        c[key] = (c[key] + 1) // 2
+    return c
+
+
+def draw(rng):
+    op = rng.choice(["project", "project", "attribute", "score", "score", "crossgram", "tokens", "masks"])
+    if op == "score":
+        dtype = rng.choice(["f32", "bf16"])
+        n_q, n_train = _log_int(rng, 1, 2048), _log_int(rng, 64, 100000)
+        F = max(64, _log_int(rng, 256, 262144) // 8 * 8)
+        while n_train * F * ELT[dtype] > 4e9 or n_q * n_train * F * 2 > (3e11 if dtype == "f32" else 4e12):
+            n_q, n_train, F = (n_q + 1) // 2, max(64, n_train // 2), max(256, F // 2 // 8 * 8)
+        return {"op": "score", "n_q": n_q, "n_train": n_train, "F": F, "dtype": dtype,
+                "precond": rng.random() < 0.4, "cosine": rng.random() < 0.3, "topk": min(n_train, _log_int(rng, 1, 200))}
+    if op == "crossgram":
+        while True:
+            c = _draw_stack(rng, 3e9)
+            c.update(op=op, n_q=_log_int(rng, 1, 8))
+            if _crossgram_flops(dict(c, ragged=False)) < (6e11 if c["dtype"] == "f32" else 4e12):
+                return c
+    if op == "masks":
+        c = _draw_stack(rng, 4e9)
+        room = min(d_in * d_out for d_in, d_out, _ in _layers(c)) // 40  # ten disjoint masks fill at most a quarter
+        c.update(op=op, m=max(1, min(room, _log_int(rng, 64, 2048))))
+        return c
+    c = _draw_stack(rng, 6e9)
+    c.update(op=op, k=rng.choice([4, 8, 16, 16, 32, 32, 48, 64, 64, _log_int(rng, 4, 64)]))
+    if op == "attribute":
+        c.update(kind=rng.choice(["kfac", "ekfac"]), n_q=_log_int(rng, 1, 16))
+    if op == "tokens":
+        c.update(n_q=_log_int(rng, 1, 8))
+    return c
+
+
+# -------------------------------------------------------------------- inputs
+def _layers(c):
+    if c["family"] == "plain":
+        return [(c["d_in"], c["d_out"], i) for i in range(c["blocks"])]
+    block = BLOCKS[c["family"]]
+    groups = 1 + max(g for _, _, g in block)
+    return [(d_in, d_out, g + groups * b) for b in range(c["blocks"]) for d_in, d_out, g in block]
+
+
+def _gen(seed, *parts):
+    g = torch.Generator(device=DEV)
+    v = seed & 0xFFFFFFFF
+    for p in parts:
+        v = (v * 1000003 + p + 1) & ((1 << 62) - 1)
+    g.manual_seed(v)
+    return g
+
+
+def _values(c, shape, g, scale=1.0):
+    """Factor values: normal, or Student-t with 4 degrees of freedom for the large models."""
+    x = torch.randn(shape, generator=g, device=DEV)
+    if c["family"] in HEAVY_TAILED:
+        u = torch.rand((2,) + tuple(shape), generator=g, device=DEV).clamp_min_(1e-30)
+        x = x / torch.sqrt(torch.log(u[0] * u[1]) * -0.5)
+        del u
+    return (x * scale if scale != 1.0 else x).to(TORCH[c["dtype"]])
+
+
+def _length_list(c, n):
+    """Lengths of a batch of texts: one full, the others anywhere in 1..T (one in the middle); the same for every seed."""
+    if not c.get("ragged"):
+        return None
+    return [c["T"] if i == 0 else max(1, (c["T"] * ((i * 7919 + 13) % 97 + 3)) // 100) for i in range(n)]
+
+
+def _factors(c, n, seed, tag):
+    """(A, B) of every layer for n examples; shared input blocks are one tensor."""
+    shared, out = {}, []
+    b_scale = 1e-3 if c["family"] == "gpt2" else 1.0
+    for i, (d_in, d_out, g) in enumerate(_layers(c)):
+        if g not in shared:
+            shared[g] = _values(c, (n, c["T"], d_in), _gen(seed, tag, 1, g))
+        out.append((shared[g], _values(c, (n, c["T"], d_out), _gen(seed, tag, 2, i), b_scale)))
+    return out
+
+
+def _maps(c, seed):
+    """Each layer's two Gaussian maps, float32 (the library rounds them to the compute type)."""
+    k = c["k"]
+    return [tuple((torch.randn((d, k), generator=_gen(seed, 3, i, side), device=DEV) / math.sqrt(k))
+                  for side, d in enumerate((d_in, d_out))) for i, (d_in, d_out, _) in enumerate(_layers(c))]
+
+
+def _session(c, seed, maps=True):
+    k = c.get("k", 1)
+    layers = [{"d_in": d_in, "d_out": d_out, "k_in": k, "k_out": k} for d_in, d_out, _ in _layers(c)]
+    if c["op"] == "masks":
+        for L in layers:
+            L.update(mask_size=c["m"], mask_id=0, mask_count=10)
+    over = None
+    if maps and "k" in c:
+        over = {i: (a.cpu().numpy(), b.cpu().numpy()) for i, (a, b) in enumerate(_maps(c, seed))}
+    return ProjectionSession(layers, dtype=c["dtype"], seed=seed & 0xFFFF, device=DEV, overrides=over)
+
+
+def _captured(c, n, seed, tag, maps=True):
+    s = _session(c, seed, maps)
+    lens = _length_list(c, n)
+    lens = torch.tensor(lens, dtype=torch.int32, device=DEV) if lens else None
+    for i, (A, B) in enumerate(_factors(c, n, seed, tag)):
+        s.capture(i, A, B, lens)
+    return s
+
+
+def _feature_dim(c):
+    return len(_layers(c)) * c["k"] * c["k"]
+
+
+def _query_rows(c, seed):
+    """Query features as stored: float32 rows whose scale is that of projected gradients."""
+    q = feature_rows(c["n_q"], _feature_dim(c), "f32", DEV)
+    q.copy_(torch.randn(q.shape, generator=_gen(seed, 4), device=DEV) * math.sqrt(c["T"]))
+    return q
+
+
+def _score_inputs(c, seed):
+    rows = []
+    for tag, n in ((5, c["n_q"]), (6, c["n_train"])):
+        x = feature_rows(n, c["F"], c["dtype"], DEV)
+        step = max(1, (1 << 28) // c["F"])
+        g = _gen(seed, tag)
+        for r in range(0, n, step):
+            m = min(step, n - r)
+            x[r:r + m].copy_(torch.randn((m, c["F"]), generator=g, device=DEV))
+        rows.append(x)
+    d = None
+    if c["precond"]:  # inverse eigenvalues: positive, over several decades
+        d = torch.pow(10.0, torch.rand(c["F"], generator=_gen(seed, 7), device=DEV) * 4 - 2)
+    return rows[0], rows[1], d
+
+
+def prepare(case, seed):
+    c = case
+    if c["op"] == "score":
+        q, x, d = _score_inputs(c, seed)
+        return {"case": c, "q": q, "x": x, "d": d}
+    if c["op"] == "crossgram":
+        return {"case": c, "train": _captured(c, c["n"], seed, 0, maps=False),
+                "query": _captured(c, c["n_q"], seed, 1, maps=False)}
+    st = {"case": c, "session": _captured(c, c["n"], seed, 0)}
+    if c["op"] in ("attribute", "tokens"):
+        st["q"] = _query_rows(c, seed)
+    if c["op"] == "attribute":
+        st["curv"] = Curvature(st["session"])
+        show = range(0, len(_layers(c)), max(1, len(_layers(c)) // 24))
+        st["sums"] = [st["curv"].field(i, f) for i in list(show)[:24] for f in ("sum_a", "sum_g")]
+    return st
+
+
+def run(state):
+    c = state["case"]
+    if c["op"] == "project":
+        return state["session"].project(c["n"])
+    if c["op"] == "masks":
+        return state["session"].project(c["n"])
+    if c["op"] == "tokens":
+        return state["session"].token_scores(state["q"], c["n"])
+    if c["op"] == "crossgram":
+        return cross_gram(state["train"], state["query"])
+    if c["op"] == "score":
+        return score(state["q"], state["x"], state["d"], topk=c["topk"], cosine=c["cosine"])
+    curv = state["curv"]
+    curv.reset()
+    phi = curv.project_and_fit(c["n"])
+    curv.eigen()
+    if c["kind"] == "ekfac":
+        curv.accumulate_ekfac(phi)
+    pq = curv.precondition(state["q"], kind=c["kind"])
+    return {"phi": phi, "sums": state["sums"], "queries": pq, "scores": score(pq, phi)[0]}
+
+
+# ---------------------------------------------------------------------- work
+def _tokens(c, n):
+    lens = _length_list(c, n)
+    return sum(lens) if lens else n * c["T"]
+
+
+def _factor_bytes(c, n=None):
+    tok = _tokens(c, c["n"] if n is None else n)
+    layers = _layers(c)
+    inputs = {g: d_in for d_in, _, g in layers}
+    return tok * ELT[c["dtype"]] * (sum(inputs.values()) + sum(d_out for _, d_out, _ in layers))
+
+
+def _crossgram_flops(c):
+    ta, tb = _tokens(c, c["n"]), _tokens(c, c["n_q"])
+    return sum(min(2 * ta * tb * (i + o + 1), 2 * (ta + tb) * i * o + 2 * c["n"] * c["n_q"] * i * o)
+               for i, o, _ in _layers(c))
+
+
+def work(case):
+    c = case
+    if c["op"] == "score":
+        e = ELT[c["dtype"]]
+        return {"bytes": (c["n_q"] + c["n_train"]) * c["F"] * e + c["n_q"] * c["n_train"] * 4 + c["n_q"] * c["topk"] * 8,
+                "flops": 2 * c["n_q"] * c["n_train"] * c["F"]}
+    if c["op"] == "crossgram":
+        return {"bytes": _factor_bytes(c) + _factor_bytes(c, c["n_q"]) + 4 * c["n"] * c["n_q"],
+                "flops": _crossgram_flops(c)}
+    tok, layers = _tokens(c, c["n"]), _layers(c)
+    if c["op"] == "masks":
+        # every value of a factor row that an entry of the masks reads (nearly all of each row), each entry's sum out
+        F = len(layers) * 10 * c["m"]
+        inputs = {g: d_in for d_in, _, g in layers}
+        touched = sum(inputs.values()) + sum(o * (1 - math.exp(-10 * c["m"] / o)) for _, o, _ in layers)
+        return {"bytes": tok * ELT[c["dtype"]] * touched + 4 * c["n"] * F, "flops": 2 * tok * F}
+    k, F = c["k"], _feature_dim(c)
+    w = {"bytes": _factor_bytes(c) + sum(i + o for i, o, _ in layers) * k * ELT[c["dtype"]] + 4 * c["n"] * F,
+         "flops": sum(2 * tok * (i + o + k) * k for i, o, _ in layers)}
+    if c["op"] == "tokens":
+        w["bytes"] += 4 * (c["n_q"] * F + c["n_q"] * c["n"] * c["T"])
+        w["flops"] += c["n_q"] * len(layers) * 2 * tok * k * (k + 1)
+    if c["op"] == "attribute":
+        w["bytes"] += 4 * (2 * c["n_q"] * F + c["n_q"] * c["n"] + 2 * len(layers) * k * k)
+        w["flops"] += len(layers) * (4 * tok * k * k + (4 * c["n"] * k ** 3 if c["kind"] == "ekfac" else 0)
+                                     + 8 * c["n_q"] * k ** 3) + 2 * c["n_q"] * c["n"] * F
+    return w
+
+
+def tolerance(case):
+    """Every product and sum is taken in float32 on inputs of either type, and the outputs are float32: what is left
+XX
+    if case["op"] == "attribute":
+        # the eigenvalue correction squares rotated sums and the damped division amplifies their rounding
+        return {"rel": 4e-5, "max": 2e-3}
+    if case["op"] == "score" and case["dtype"] == "bf16" and case["precond"]:
+        # scaled queries are rounded to bf16 once: a last-bit difference of the scaling moves a query value by 2^-9
+        return {"rel": 1e-4, "max": 5e-3, "differ": 0.01}
+    return {"rel": 1e-5, "max": 5e-4, "differ": 0.005}
+
+
+# --------------------------------------------------------------------- exact
+def _live(c, X, n):
+    """X with the rows past each example's length zeroed, float64."""
+    X = X.double()
+    lens = _length_list(c, n)
+    if lens:
+        t = torch.arange(c["T"], device=X.device)
+        X = X * (t[None, :] < torch.tensor(lens, device=X.device)[:, None]).unsqueeze(-1)
+    return X
+
+
+def _projected(c, seed):
+    """Per layer (a~, g~) in float64."""
+    out = []
+    for (A, B), maps in zip(_factors(c, c["n"], seed, 0), _maps(c, seed)):
+        P = [m.to(TORCH[c["dtype"]]).double() for m in maps]
+        out.append((_live(c, A, c["n"]) @ P[0], _live(c, B, c["n"]) @ P[1]))
+    return out
+
+
+def _blocks_of(proj):
+    return [torch.bmm(a.transpose(1, 2).contiguous(), g) for a, g in proj]
+
+
+def _rows(blocks):
+    return torch.cat([b.reshape(b.shape[0], -1) for b in blocks], dim=1)
+
+
+def _philox(counter, key):
+    """Philox4x32-10 over uint64 arrays of 32-bit words (Salmon et al., SC'11)."""
+    c, k = [np.asarray(v, dtype=np.uint64) for v in counter], [int(v) for v in key]
+    m = np.uint64(0xFFFFFFFF)
+    for _ in range(10):
+        p0, p1 = c[0] * np.uint64(0xD2511F53), c[2] * np.uint64(0xCD9E8D57)
+        c = [(p1 >> np.uint64(32)) ^ c[1] ^ np.uint64(k[0]), p1 & m, (p0 >> np.uint64(32)) ^ c[3] ^ np.uint64(k[1]), p0 & m]
+        k = [(k[0] + 0x9E3779B9) & 0xFFFFFFFF, (k[1] + 0xBB67AE85) & 0xFFFFFFFF]
+    return c
+
+
+def _splitmix(x):
+    w = (1 << 64) - 1
+    z = (x + 0x9E3779B97F4A7C15) & w
+    z = ((z ^ (z >> 30)) * 0xBF58476D1CE4E5B9) & w
+    z = ((z ^ (z >> 27)) * 0x94D049BB133111EB) & w
+    return z ^ (z >> 31)
+
+
+def _mask_entries(seed, layer, d_in, d_out, m, count):
+    """(rows, cols) of `count` masks of m entries: distinct draws in order, each run of m sorted by c * d_out + r."""
+    s = _splitmix(_splitmix(seed) ^ ((1 << 63) | layer))
+    i = np.arange(4 * m * count + 64, dtype=np.uint64)
+    x = _philox((i & np.uint64(0xFFFFFFFF), i >> np.uint64(32), i * np.uint64(0), i * np.uint64(0)), (s & 0xFFFFFFFF, s >> 32))
+    u = ((x[0] << np.uint64(32)) | x[1]) % np.uint64(d_in * d_out)
+    _, first = np.unique(u, return_index=True)
+    u = np.sort(u[np.sort(first)][:m * count].reshape(count, m), axis=1).reshape(-1).astype(np.int64)
+    return u % d_out, u // d_out
+
+
+def exact(case, seed):
+    c = case
+    if c["op"] == "score":
+        q, x, d = _score_inputs(c, seed)
+        q = q.double() * d.double() if d is not None else q.double()
+        S = torch.empty((c["n_q"], c["n_train"]), dtype=torch.float64, device=DEV)
+        step = max(1, (1 << 28) // c["F"])
+        for r in range(0, c["n_train"], step):
+            xr = x[r:r + step].double()
+            S[:, r:r + step] = q @ xr.t()
+            if c["cosine"]:
+                S[:, r:r + step] /= q.norm(dim=1)[:, None] * xr.norm(dim=1)[None, :]
+        return S, None, torch.topk(S, c["topk"], dim=1).values
+    if c["op"] == "crossgram":
+        K = torch.zeros((c["n"], c["n_q"]), dtype=torch.float64, device=DEV)
+        for (A, B), (Aq, Bq) in zip(_factors(c, c["n"], seed, 0), _factors(c, c["n_q"], seed, 1)):
+            A, B = _live(c, A, c["n"]), _live(c, B, c["n"])
+            Aq, Bq = _live(c, Aq, c["n_q"]), _live(c, Bq, c["n_q"])
+            for j in range(c["n_q"]):
+                W = Bq[j].t().contiguous() @ Aq[j]  # the query's dense gradient; <g a^T, W> = g^T W a per token
+                for i in range(c["n"]):
+                    K[i, j] += ((B[i] @ W) * A[i]).sum()
+        return K
+    if c["op"] == "masks":
+        out = []
+        for li, ((d_in, d_out, _), (A, B)) in enumerate(zip(_layers(c), _factors(c, c["n"], seed, 0))):
+            r, col = _mask_entries(seed & 0xFFFF, li, d_in, d_out, c["m"], 10)
+            A, B = _live(c, A, c["n"]), _live(c, B, c["n"])
+            r, col = torch.from_numpy(r).to(DEV), torch.from_numpy(col).to(DEV)
+            part = []
+            for e in range(0, r.numel(), 2048):
+                part.append((B[:, :, r[e:e + 2048]] * A[:, :, col[e:e + 2048]]).sum(dim=1))
+            out.append(torch.cat(part, dim=1))
+        return torch.cat(out, dim=1)
+    proj = _projected(c, seed)
+    if c["op"] == "project":
+        return _rows(_blocks_of(proj))
+    k = c["k"]
+    q = _query_rows(c, seed).double()
+    if c["op"] == "tokens":
+        s = torch.zeros((c["n_q"], c["n"], c["T"]), dtype=torch.float64, device=DEV)
+        for i, (a, g) in enumerate(proj):
+            for j in range(c["n_q"]):
+                R = q[j, i * k * k:(i + 1) * k * k].view(k, k)
+                s[j] += ((a @ R) * g).sum(-1)
+        return s, _rows(_blocks_of(proj))
+    blocks = _blocks_of(proj)
+    sums, pq = [], []
+    n_layers, tok = len(_layers(c)), _tokens(c, c["n"])
+    show = list(range(0, n_layers, max(1, n_layers // 24)))[:24]
+    for i, (a, g) in enumerate(proj):
+        a, g = a.reshape(-1, k), g.reshape(-1, k)
+        sa, sg = a.t().contiguous() @ a, g.t().contiguous() @ g
+        if i in show:
+            sums += [sa, sg]
+        la, qa = torch.linalg.eigh((sa / tok).cpu())
+        lg, qg = torch.linalg.eigh((sg / c["n"]).cpu())
+        la, qa, lg, qg = (v.to(DEV) for v in (la, qa, lg, qg))
+        E = la[:, None] * lg[None, :]
+        if c["kind"] == "ekfac":
+            E = torch.stack([(qa.t() @ b @ qg) ** 2 for b in blocks[i]]).mean(0)
+        for j in range(c["n_q"]):
+            R = q[j, i * k * k:(i + 1) * k * k].view(k, k)
+            pq.append((j, i, qa @ ((qa.t() @ R @ qg) / (E + 0.1 * E.mean())) @ qg.t()))
+    queries = torch.stack([torch.cat([v.reshape(-1) for jj, _, v in pq if jj == j]) for j in range(c["n_q"])])
+    phi = _rows(blocks)
+    return {"phi": phi, "sums": sums, "queries": queries, "scores": queries @ phi.t()}
