@@ -129,6 +129,64 @@ __device__ inline f32x4 frag_mma<4>(i32x4 a, i32x4 b, f32x4 c) {
   return c;
 }
 
+// A float32 value as three bf16 terms, hi + mid + lo = v exactly (hi and mid
+// rounded to nearest: |v - hi| <= 2^-9 |v|, and the remainder left for lo has at
+// most 8 significant bits), for finite v whose rounded hi is finite and away
+// from the subnormals.  Products of two split values keep the six terms down
+// to 2^-18: the three left out are at most 2^-26 of the product together, below
+// the float32 rounding of the sum they are added to.  Non-finite values do not
+// survive the split (inf - inf): kernels that use it recompute in float32
+// wherever a result is not finite.
+struct Split3 {
+  bf16x8 hi, mid, lo;
+};
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+__device__ inline uint32_t pack_bf16(float a, float b) {  // round to nearest even, a in the low half
+  const f32x2 v = {a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+__device__ inline void split_pair(float a, float b, uint32_t* hi, uint32_t* mid, uint32_t* lo) {
+  const uint32_t h = pack_bf16(a, b);
+  const float ra = a - __builtin_bit_cast(float, h << 16), rb = b - __builtin_bit_cast(float, h & 0xFFFF0000u);
+  const uint32_t m = pack_bf16(ra, rb);
+  const float sa = ra - __builtin_bit_cast(float, m << 16), sb = rb - __builtin_bit_cast(float, m & 0xFFFF0000u);
+  *hi = h;
+  *mid = m;
+  *lo = pack_bf16(sa, sb);
+}
+// The eight values of two float32 fragments as the K slots of one bf16 operand.
+__device__ inline Split3 split3(i32x4 u, i32x4 v) {
+  const f32x4 a = __builtin_bit_cast(f32x4, u), b = __builtin_bit_cast(f32x4, v);
+  uint32_t h0, h1, h2, h3, m0, m1, m2, m3, l0, l1, l2, l3;
+  split_pair(a.x, a.y, &h0, &m0, &l0);
+  split_pair(a.z, a.w, &h1, &m1, &l1);
+  split_pair(b.x, b.y, &h2, &m2, &l2);
+  split_pair(b.z, b.w, &h3, &m3, &l3);
+  const i32x4 h = {(int)h0, (int)h1, (int)h2, (int)h3}, m = {(int)m0, (int)m1, (int)m2, (int)m3},
+              l = {(int)l0, (int)l1, (int)l2, (int)l3};
+  return Split3{__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
+}
+__device__ inline f32x4 mfma_bf16_16(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+// Term p (0 .. 5, smallest products first) of a split product.
+template <int p>
+__device__ inline f32x4 split_term(const Split3& a, const Split3& b, f32x4 c) {
+  if constexpr (p == 0) return mfma_bf16_16(a.lo, b.hi, c);
+  if constexpr (p == 1) return mfma_bf16_16(a.hi, b.lo, c);
+  if constexpr (p == 2) return mfma_bf16_16(a.mid, b.mid, c);
+  if constexpr (p == 3) return mfma_bf16_16(a.mid, b.hi, c);
+  if constexpr (p == 4) return mfma_bf16_16(a.hi, b.mid, c);
+  return mfma_bf16_16(a.hi, b.hi, c);
+}
+// Whether any element is infinite or NaN.
+__device__ inline bool not_finite(f32x4 v) {
+  const float s = (v.x - v.x) + (v.y - v.y) + (v.z - v.z) + (v.w - v.w);  // 0, or NaN
+  return !(s == 0.f);
+}
+
 // Workgroup barrier that orders LDS accesses only.  __syncthreads() also
 // fences global memory, which makes the compiler wait for every outstanding
 // global load (vmcnt(0)) and would drain register prefetch pipelines.

@@ -101,13 +101,20 @@ hipError_t launch_reduce(const ReduceTask* tasks, int n_tasks, int n_examples, i
 // n*T rows) slab by slab over the feature dimension d, writing float32
 // partial projections [slab][row][tile cols]; stage 2 sums the slabs and
 // contracts each example's tokens into its layer block of phi.
-// Rows per stage-1 workgroup of the instance with nt_inst tiles: 4 waves of
-// 4 row tiles (2 at 8 tiles, where 4 would not fit the register file).
+// Rows per stage-1 workgroup: 4 waves of 4 row tiles on the direct-load stream
+// (aligned rows); the same on the register path (unaligned rows) up to 4 map
+// tiles, 2 row tiles at 8, where 4 would not fit the register file.
+constexpr int split_stream_rows(int elt) { return elt == 2 ? 256 : 128; }
 constexpr int split_rt_of(int nt_inst) { return nt_inst <= 4 ? 4 : 2; }
 constexpr int split_rows_of(int nt_inst) { return 4 * split_rt_of(nt_inst) * 16; }
+constexpr int kSplitMaxTilesF32 = 4;   // map tiles of one aligned float32 op
 constexpr int kSplitSlabQuantum = 128;  // slab widths are multiples of this
 struct SplitOp {                    // one factor block: a group's A or a member's B
   const void* X;                    // [rows, ld] row-major
+  const int32_t* lengths;           // [n] or null: row i is token i % T of example i / T
+  int32_t T;
+  int32_t out_ld;                   // floats per projected row
+  int32_t once, pad0;               // no other op of the call reads X
   int32_t rows, ld;                 // n*T, d
   int32_t slab_cols, n_slabs;
   int32_t nt;                       // 16-column tiles of the projected rows
@@ -130,7 +137,7 @@ struct ContractTask {               // one layer
   int64_t partial_base;             // else: float offset of [example][chunk][ki16 x ko16]
   const int32_t* lengths;           // [n] or null
 };
-// One launch per instance (elt, aligned, tiles); items of that instance only.
+// Aligned: one launch for every op (nt unused); unaligned: one per tile count.
 hipError_t launch_split_project(int elt_bytes, int aligned, int nt, const SplitItem* items,
                                 int n_items, const SplitOp* ops, float* out, hipStream_t s);
 int split_nt_instance(int nt_req);  // tiles of the instance that serves nt_req tiles
@@ -144,7 +151,8 @@ struct SlabSumTask {
 hipError_t launch_slab_sum(const SlabSumTask* tasks, int n_tasks, int64_t max_n4, float* out,
                            hipStream_t s);
 // Grid (max_tchunks, n_examples, n_tasks); chunks past a task's n_tchunks exit.
-hipError_t launch_split_contract(const ContractTask* tasks, int n_tasks, int n_examples,
+// na, nb: the largest input and output tile counts over the tasks.
+hipError_t launch_split_contract(int na, int nb, const ContractTask* tasks, int n_tasks, int n_examples,
                                  int max_tchunks, const float* proj, float* partials, void* phi,
                                  int phi_bf16, int64_t ld_phi, hipStream_t s);
 

@@ -48,6 +48,7 @@ struct Plan {
   std::vector<SlabSumTask> slabsum;
   int64_t slabsum_max_n4 = 0;
   int split_max_tchunks = 0, split_max_out = 0;
+  int split_na = 0, split_nb = 0;  // largest tile counts over the contraction tasks
   // mask layers (gathered DW entries)
   std::vector<MaskTask> mtasks;
   std::vector<MaskItem> mitems;

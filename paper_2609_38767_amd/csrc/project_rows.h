@@ -262,5 +262,327 @@ __device__ inline void project_rows_dma(const rsrc_t r, int r_wave, int nrows, i
   stage_barrier();  // every wave is done with the ring before the next call refills it
 }
 
+// ---------------------------------------------------------------------------
+// The bf16 direct-load stream with per-row validity and a ring of D stages:
+// acc[rt][t] += (X[rows, 0:d] P[0:d, tile t])^T, the map fragment as the first
+// MFMA operand; stages, chunk swizzle and map fragments as in project_rows_dma.
+// rowoff[i]: byte offset in `r` of the chunk this lane loads of row group i's
+// stage 0 (row i * 8 + lane / 8 of the wave, chunk (lane % 8) ^ (row % 8)), or
+// kFarOff for a row that must not be read (it reads as zero).  P(t, &base,
+// &stride): the packed map's fragment (k-block kb, tile t) is at base + kb *
+// stride; nt tiles are in use.  Stages s .. s +
+// D - 1 are in flight or in use: the wait for stage s leaves the loads of the
+// later stages already issued outstanding, the barrier publishes the
+// shared map fragments, and stage s + D is issued into the wave's own buffer
+// s % D once its reads of stage s are done.  A map slot is refilled D + 1
+// stages later: its readers (stage s - 1) all passed stage s's barrier.
+constexpr uint32_t kFarOff = 0x80000000u;  // + any column offset: past every descriptor used with it (< 2 GiB)
+
+template <int RT, int NT, int D>
+struct StreamLds {
+  static_assert((2 * NT) % kWaves == 0, "NT / 2 projection fragments per wave and stage");
+  static constexpr int kWaveStage = RT * 16 * 128;   // bytes per wave and stage
+  static constexpr int kLoads = RT * 16 / 8;         // 1 KiB row-group loads per stage
+  static constexpr int kMapLoads = 2 * NT / kWaves;  // this wave's fragments per stage
+  static constexpr int kOps = kLoads + kMapLoads;
+  static_assert((D - 1) * kOps < 64, "vmcnt range");
+  static constexpr int kMapOff = kWaves * D * kWaveStage;
+  static constexpr int kMapStage = 2 * NT * kFragBytes;
+  static constexpr int kBytes = kMapOff + (D + 1) * kMapStage;
+};
+
+// One k-block's operand fragments from LDS: RT row tiles (2 KiB apart from
+// byte address xa) and NT map fragments (1 KiB apart from pa), waited for in
+// the same block.  Inline assembly, because the compiler cannot tell which LDS
+// bytes a direct load in flight will write and would put vmcnt(0) before the
+// reads, draining the ring each stage.
+template <int RT, int NT>
+__device__ inline void read_frags(i32x4 (&x)[RT], i32x4 (&p)[NT], uint32_t xa, uint32_t pa) {
+  static_assert((RT == 2 || RT == 4) && (NT == 2 || NT == 4 || NT == 6 || NT == 8), "row and map tiles");
+  if constexpr (RT == 2 && NT == 2)
+    asm volatile("ds_read_b128 %0, %[xa] offset:0\n\t" "ds_read_b128 %1, %[xa] offset:2048\n\t"
+                 "ds_read_b128 %2, %[pa] offset:0\n\t" "ds_read_b128 %3, %[pa] offset:1024\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(x[0]), "=&v"(x[1]), "=&v"(p[0]), "=&v"(p[1])
+                 : [xa] "v"(xa), [pa] "v"(pa)
+                 : "memory");
+  else if constexpr (RT == 2 && NT == 4)
+    asm volatile("ds_read_b128 %0, %[xa] offset:0\n\t" "ds_read_b128 %1, %[xa] offset:2048\n\t"
+                 "ds_read_b128 %2, %[pa] offset:0\n\t" "ds_read_b128 %3, %[pa] offset:1024\n\t"
+                 "ds_read_b128 %4, %[pa] offset:2048\n\t" "ds_read_b128 %5, %[pa] offset:3072\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(x[0]), "=&v"(x[1]), "=&v"(p[0]), "=&v"(p[1]), "=&v"(p[2]), "=&v"(p[3])
+                 : [xa] "v"(xa), [pa] "v"(pa)
+                 : "memory");
+  else if constexpr (RT == 2 && NT == 6)
+    asm volatile("ds_read_b128 %0, %[xa] offset:0\n\t" "ds_read_b128 %1, %[xa] offset:2048\n\t"
+                 "ds_read_b128 %2, %[pa] offset:0\n\t" "ds_read_b128 %3, %[pa] offset:1024\n\t"
+                 "ds_read_b128 %4, %[pa] offset:2048\n\t" "ds_read_b128 %5, %[pa] offset:3072\n\t"
+                 "ds_read_b128 %6, %[pa] offset:4096\n\t" "ds_read_b128 %7, %[pa] offset:5120\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(x[0]), "=&v"(x[1]), "=&v"(p[0]), "=&v"(p[1]), "=&v"(p[2]), "=&v"(p[3]), "=&v"(p[4]), "=&v"(p[5])
+                 : [xa] "v"(xa), [pa] "v"(pa)
+                 : "memory");
+  else if constexpr (RT == 2 && NT == 8)
+    asm volatile("ds_read_b128 %0, %[xa] offset:0\n\t" "ds_read_b128 %1, %[xa] offset:2048\n\t"
+                 "ds_read_b128 %2, %[pa] offset:0\n\t" "ds_read_b128 %3, %[pa] offset:1024\n\t"
+                 "ds_read_b128 %4, %[pa] offset:2048\n\t" "ds_read_b128 %5, %[pa] offset:3072\n\t"
+                 "ds_read_b128 %6, %[pa] offset:4096\n\t" "ds_read_b128 %7, %[pa] offset:5120\n\t"
+                 "ds_read_b128 %8, %[pa] offset:6144\n\t" "ds_read_b128 %9, %[pa] offset:7168\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(x[0]), "=&v"(x[1]), "=&v"(p[0]), "=&v"(p[1]), "=&v"(p[2]), "=&v"(p[3]), "=&v"(p[4]), "=&v"(p[5]), "=&v"(p[6]), "=&v"(p[7])
+                 : [xa] "v"(xa), [pa] "v"(pa)
+                 : "memory");
+  else if constexpr (RT == 4 && NT == 2)
+    asm volatile("ds_read_b128 %0, %[xa] offset:0\n\t" "ds_read_b128 %1, %[xa] offset:2048\n\t"
+                 "ds_read_b128 %2, %[xa] offset:4096\n\t" "ds_read_b128 %3, %[xa] offset:6144\n\t"
+                 "ds_read_b128 %4, %[pa] offset:0\n\t" "ds_read_b128 %5, %[pa] offset:1024\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(p[0]), "=&v"(p[1])
+                 : [xa] "v"(xa), [pa] "v"(pa)
+                 : "memory");
+  else if constexpr (RT == 4 && NT == 4)
+    asm volatile("ds_read_b128 %0, %[xa] offset:0\n\t" "ds_read_b128 %1, %[xa] offset:2048\n\t"
+                 "ds_read_b128 %2, %[xa] offset:4096\n\t" "ds_read_b128 %3, %[xa] offset:6144\n\t"
+                 "ds_read_b128 %4, %[pa] offset:0\n\t" "ds_read_b128 %5, %[pa] offset:1024\n\t"
+                 "ds_read_b128 %6, %[pa] offset:2048\n\t" "ds_read_b128 %7, %[pa] offset:3072\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(p[0]), "=&v"(p[1]), "=&v"(p[2]), "=&v"(p[3])
+                 : [xa] "v"(xa), [pa] "v"(pa)
+                 : "memory");
+  else if constexpr (RT == 4 && NT == 6)
+    asm volatile("ds_read_b128 %0, %[xa] offset:0\n\t" "ds_read_b128 %1, %[xa] offset:2048\n\t"
+                 "ds_read_b128 %2, %[xa] offset:4096\n\t" "ds_read_b128 %3, %[xa] offset:6144\n\t"
+                 "ds_read_b128 %4, %[pa] offset:0\n\t" "ds_read_b128 %5, %[pa] offset:1024\n\t"
+                 "ds_read_b128 %6, %[pa] offset:2048\n\t" "ds_read_b128 %7, %[pa] offset:3072\n\t"
+                 "ds_read_b128 %8, %[pa] offset:4096\n\t" "ds_read_b128 %9, %[pa] offset:5120\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(p[0]), "=&v"(p[1]), "=&v"(p[2]), "=&v"(p[3]), "=&v"(p[4]), "=&v"(p[5])
+                 : [xa] "v"(xa), [pa] "v"(pa)
+                 : "memory");
+  else if constexpr (RT == 4 && NT == 8)
+    asm volatile("ds_read_b128 %0, %[xa] offset:0\n\t" "ds_read_b128 %1, %[xa] offset:2048\n\t"
+                 "ds_read_b128 %2, %[xa] offset:4096\n\t" "ds_read_b128 %3, %[xa] offset:6144\n\t"
+                 "ds_read_b128 %4, %[pa] offset:0\n\t" "ds_read_b128 %5, %[pa] offset:1024\n\t"
+                 "ds_read_b128 %6, %[pa] offset:2048\n\t" "ds_read_b128 %7, %[pa] offset:3072\n\t"
+                 "ds_read_b128 %8, %[pa] offset:4096\n\t" "ds_read_b128 %9, %[pa] offset:5120\n\t"
+                 "ds_read_b128 %10, %[pa] offset:6144\n\t" "ds_read_b128 %11, %[pa] offset:7168\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(p[0]), "=&v"(p[1]), "=&v"(p[2]), "=&v"(p[3]), "=&v"(p[4]), "=&v"(p[5]), "=&v"(p[6]), "=&v"(p[7])
+                 : [xa] "v"(xa), [pa] "v"(pa)
+                 : "memory");
+}
+
+template <int RT, int NT, int D, class Frag>
+__device__ inline void stream_rows(const rsrc_t r, const uint32_t (&rowoff)[StreamLds<RT, NT, D>::kLoads], int d,
+                                   int nt, const Frag& P, bool once, f32x4 (&acc)[RT][NT], uint8_t* lds) {
+  using C = StreamLds<RT, NT, D>;
+  constexpr int EPL = 8, KR = 4 * EPL;
+  const int lane = threadIdx.x & 63, g = lane >> 4, m16 = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nkb = (d + KR - 1) / KR;
+  const int nst = (nkb + 1) / 2;
+  uint8_t* own = lds + wave * D * C::kWaveStage;
+  // LDS addresses of this lane's reads of stage slot 0: row m16 of each row
+  // tile (its chunk g of k-block 0; k-block 1 is 64 bytes across), and the maps
+  typedef __attribute__((address_space(3))) uint8_t lds_u8;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)lds;
+  const uint32_t x0 = lds0 + (uint32_t)(wave * D * C::kWaveStage + m16 * 128 + ((g ^ (m16 & 7)) << 4));
+  const uint32_t m0 = lds0 + (uint32_t)(C::kMapOff + lane * 16);
+  // fragment f = wave * kMapLoads + i of a stage is k-block 2s + f / NT of tile f % NT
+  int f_kbl[C::kMapLoads], f_t[C::kMapLoads];
+  int64_t f_stride[C::kMapLoads];
+  const uint8_t* f_base[C::kMapLoads];
+#pragma unroll
+  for (int i = 0; i < C::kMapLoads; ++i) {
+    const int f = wave * C::kMapLoads + i;
+    f_kbl[i] = f / NT;
+    f_t[i] = f % NT;
+    P(f_t[i], &f_base[i], &f_stride[i]);
+  }
+  auto issue = [&](int s) {
+    uint8_t* xs = own + (s % D) * C::kWaveStage;
+    const uint32_t colb = (uint32_t)s * 128;
+    const bool whole = (s + 1) * 2 * KR <= d;  // uniform: no column of the stage lies past d
+#pragma unroll
+    for (int i = 0; i < C::kLoads; ++i) {
+      const int c = (lane & 7) ^ ((lane >> 3) & 7);  // row i * 8 + lane / 8: its low three bits are lane / 8
+      uint32_t off = rowoff[i] + colb;
+      if (!whole && s * 2 * KR + c * EPL >= d) off = kFarOff;
+      if (once)  // uniform: streamed past L2's other lines (nt)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, DATTRI_LDS_PTR(xs + i * 1024), 16, off, 0, 0, 2);
+      else
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, DATTRI_LDS_PTR(xs + i * 1024), 16, off, 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < C::kMapLoads; ++i) {
+      const int kb = 2 * s + f_kbl[i];
+      uint8_t* ms = lds + C::kMapOff + (s % (D + 1)) * C::kMapStage + (f_kbl[i] * NT + f_t[i]) * kFragBytes;
+      const uint32_t moff = (f_t[i] < nt && kb < nkb) ? (uint32_t)(kb * f_stride[i] + lane * 16) : kFarOff;
+      const rsrc_t rp = make_rsrc(f_base[i], (uint32_t)((int64_t)nkb * f_stride[i]));
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rp, DATTRI_LDS_PTR(ms), 16, moff, 0, 0, 0);
+    }
+  };
+  auto stage_barrier = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+#pragma unroll
+  for (int s = 0; s < D; ++s)
+    if (s < nst) issue(s);
+  for (int s = 0; s < nst; ++s) {
+    const int later = nst - 1 - s;  // stages already issued behind stage s (at most D - 1)
+    if (later >= D - 1)
+      wait_vmcnt_dma<(D - 1) * C::kOps>();
+    else if (D > 3 && later == 2)
+      wait_vmcnt_dma<2 * C::kOps>();
+    else if (D > 2 && later == 1)
+      wait_vmcnt_dma<C::kOps>();
+    else
+      wait_vmcnt_dma<0>();
+    stage_barrier();
+    const uint32_t xs = x0 + (uint32_t)((s % D) * C::kWaveStage);
+    const uint32_t ms = m0 + (uint32_t)((s % (D + 1)) * C::kMapStage);
+#pragma unroll
+    for (int kbl = 0; kbl < 2; ++kbl) {
+      if (2 * s + kbl < nkb) {  // uniform
+        i32x4 x[RT], pf[NT];
+        read_frags<RT, NT>(x, pf, kbl ? xs ^ 64u : xs, ms + (uint32_t)(kbl * NT * kFragBytes));
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          if (t < nt) {
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) acc[rt][t] = frag_mma<2>(pf[t], x[rt], acc[rt][t]);
+          }
+        }
+      }
+    }
+    if (s + D < nst) issue(s + D);  // this wave's reads of the buffer are done (read_frags waited)
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The float32 stream: products on bf16 MFMA with both operands split into three
+// bf16 terms (split3): 6 MFMA of 16 cycles per tile product where float32 MFMA
+// takes 8 of 32, so maps of up to 4 tiles stay bound by the row stream.  A
+// stage is 32 columns, one K = 32 step: its two float32 k-blocks give K slots
+// 0-3 and 4-7 of every lane, for rows and maps alike.  A wave's rows go
+// straight into registers, two stages ahead, and are split there; the map
+// fragments are shared by the workgroup: wave t splits tile t of stage s + 1
+// while stage s is multiplied, into double-buffered bf16 planes in LDS.
+// Measured on 32 blocks of 4096 rows of 4096 (2.15 GB): 0.45 ms with k = 16
+// (HBM-bound), 0.54 ms with k = 64, where the vector ALU (43% of cycles:
+// splitting) and the matrix cores (40%) take turns on the issue port; float32
+// MFMA with rows streamed through LDS took 1.3 times as long.  Rows staged in
+// LDS by direct loads, and 256-row workgroups, measured the same at k = 64.
+template <int NT>
+struct StreamF32Lds {
+  static_assert(NT <= kWaves, "one map tile per wave is split");
+  static constexpr int kPlane = NT * kFragBytes;  // hi, mid, lo planes of NT fragments
+  static constexpr int kBytes = 2 * 3 * kPlane;
+};
+
+// rowoff[rt]: byte offset in `r` of this lane's 16 bytes of stage 0 in row
+// m16 of row tile rt (chunk lane / 16), or kFarOff for a row not to be read.
+// P, nt as for stream_rows; live: the wave has a row to read (uniform).
+template <int RT, int NT, class Frag>
+__device__ inline void stream_rows_f32(const rsrc_t r, const uint32_t (&rowoff)[RT], int d, int nt, const Frag& P,
+                                       bool live, f32x4 (&acc)[RT][NT], uint8_t* lds) {
+  using C = StreamF32Lds<NT>;
+  const int lane = threadIdx.x & 63, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nkb = (d + 15) / 16;
+  const int nst = (nkb + 1) / 2;
+  const uint8_t* m_base;
+  int64_t m_stride;
+  P(wave, &m_base, &m_stride);
+  const bool splits = wave < nt;  // uniform over the wave
+  const rsrc_t rm = make_rsrc(m_base, splits ? (uint32_t)((int64_t)nkb * m_stride) : 0u);
+  // no branch around any load: behind one, the compiler's wait counts fall back to vmcnt(0)
+  auto load_x = [&](int s, i32x4 (&x)[RT][2]) {
+    const int col = s * 32 + g * 4;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const bool in = col + h * 16 < d;
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) x[rt][h] = load16(r, in ? rowoff[rt] + (uint32_t)(s * 128 + h * 64) : kFarOff);
+    }
+  };
+  auto load_m = [&](int s, i32x4 (&m)[2]) {  // k-blocks past the map read as zero
+#pragma unroll
+    for (int h = 0; h < 2; ++h) m[h] = load16(rm, 2 * s + h < nkb ? (uint32_t)((2 * s + h) * m_stride + lane * 16) : kFarOff);
+  };
+  auto put_planes = [&](int buf, const i32x4 (&m)[2]) {
+    if (splits) {
+      const Split3 v = split3(m[0], m[1]);
+      uint8_t* w = lds + buf * 3 * C::kPlane + wave * kFragBytes + lane * 16;
+      *(bf16x8*)w = v.hi;
+      *(bf16x8*)(w + C::kPlane) = v.mid;
+      *(bf16x8*)(w + 2 * C::kPlane) = v.lo;
+    }
+  };
+  i32x4 x[2][RT][2], m[2][2];
+  load_m(0, m[0]);
+  load_x(0, x[0]);
+  load_m(1, m[1]);
+  load_x(1, x[1]);
+  put_planes(0, m[0]);
+  load_m(2, m[0]);
+  // stages by pairs (register arrays indexed statically); an odd last stage's
+  // partner reads zeros
+  for (int s0 = 0; s0 < nst; s0 += 2) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int s = s0 + q;
+      lds_barrier();  // planes of stage s are written, those of stage s - 1 read
+      put_planes(q ^ 1, m[q ^ 1]);
+      load_m(s + 3, m[q ^ 1]);
+      if (live) {
+        Split3 pv[NT];
+        const uint8_t* pl = lds + q * 3 * C::kPlane + lane * 16;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {  // tiles >= nt multiply whatever the planes hold and are dropped
+          pv[t].hi = *(const bf16x8*)(pl + t * kFragBytes);
+          pv[t].mid = *(const bf16x8*)(pl + C::kPlane + t * kFragBytes);
+          pv[t].lo = *(const bf16x8*)(pl + 2 * C::kPlane + t * kFragBytes);
+        }
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+          const Split3 xv = split3(x[q][rt][0], x[q][rt][1]);
+#define DATTRI_TERM(p) _Pragma("unroll") for (int t = 0; t < NT; ++t) acc[rt][t] = split_term<p>(pv[t], xv, acc[rt][t]);
+          DATTRI_TERM(0) DATTRI_TERM(1) DATTRI_TERM(2) DATTRI_TERM(3) DATTRI_TERM(4) DATTRI_TERM(5)
+#undef DATTRI_TERM
+        }
+      }
+      load_x(s + 2, x[q]);
+    }
+  }
+}
+
+// The same product with float32 MFMA and operands loaded straight into
+// registers: for blocks whose split product is not finite.  row0: byte offset
+// in `r` of this lane's row of row tile 0 (rows 16 ld floats apart per tile),
+// rows: bit rt set where that row may be read.
+template <int RT, int NT, class Frag>
+__device__ inline void plain_rows_f32(const rsrc_t r, uint32_t row0, int64_t ld, uint32_t rows, int d,
+                                      int nt, const Frag& P, f32x4 (&acc)[RT][NT]) {
+  const int lane = threadIdx.x & 63, g = lane >> 4;
+  const int nkb = (d + 15) / 16;
+  for (int kb = 0; kb < nkb; ++kb) {
+    const int col = kb * 16 + g * 4;
+    i32x4 x[RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+      x[rt] = load16(r, ((rows >> rt) & 1u) && col < d ? row0 + (uint32_t)((rt * 16 * ld + col) * 4) : kFarOff);
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+      if (t < nt) {
+        const uint8_t* pb;
+        int64_t ps;
+        P(t, &pb, &ps);
+        const i32x4 pf = *(const i32x4*)(pb + kb * ps + lane * 16);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) acc[rt][t] = frag_mma<4>(pf, x[rt], acc[rt][t]);
+      }
+  }
+}
+
 }  // namespace dev
 }  // namespace dattri

@@ -2,6 +2,7 @@
 // cost model that routes each layer (Sec. 3.2 "FLOP-aware routing", App. A.4),
 // launch planning and the C ABI declared in include/dattri.h.
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -115,7 +116,22 @@ Counts layer_counts(const Layer& L, int64_t T, int elt) {
 
 // Kernel launches of a layer's factored route if it were projected alone: the
 // launch plan of a one-layer context decides fused or split form and stages.
-int factored_launches(const dattri_ctx* ctx, const Layer& L) {
+// `memo` (optional) keeps the counts of the sizes already planned in this
+// call: a model's blocks repeat a few layer shapes.
+using LaunchMemo = std::vector<std::pair<std::array<int32_t, 7>, int>>;
+int plan_launches(const dattri_ctx* ctx, const Layer& L);
+int factored_launches(const dattri_ctx* ctx, const Layer& L, LaunchMemo* memo) {
+  if (!memo) return plan_launches(ctx, L);
+  const int32_t al = (((uintptr_t)L.A % 16 == 0) ? 1 : 0) | (((uintptr_t)L.B % 16 == 0) ? 2 : 0) |
+                     (L.A == L.B ? 4 : 0);  // all a one-layer plan reads of the captures besides their sizes
+  const std::array<int32_t, 7> key = {L.d_in, L.d_out, L.k_in, L.k_out, L.n, L.T, al};
+  for (const auto& m : *memo)
+    if (m.first == key) return m.second;
+  const int count = plan_launches(ctx, L);
+  memo->push_back({key, count});
+  return count;
+}
+int plan_launches(const dattri_ctx* ctx, const Layer& L) {
   dattri_ctx one;
   one.dtype = ctx->dtype;
   one.elt = ctx->elt;
@@ -197,7 +213,8 @@ FusedShape fused_shape(const Layer& L, int64_t n, const dattri_cost_model& m) {
 
 // Predicted times (us) of both routes for the layer's capture (n, T).
 // f_launch_us (optional) receives the launch part of the factored time.
-void predict(const dattri_ctx* ctx, const Layer& L, double* f_us, double* m_us, double* f_launch_us = nullptr) {
+void predict(const dattri_ctx* ctx, const Layer& L, double* f_us, double* m_us, double* f_launch_us = nullptr,
+             LaunchMemo* memo = nullptr) {
   const dattri_cost_model& m = ctx->cost;
   const int64_t n = L.n;
   const Counts c = layer_counts(L, L.T, ctx->elt);
@@ -205,7 +222,7 @@ void predict(const dattri_ctx* ctx, const Layer& L, double* f_us, double* m_us, 
     return std::max(flops / (tflops * 1e6), bytes / (gbs * 1e3));  // microseconds
   };
   *f_us = m.call_us + t((double)c.f_flops * n, m.factored_tflops, (double)c.f_bytes * n, m.factored_gbs);
-  const double fl = n > 0 ? factored_launches(ctx, L) * m.launch_us : 0.0;
+  const double fl = n > 0 ? factored_launches(ctx, L, memo) * m.launch_us : 0.0;
   *f_us += fl;
   if (f_launch_us) *f_launch_us = fl;
   if (fused_materialized(L, ctx->elt)) {
@@ -226,12 +243,12 @@ void predict(const dattri_ctx* ctx, const Layer& L, double* f_us, double* m_us, 
           3.0 * chunks * m.launch_us;
 }
 
-dattri_route choose_route(const dattri_ctx* ctx, const Layer& L, dattri_route forced) {
+dattri_route choose_route(const dattri_ctx* ctx, const Layer& L, dattri_route forced, LaunchMemo* memo = nullptr) {
   if (L.mask_size > 0) return DATTRI_ROUTE_MASK;  // gathered from the factors, whatever the request
   if (forced != DATTRI_ROUTE_AUTO) return forced;
   if (!factored_supported(L)) return DATTRI_ROUTE_MATERIALIZED;
   double f, m;
-  predict(ctx, L, &f, &m);
+  predict(ctx, L, &f, &m, nullptr, memo);
   return f <= m ? DATTRI_ROUTE_FACTORED : DATTRI_ROUTE_MATERIALIZED;
 }
 
@@ -251,12 +268,13 @@ const std::vector<dattri_route>& call_routes(const dattri_ctx* ctx, dattri_route
   std::vector<dattri_route> route(ctx->layers.size(), DATTRI_ROUTE_FACTORED);
   std::vector<double> f_work(ctx->layers.size(), 0.0), m_us(ctx->layers.size(), 0.0);
   bool any_factored = false;
+  LaunchMemo memo;
   for (size_t l = 0; l < ctx->layers.size(); ++l) {
     const Layer& L = ctx->layers[l];
-    route[l] = choose_route(ctx, L, forced);
+    route[l] = choose_route(ctx, L, forced, &memo);
     if (forced == DATTRI_ROUTE_AUTO && route[l] == DATTRI_ROUTE_MATERIALIZED && factored_supported(L)) {
       double f, fl;
-      predict(ctx, L, &f, &m_us[l], &fl);
+      predict(ctx, L, &f, &m_us[l], &fl, &memo);
       f_work[l] = f - fl;
     }
     any_factored = any_factored || route[l] == DATTRI_ROUTE_FACTORED;
@@ -273,8 +291,7 @@ const std::vector<dattri_route>& call_routes(const dattri_ctx* ctx, dattri_route
 // The split form serves every factored group when the fused kernel would have
 // fewer than kSplitMinFusedItems work items.
 constexpr int64_t kSplitMinFusedItems = 1024;
-constexpr int64_t kSplitTargetItems = 1024;   // stage-1 workgroups aimed for
-constexpr int64_t kContractTargetItems = 512; // stage-2 workgroups aimed for
+constexpr int kCus = 256;                     // MI355X compute units
 constexpr int64_t kGProjTargetBlocks = 1024;  // G-projection workgroups aimed for
 
 dattri_status check_captures(const dattri_ctx* ctx, int32_t* n_out) {
@@ -545,19 +562,46 @@ dattri_status dattri::build_plan(const dattri_ctx* ctx, dattri_route forced, Pla
     struct Pending { int a_op, b_op; };
     std::vector<Pending> pend;
     const size_t op0 = P.sops.size();
+    // Groups kept apart for the fused kernel's registers share one pass over
+    // their input block here while the bf16 direct-load stream holds their
+    // tiles (k = 64: q with k, gate with up): 11.8 -> 10.9 GB through the CUs
+    // per 4 Qwen-shaped blocks of 32 x 512 rows.
+    std::vector<std::vector<int>> sgroups;
+    std::vector<int> sg_tiles;
+    std::vector<char> sg_al;
     for (size_t g : split_groups) {
       const Layer& H = ctx->layers[group_layers[g][0]];
+      size_t m = sgroups.size();
+      if (elt == 2 && gshape[g].aligned)
+        for (size_t i = 0; i < sgroups.size() && m == sgroups.size(); ++i) {
+          const Layer& I = ctx->layers[sgroups[i][0]];
+          if (sg_al[i] && I.A == H.A && I.d_in == H.d_in && I.T == H.T && I.lengths == H.lengths &&
+              sg_tiles[i] + gshape[g].na <= kMaxGroupTiles)
+            m = i;
+        }
+      if (m == sgroups.size()) {
+        sgroups.push_back({});
+        sg_tiles.push_back(0);
+        sg_al.push_back(gshape[g].aligned != 0);
+      }
+      sgroups[m].insert(sgroups[m].end(), group_layers[g].begin(), group_layers[g].end());
+      sg_tiles[m] += gshape[g].na;
+    }
+    for (const std::vector<int>& members : sgroups) {
+      const Layer& H = ctx->layers[members[0]];
       const int rows = n * H.T;
       SplitOp A;
       std::memset(&A, 0, sizeof(A));
       A.X = H.A;
       A.rows = rows;
+      A.lengths = H.lengths;
+      A.T = H.T;
       A.ld = H.d_in;
       A.aligned = ((uintptr_t)H.A % 16 == 0) && (H.d_in * elt) % 16 == 0;
       std::vector<SplitOp> Bs;
       int na = 0;
       const int a_op = (int)P.sops.size();
-      for (int li : group_layers[g]) {
+      for (int li : members) {
         const Layer& L = ctx->layers[li];
         const int mt = tiles16(L.k_in);
         for (int t = 0; t < mt; ++t) {
@@ -569,6 +613,8 @@ dattri_status dattri::build_plan(const dattri_ctx* ctx, dattri_route forced, Pla
         std::memset(&B, 0, sizeof(B));
         B.X = L.B;
         B.rows = rows;
+        B.lengths = L.lengths;
+        B.T = L.T;
         B.ld = L.d_out;
         B.aligned = ((uintptr_t)L.B % 16 == 0) && (L.d_out * elt) % 16 == 0;
         B.nt = tiles16(L.k_out);
@@ -596,36 +642,58 @@ dattri_status dattri::build_plan(const dattri_ctx* ctx, dattri_route forced, Pla
       P.sops.push_back(A);
       for (const SplitOp& B : Bs) P.sops.push_back(B);
     }
-    // slab width: about kSplitTargetItems stage-1 workgroups in total
-    int64_t work = 0;
-    for (size_t o = op0; o < P.sops.size(); ++o)
-      work += (int64_t)((P.sops[o].rows + split_rows_of(split_nt_instance(P.sops[o].nt)) - 1) /
-                        split_rows_of(split_nt_instance(P.sops[o].nt))) * P.sops[o].ld;
-    int64_t slab = (work + kSplitTargetItems - 1) / kSplitTargetItems;
-    slab = std::max<int64_t>(kSplitSlabQuantum, (slab + kSplitSlabQuantum - 1) / kSplitSlabQuantum * kSplitSlabQuantum);
+    // Slab width.  A call of W bytes cut into items of s bytes over the chip's
+    // workgroup slots (one per CU for bf16, three for float32) ends about W /
+    // slots + s / 2 behind its start (half an item of tail), and every item
+    // adds a fixed cost c, in bytes of streaming: its prologue and its
+    // projected rows written and read again.  The sum is least at s =
+    // sqrt(2 c W / slots).
+    double work = 0.0, fixed = 0.0;
+    const int srows = split_stream_rows(elt), slots = elt == 2 ? kCus : 3 * kCus;
+    for (size_t o = op0; o < P.sops.size(); ++o) {
+      const SplitOp& O = P.sops[o];
+      const double bytes = (double)O.rows * O.ld * elt;
+      work += bytes;
+      fixed += bytes * ((elt == 2 ? 65536.0 : 24576.0) + 2.0 * srows * O.nt * 16 * 4);
+    }
+    const double item_bytes = work > 0 ? std::sqrt(2.0 * (fixed / work) * work / slots) : 1.0;
+    for (size_t o = op0; o < P.sops.size(); ++o) {
+      SplitOp& O = P.sops[o];
+      const double row_bytes = (double)std::min(O.rows, srows) * O.ld * elt;
+      const int64_t cap = std::max<int64_t>(1, O.ld / kSplitSlabQuantum);
+      const int64_t want = std::min<int64_t>(cap, std::max<int64_t>(1, std::llround(row_bytes / item_bytes)));
+      O.slab_cols = (int32_t)(((O.ld + want - 1) / want + kSplitSlabQuantum - 1) / kSplitSlabQuantum * kSplitSlabQuantum);
+      O.n_slabs = (O.ld + O.slab_cols - 1) / O.slab_cols;
+    }
     size_t proj_floats = 0;
     for (size_t o = op0; o < P.sops.size(); ++o) {
       SplitOp& O = P.sops[o];
-      O.slab_cols = (int32_t)std::min<int64_t>(slab, (O.ld + kSplitSlabQuantum - 1) / kSplitSlabQuantum * kSplitSlabQuantum);
-      O.n_slabs = (O.ld + O.slab_cols - 1) / O.slab_cols;
       O.out_base = (int64_t)proj_floats;
-      proj_floats += (size_t)O.n_slabs * O.rows * O.nt * 16;
+      O.out_ld = O.nt * 16;
+      proj_floats += (size_t)O.n_slabs * O.rows * O.out_ld;
     }
-    // token chunks: about kContractTargetItems stage-2 workgroups in total
-    const int64_t per_chunk = (int64_t)pend.size() * std::max(n, 1);
-    const int64_t want_chunks = std::max<int64_t>(1, (kContractTargetItems + per_chunk - 1) / per_chunk);
+    // Contraction: one workgroup per (layer, example) unless that leaves most
+    // CUs idle over long sequences (then chunks of 512 tokens), and at most
+    // 65536 tokens per chunk (byte offsets inside a chunk stay below 2 GiB).
+    // It adds the slabs on load; where few workgroups would each add many, or
+    // projected rows are kept for a later pass, they are added into slab 0 by
+    // a launch of their own first.
+    const int64_t con_wgs = (int64_t)pend.size() * std::max(n, 1);
     size_t spart_floats = 0;
+    std::vector<char> sum_op(P.sops.size(), 0);
     for (size_t i = 0; i < pend.size(); ++i) {
       ContractTask& C = P.ctasks[P.ctasks.size() - pend.size() + i];
       const SplitOp& A = P.sops[pend[i].a_op];
       const SplitOp& B = P.sops[pend[i].b_op];
-      // slabs are summed into slab 0 before the contraction
-      C.a_base = A.out_base; C.a_ld = A.nt * 16; C.a_slabs = 1;
-      C.b_base = B.out_base; C.b_ld = B.nt * 16; C.b_slabs = 1;
-      const int64_t tc = (C.T + want_chunks - 1) / want_chunks;
-      C.tok_chunk = (int32_t)std::max<int64_t>(64, (tc + 31) / 32 * 32);
+      const bool pre = rows || (con_wgs < kCus && A.n_slabs + B.n_slabs > 8);
+      if (pre) sum_op[pend[i].a_op] = sum_op[pend[i].b_op] = 1;
+      C.a_base = A.out_base; C.a_ld = A.out_ld; C.a_slabs = A.n_slabs;
+      C.b_base = B.out_base; C.b_ld = B.out_ld; C.b_slabs = B.n_slabs;
+      C.tok_chunk = con_wgs < kCus / 2 && C.T > 1024 ? 512 : std::max(std::min(C.T, 65536), 1);
       C.n_tchunks = std::max(1, (C.T + C.tok_chunk - 1) / C.tok_chunk);
       P.split_max_tchunks = std::max(P.split_max_tchunks, C.n_tchunks);
+      P.split_na = std::max(P.split_na, tiles16(C.k_in));
+      P.split_nb = std::max(P.split_nb, tiles16(C.k_out));
       if (C.n_tchunks > 1) {
         const int ki16 = tiles16(C.k_in) * 16, ko16 = tiles16(C.k_out) * 16;
         C.partial_base = (int64_t)spart_floats;
@@ -644,37 +712,67 @@ dattri_status dattri::build_plan(const dattri_ctx* ctx, dattri_route forced, Pla
         P.split_max_out = std::max(P.split_max_out, C.k_in * C.k_out);
       }
     }
+    for (size_t i = 0; i < pend.size(); ++i) {  // ops summed beforehand hold one slab
+      ContractTask& C = P.ctasks[P.ctasks.size() - pend.size() + i];
+      if (sum_op[pend[i].a_op]) C.a_slabs = 1;
+      if (sum_op[pend[i].b_op]) C.b_slabs = 1;
+    }
     P.proj_bytes = proj_floats * 4;
     P.spart_bytes = spart_floats * 4;
     for (size_t o = op0; o < P.sops.size(); ++o) {
       const SplitOp& O = P.sops[o];
-      if (O.n_slabs <= 1 || O.rows == 0) continue;
+      if (!sum_op[o] || O.n_slabs <= 1 || O.rows == 0) continue;
       SlabSumTask T;
       std::memset(&T, 0, sizeof(T));
       T.base = O.out_base;
-      T.n4 = (int64_t)O.rows * O.nt * 4;
+      T.n4 = (int64_t)O.rows * O.out_ld / 4;
       T.stride4 = T.n4;
       T.n_slabs = O.n_slabs;
       P.slabsum.push_back(T);
       P.slabsum_max_n4 = std::max(P.slabsum_max_n4, T.n4);
     }
-    // One launch per kernel instance (aligned, tiles).  Inside a launch, the
-    // items of one op run on one XCD, so its projection map is fetched into
-    // that XCD's L2 once and read there by all its row blocks: ops (units of
-    // ops over the same block) are dealt, costliest first, to the
-    // least-loaded of 8 per-XCD queues and the queues interleaved (workgroup i
-    // runs on XCD i mod 8); short queues are padded with items that exit at
-    // once.  Launches with fewer than 4 units per XCD keep the items in op
-    // order over all XCDs (a few wide layers would otherwise leave XCDs idle).
+    // Aligned float32 ops of more tiles than the stream holds: one op per run
+    // of tiles over the same block, side by side below.
+    if (elt == 4)
+      for (size_t o = op0, end = P.sops.size(); o < end; ++o) {
+        if (!P.sops[o].aligned || P.sops[o].nt <= kSplitMaxTilesF32) continue;
+        const SplitOp whole = P.sops[o];
+        P.sops[o].nt = kSplitMaxTilesF32;
+        for (int t0 = kSplitMaxTilesF32; t0 < whole.nt; t0 += kSplitMaxTilesF32) {
+          SplitOp Q = whole;
+          Q.nt = std::min(kSplitMaxTilesF32, whole.nt - t0);
+          Q.out_base += 16 * t0;
+          for (int t = 0; t < Q.nt; ++t) {
+            Q.ptile[t] = whole.ptile[t0 + t];
+            Q.ptile_local[t] = whole.ptile_local[t0 + t];
+            Q.ptile_nt[t] = whole.ptile_nt[t0 + t];
+          }
+          P.sops.push_back(Q);
+        }
+      }
+    // One launch for every aligned op (the kernel takes any tile count), one
+    // per tile count for unaligned ones.  Inside a launch, the items of an
+    // op run on one XCD (workgroup i runs on XCD i mod 8), so its projection
+    // map crosses into one L2 and not into all eight:
+    // over 8 XCDs the maps of 96 Pythia-410M-shaped float32 layers, k = 64, add
+    // up to 0.8 GB beside 4.1 GB of rows.  Ops over the same block (the input of
+    // layers kept apart, e.g. q/k/v) go together, interleaved per item, and
+    // share its rows through that L2.  Such units are dealt, costliest first, to
+    // the least loaded of 8 queues; a unit above an eighth of a queue is cut
+    // into runs of row blocks first, so that few wide layers still fill the
+    // chip evenly.  The queues are interleaved, short ones padded with items
+    // that exit at once.
     for (int al = 1; al >= 0; --al)
       for (int nt : {1, 2, 4, 8}) {
+        if (al && nt > 1) break;
         std::vector<size_t> ops;
+        double total = 0.0;
         for (size_t o = op0; o < P.sops.size(); ++o)
-          if (P.sops[o].aligned == al && split_nt_instance(P.sops[o].nt) == nt) ops.push_back(o);
+          if (P.sops[o].aligned == al && (al || split_nt_instance(P.sops[o].nt) == nt)) {
+            ops.push_back(o);
+            total += (double)P.sops[o].rows * P.sops[o].ld;
+          }
         if (ops.empty()) continue;
-        // ops that stream the same block (the input of layers kept apart, e.g.
-        // q/k/v) form a unit whose items are interleaved per (row block,
-        // slab), so the side-by-side workgroups share its rows through L2
         std::vector<std::vector<size_t>> units;
         for (size_t o : ops) {
           const SplitOp& O = P.sops[o];
@@ -688,41 +786,49 @@ dattri_status dattri::build_plan(const dattri_ctx* ctx, dattri_route forced, Pla
           if (u == units.size()) units.push_back({});
           units[u].push_back(o);
         }
-        const int rows_wg = split_rows_of(nt);
-        const int first = (int)P.sitems.size();
-        if (units.size() < (size_t)4 * kXcds) {
-          // too few units to keep every XCD busy with whole units: items in op
-          // order, spread over all XCDs
-          for (size_t o : ops) {
-            const SplitOp& O = P.sops[o];
-            const int rblocks = (O.rows + rows_wg - 1) / rows_wg;
-            for (int rb = 0; rb < rblocks; ++rb)
-              for (int sl = 0; sl < O.n_slabs; ++sl) P.sitems.push_back({(int)o, rb, sl, 0});
+        for (const auto& u : units) P.sops[u[0]].once = u.size() == 1;
+        const int rows_wg = al ? split_stream_rows(elt) : split_rows_of(nt);
+        struct Piece { size_t unit; int rb0, rb1; double cost, item; };
+        std::vector<Piece> pieces;
+        for (size_t u = 0; u < units.size(); ++u) {
+          const SplitOp& O = P.sops[units[u][0]];
+          const int rbs = (O.rows + rows_wg - 1) / rows_wg;
+          const double cost = (double)O.ld * O.rows * (double)units[u].size();
+          const int cuts = (int)std::min<int64_t>(std::max(rbs, 1), (int64_t)std::ceil(cost / (total / 64.0)));
+          for (int c = 0; c < cuts; ++c) {
+            const int rb0 = (int)((int64_t)rbs * c / cuts), rb1 = (int)((int64_t)rbs * (c + 1) / cuts);
+            if (rb1 > rb0) pieces.push_back({u, rb0, rb1, cost * (rb1 - rb0) / rbs, (double)O.slab_cols});
           }
-          P.slaunches.push_back({elt, al, nt, first, (int)P.sitems.size() - first});
-          continue;
         }
-        auto cost = [&](const std::vector<size_t>& u) {  // every op's workgroups stream the block
-          return (double)P.sops[u[0]].rows * P.sops[u[0]].ld * (double)u.size();
-        };
-        std::stable_sort(units.begin(), units.end(),
-                         [&](const std::vector<size_t>& a, const std::vector<size_t>& b) { return cost(a) > cost(b); });
-        std::vector<std::vector<SplitItem>> q(kXcds);
+        std::stable_sort(pieces.begin(), pieces.end(), [](const Piece& a, const Piece& b) { return a.cost > b.cost; });
+        std::vector<Piece> q[kXcds];
         double load[kXcds] = {0};
-        for (const auto& u : units) {
-          const SplitOp& O = P.sops[u[0]];
+        for (const Piece& p : pieces) {
           const int x = (int)(std::min_element(load, load + kXcds) - load);
-          const int rblocks = (O.rows + rows_wg - 1) / rows_wg;
-          for (int rb = 0; rb < rblocks; ++rb)
-            for (int sl = 0; sl < O.n_slabs; ++sl)
-              for (size_t o : u) q[x].push_back({(int)o, rb, sl, 0});
-          load[x] += cost(u);
+          q[x].push_back(p);
+          load[x] += p.cost;
         }
         size_t len = 0;
-        for (const auto& v : q) len = std::max(len, v.size());
-        for (size_t i = 0; i < len; ++i)
-          for (int x = 0; x < kXcds; ++x)
-            P.sitems.push_back(i < q[x].size() ? q[x][i] : SplitItem{-1, 0, 0, 0});
+        for (int x = 0; x < kXcds; ++x) {
+          // widest items first: the queue ends on its cheapest ones
+          std::stable_sort(q[x].begin(), q[x].end(), [](const Piece& a, const Piece& b) { return a.item > b.item; });
+          size_t m = 0;
+          for (const Piece& p : q[x])
+            m += (size_t)(p.rb1 - p.rb0) * P.sops[units[p.unit][0]].n_slabs * units[p.unit].size();
+          len = std::max(len, m);
+        }
+        const int first = (int)P.sitems.size();
+        P.sitems.resize(P.sitems.size() + len * kXcds, SplitItem{-1, 0, 0, 0});
+        for (int x = 0; x < kXcds; ++x) {
+          SplitItem* at = P.sitems.data() + first + x;
+          for (const Piece& p : q[x])
+            for (int rb = p.rb0; rb < p.rb1; ++rb)
+              for (int sl = 0; sl < P.sops[units[p.unit][0]].n_slabs; ++sl)
+                for (size_t o : units[p.unit]) {
+                  *at = {(int)o, rb, sl, 0};
+                  at += kXcds;
+                }
+        }
         const int count = (int)P.sitems.size() - first;
         if (count) P.slaunches.push_back({elt, al, nt, first, count});
       }
@@ -930,8 +1036,8 @@ dattri_status dattri::build_plan(const dattri_ctx* ctx, dattri_route forced, Pla
     for (const SplitRows& R : split_rows) {
       const SplitOp& A = P.sops[R.a_op];
       const SplitOp& B = P.sops[R.b_op];
-      P.row_srcs.push_back({R.layer, 0, P.off_proj + (size_t)A.out_base * 4, A.nt * 16, R.a_col0});
-      P.row_srcs.push_back({R.layer, 1, P.off_proj + (size_t)B.out_base * 4, B.nt * 16, 0});
+      P.row_srcs.push_back({R.layer, 0, P.off_proj + (size_t)A.out_base * 4, A.out_ld, R.a_col0});
+      P.row_srcs.push_back({R.layer, 1, P.off_proj + (size_t)B.out_base * 4, B.out_ld, 0});
     }
     for (size_t l = 0; l < ctx->layers.size(); ++l)
       if (route[l] == DATTRI_ROUTE_MATERIALIZED) P.mat_layers.push_back((int)l);
@@ -1257,8 +1363,8 @@ dattri_status dattri::run_plan(dattri_ctx* ctx, const Plan& P, void* phi, dattri
                             P.slabsum_max_n4, proj, s));
   float* spart = (float*)(ws + P.off_spart);
   if (!P.ctasks.empty())
-    HIP_TRY(launch_split_contract(d_ctasks, (int)P.ctasks.size(), n, P.split_max_tchunks, proj, spart,
-                                  phi, phi_bf16, ld_phi, s));
+    HIP_TRY(launch_split_contract(P.split_na, P.split_nb, d_ctasks, (int)P.ctasks.size(), n, P.split_max_tchunks,
+                                  proj, spart, phi, phi_bf16, ld_phi, s));
   if (!P.stasks.empty())
     HIP_TRY(launch_reduce((const ReduceTask*)(tab + P.off_stasks), (int)P.stasks.size(), n,
                           P.split_max_out, spart, phi, phi_bf16, ld_phi, s));
