@@ -190,7 +190,111 @@ __device__ inline void ghost_tile_dma(const GhostEntry& E, const GhostTile& tl, 
   stage_barrier();
 }
 
-// Register-staged form (float32 entries, unaligned rows): stages of 128 bytes
+// float32 form of a tile's two Grams (entries with E.dma set): stages of 32
+// features, one K = 32 step of bf16 MFMA on values split into three bf16 terms
+// (split3; 6 MFMA of 16 cycles per 16 x 16 x 32 product where float32 MFMA
+// takes 8 of 32).  Each thread loads 32 bytes of two rows per side into
+// registers, one stage ahead, splits them once and writes 16 bytes to each of
+// the hi, mid and lo planes in LDS (64 bytes per row and plane, swizzled as in
+// the direct-load form), from where the four waves read operands: a value is
+// split once per tile and used by 128 products.  Two workgroups share a CU, so
+// one's splitting runs beside the other's MFMA.  live: this wave's 64 x 64
+// block has rows of both sides inside their lengths (others only stage).
+// Bound by the issue of 96 MFMA and about 220 vector instructions per stage
+// and wave.
+constexpr int kGhPlane = kGhRows * 64;  // bytes of one side's plane
+
+__device__ inline void ghost_tile_split(const GhostEntry& E, const GhostTile& tl, bool live, uint8_t* lds,
+                                        f32x4 (&acc)[2][4][4]) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int g = lane >> 4, m16 = lane & 15, wm = wave >> 1, wn = wave & 1;
+  // this thread's rows (tid / 4 and 64 further) and 8-feature piece tid % 4 of
+  // each side; row index relative to the tile's first example, where the
+  // descriptors start
+  const int pc = tid & 3;
+  int rel[2][2];
+  bool ok[2][2];
+  rsrc_t rA[2], rB[2];
+#pragma unroll
+  for (int side = 0; side < 2; ++side) {
+    const int R0 = (side ? tl.ct : tl.rt) * kGhRows;
+    const int Tp = side ? E.Tp2 : E.Tp1, T = side ? E.T2 : E.T1, n = side ? E.n2 : E.n1;
+    const int32_t* len = side ? E.len2 : E.len1;
+    const int e0 = R0 / Tp;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int R = R0 + (tid >> 2) + 64 * t, e = R / Tp, tt = R - e * Tp;
+      int t_eff = T;
+      if (e < n && len) t_eff = min(max(len[e], 0), T);
+      ok[side][t] = e < n && tt < t_eff;
+      rel[side][t] = (e - e0) * T + tt;
+    }
+    const uint8_t* a = (const uint8_t*)(side ? E.A2 : E.A1);
+    const uint8_t* b = (const uint8_t*)(side ? E.B2 : E.B1);
+    const int64_t ra = (int64_t)(n - e0) * T * E.d_in * 4, rb = (int64_t)(n - e0) * T * E.d_out * 4;
+    rA[side] = make_rsrc(a + (int64_t)e0 * T * E.d_in * 4, (uint32_t)min<int64_t>(ra, kOOB));
+    rB[side] = make_rsrc(b + (int64_t)e0 * T * E.d_out * 4, (uint32_t)min<int64_t>(rb, kOOB));
+  }
+  const int nk0 = (E.d_in + 31) / 32, ns = nk0 + (E.d_out + 31) / 32;
+  i32x4 x[2][2][2];  // [side][row][half]
+  auto load = [&](int st) {
+    const bool p = st >= nk0;
+    const int col = (p ? st - nk0 : st) * 32 + pc * 8, d = p ? E.d_out : E.d_in;
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+      const rsrc_t r = p ? rB[side] : rA[side];
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          x[side][t][h] = load16(r, ok[side][t] && col + 4 * h < d
+                                        ? (uint32_t)(((int64_t)rel[side][t] * d + col + 4 * h) * 4)
+                                        : kOOB);
+    }
+  };
+  auto put = [&] {
+#pragma unroll
+    for (int side = 0; side < 2; ++side)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const int row = (tid >> 2) + 64 * t;
+        const Split3 v = split3(x[side][t][0], x[side][t][1]);
+        uint8_t* w = lds + side * 3 * kGhPlane + row * 64 + ((pc ^ gswz16(row)) << 4);
+        *(bf16x8*)w = v.hi;
+        *(bf16x8*)(w + kGhPlane) = v.mid;
+        *(bf16x8*)(w + 2 * kGhPlane) = v.lo;
+      }
+  };
+  auto get = [&](int side, int row) {
+    const uint8_t* w = lds + side * 3 * kGhPlane + row * 64 + ((g ^ gswz16(row)) << 4);
+    return Split3{*(const bf16x8*)w, *(const bf16x8*)(w + kGhPlane), *(const bf16x8*)(w + 2 * kGhPlane)};
+  };
+  auto multiply = [&](f32x4 (&c)[4][4]) {
+    Split3 b[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) b[j] = get(1, wn * 64 + 16 * j + m16);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const Split3 a = get(0, wm * 64 + 16 * i + m16);
+#define DATTRI_TERM(p) _Pragma("unroll") for (int j = 0; j < 4; ++j) c[i][j] = split_term<p>(a, b[j], c[i][j]);
+      DATTRI_TERM(0) DATTRI_TERM(1) DATTRI_TERM(2) DATTRI_TERM(3) DATTRI_TERM(4) DATTRI_TERM(5)
+#undef DATTRI_TERM
+    }
+  };
+  load(0);
+  auto stage = [&](int st, f32x4 (&c)[4][4]) {
+    lds_barrier();  // the previous stage's operands are read
+    put();
+    load(st + 1);  // past the last stage: columns past d, zeros never used
+    lds_barrier();
+    if (live) multiply(c);
+  };
+  for (int st = 0; st < nk0; ++st) stage(st, acc[0]);
+  for (int st = nk0; st < ns; ++st) stage(st, acc[1]);
+}
+
+// Register-staged form (unaligned rows; float32 tiles whose split products are
+// not finite): stages of 128 bytes
 // of features per row are double-buffered in LDS (rows XOR-swizzled by
 // 16-byte chunk) and the next stage is prefetched into registers while the
 // current one is multiplied.  smem: 2 x 2 x 128 x 128 bytes.
@@ -296,10 +400,65 @@ __global__ __launch_bounds__(256, 2) void ghost_kernel(const GhostEntry* __restr
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc[p][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  if (ELT == 2 && E.dma)  // uniform
-    ghost_tile_dma(E, tl, &smem[0][0][0], acc);
-  else
-    ghost_tile_reg<ELT>(E, tl, smem, acc);
+  // rows of both sides inside their examples' lengths: a tile without any on
+  // one side is zero
+  bool any[2][2] = {{true, true}, {true, true}};  // [side][64-row half]
+  if (E.len1 || E.len2) {  // uniform
+    uint32_t bits = 0;
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+      const int Tp = side ? E.Tp2 : E.Tp1, T = side ? E.T2 : E.T1, n = side ? E.n2 : E.n1;
+      const int32_t* len = side ? E.len2 : E.len1;
+      const int row = threadIdx.x & (kGhRows - 1);
+      const int R = (side ? tl.ct : tl.rt) * kGhRows + row, e = R / Tp, t = R - e * Tp;
+      int t_eff = T;
+      if (e < n && len) t_eff = min(max(len[e], 0), T);
+      if (e < n && t < t_eff) bits |= 1u << (2 * side + (row >> 6));
+    }
+    uint32_t* w = (uint32_t*)&smem[0][0][0];
+    if (threadIdx.x < 4) w[threadIdx.x] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if ((bits >> i) & 1u) w[i] = 1u;  // every writer writes the same value
+    __syncthreads();
+    any[0][0] = w[0]; any[0][1] = w[1]; any[1][0] = w[2]; any[1][1] = w[3];
+    __syncthreads();
+  }
+  const bool some = (any[0][0] || any[0][1]) && (any[1][0] || any[1][1]);
+  if (some) {  // uniform
+    if (ELT == 2 && E.dma) {
+      ghost_tile_dma(E, tl, &smem[0][0][0], acc);
+    } else if (ELT == 4 && E.dma) {
+      ghost_tile_split(E, tl, any[0][wm] && any[1][wn], &smem[0][0][0], acc);
+      bool bad = false;
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) bad = bad || not_finite(acc[p][i][j]);
+      uint32_t* w = (uint32_t*)&smem[0][0][0];
+      __syncthreads();
+      if (threadIdx.x == 0) *w = 0u;
+      __syncthreads();
+      if (bad) *w = 1u;
+      __syncthreads();
+      const bool redo = *w != 0u;
+      __syncthreads();
+      if (redo) {  // infinities or NaN among the inputs, or an overflow: float32 products
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[p][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        ghost_tile_reg<ELT>(E, tl, smem, acc);
+      }
+    } else {
+      ghost_tile_reg<ELT>(E, tl, smem, acc);
+    }
+  }
 
   // Hadamard product of the two Grams, summed per 16 x 16 block (lanes hold
   // the same (row, column) of both accumulators)
@@ -318,39 +477,51 @@ __global__ __launch_bounds__(256, 2) void ghost_kernel(const GhostEntry* __restr
     }
 }
 
-// K[I][J] (diag: out[I]) = sum over entries, in order, of the block sums of
-// segment (i, j) = (I - out0, J) (diag: (I - out0, I - out0)) of every entry
-// holding that pair: blocks [i*Tp1/16, (i+1)*Tp1/16) x [j*Tp2/16, ...).  One
-// workgroup per output; thread t sums blocks t, t+256, ... of each entry in
-// order, then a fixed tree.
-__global__ __launch_bounds__(256) void ghost_reduce_kernel(const GhostEntry* __restrict__ entries,
+// K[I][J] (diag: out[I]) = sum over entries of the block sums of segment
+// (i, j) = (I - out0, J) (diag: (I - out0, I - out0)) of every entry holding
+// that pair: blocks [i*Tp1/16, (i+1)*Tp1/16) x [j*Tp2/16, ...).  One workgroup
+// of 16 waves per output: wave w sums the entries w, w + 16, ... in order, lane
+// t the blocks t, t + 64, ... of each, then a fixed tree over lanes and waves.
+// (A whole workgroup per entry, one entry after another, spent 0.12 ms on the
+// latencies of 48 entries; 0.01 ms with 16 entries at a time.)
+constexpr int kGhRedWaves = 16;
+
+__global__ __launch_bounds__(64 * kGhRedWaves) void ghost_reduce_kernel(const GhostEntry* __restrict__ entries,
                                                            int n_entries, const float* __restrict__ parts,
                                                            int n_cols, float* __restrict__ K, int64_t ld,
                                                            int diag, int accumulate) {
-  __shared__ float red[256];
-  const int cell = blockIdx.x;
+  __shared__ float red[kGhRedWaves];
+  const int cell = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int I = diag ? cell : cell / n_cols, J = diag ? cell : cell % n_cols;
   float s = 0.f;
-  for (int e = 0; e < n_entries; ++e) {
+  for (int e = wave; e < n_entries; e += kGhRedWaves) {
     const GhostEntry& E = entries[e];
     const int i = I - E.out0, j = diag ? i : J;
     if (i < 0 || i >= E.n1 || j < 0 || j >= E.n2) continue;
     const int rb = E.Tp1 / 16, cb = E.Tp2 / 16;
     const int nblk = rb * cb;
-    for (int b = threadIdx.x; b < nblk; b += 256) {
-      const int br = i * rb + b / cb, bc = j * cb + b % cb;
-      s += parts[E.part_off + (int64_t)br * E.nbc + bc];
+    const float* p = parts + E.part_off + (int64_t)i * rb * E.nbc + j * cb;
+    for (int b0 = lane; b0 < nblk; b0 += 4 * 64) {  // four loads in flight per lane
+      float v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int b = b0 + 64 * u;
+        v[u] = b < nblk ? p[(int64_t)(b / cb) * E.nbc + b % cb] : 0.f;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) s += v[u];
     }
   }
-  red[threadIdx.x] = s;
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
+  if (lane == 0) red[wave] = s;
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
   if (threadIdx.x == 0) {
+    float t = 0.f;
+#pragma unroll
+    for (int w = 0; w < kGhRedWaves; ++w) t += red[w];
     float* dst = diag ? &K[I] : &K[(int64_t)I * ld + J];
-    *dst = accumulate ? *dst + red[0] : red[0];
+    *dst = accumulate ? *dst + t : t;
   }
 }
 
@@ -369,7 +540,7 @@ hipError_t launch_ghost_reduce(const GhostEntry* entries, int n_entries, const f
                                hipStream_t s) {
   const int cells = diag ? n_rows : n_rows * n_cols;
   if (cells <= 0) return hipSuccess;
-  hipLaunchKernelGGL(ghost_reduce_kernel, dim3(cells), dim3(256), 0, s, entries, n_entries, parts, n_cols,
+  hipLaunchKernelGGL(ghost_reduce_kernel, dim3(cells), dim3(64 * kGhRedWaves), 0, s, entries, n_entries, parts, n_cols,
                      K, ld, diag, accumulate);
   return hipGetLastError();
 }

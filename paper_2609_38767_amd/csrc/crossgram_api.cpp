@@ -164,12 +164,13 @@ dattri_status check_pair(const dattri_ctx* a, const dattri_ctx* b) {
   return DATTRI_OK;
 }
 
-// Whether the factorized kernel can stream an entry's token rows by direct
-// loads: bf16, 16-byte aligned rows, and the rows one tile touches (at most
-// 128 + 2 T from the tile's first example) within 32-bit byte offsets.
+// Whether the factorized kernel can address an entry's token rows through one
+// descriptor per tile and side (bf16: direct loads; float32: the split form):
+// 16-byte aligned rows, and the rows one tile touches (at most 128 + 2 T from
+// the tile's first example) within 32-bit byte offsets.
 bool ghost_dma_ok(const GhostEntry& E, int elt) {
   const int64_t d = std::max(E.d_in, E.d_out), lim = (int64_t)kOOBLimit;
-  return elt == 2 && E.aligned && (128 + 2 * (int64_t)E.T1) * d * elt < lim &&
+  return E.aligned && (128 + 2 * (int64_t)E.T1) * d * elt < lim &&
          (128 + 2 * (int64_t)E.T2) * d * elt < lim;
 }
 
