@@ -16,8 +16,8 @@
 // stat_reduce_kernel fixed-order sum of partial blocks into the state.
 // eigen_kernel       cyclic Jacobi in float64, one workgroup per matrix: each
 //                    round applies n/2 rotations on disjoint index pairs (the
-//                    round-robin ordering), rows then columns of the LDS copy,
-//                    and accumulates the rotations into V.
+//                    round-robin ordering) to both sides of the LDS copy and
+//                    accumulates the rotations into V.
 // ekfac_kernel       sum over training rows of (Q_A^T Psi Q_G)^2 (float32 MFMA,
 //                    one wave per row).
 // precond_kernel     Q_A [(Q_A^T Psi Q_G) / (E + delta)] Q_G^T per query block.
@@ -460,13 +460,34 @@ __device__ inline double wave_sum(double v) {
   return v;
 }
 
-__global__ __launch_bounds__(256) void eigen_kernel(const EigTask* __restrict__ tasks,
-                                                    uint8_t* __restrict__ state) {
+// 1 / sqrt(y) for y in [1, 2], to float64 rounding: the hardware estimate and
+// two Newton steps.
+__device__ inline double rsqrt_near(double y) {
+  double r = __builtin_amdgcn_rsq(y);
+  r = r * fma(-0.5 * y * r, r, 1.5);
+  return r * fma(-0.5 * y * r, r, 1.5);
+}
+
+// Workgroup of 16 waves per matrix.  A round is two phases: 32 threads form the
+// rotations; then thread (i, j) of the 32 x 32 grid applies both sides to the
+// 2 x 2 block of pairs i and j (A <- J^T A J in one pass) and the rotation of
+// pair j to rows i and i + 32 of V.  The tangent of a rotation comes from
+// hardware estimates (about 2^-24: the rotated a_pq is then that small a part of
+// itself instead of zero, which the quadratic convergence does not notice),
+// its cosine to float64 rounding with s = t c, so the rotations are orthogonal
+// to rounding.  Bound by the LDS port: 128 KiB per round of k = 64 (about 1000
+// of about 2600 cycles, the rest being the rotations' latency and two
+// barriers).  56 matrices of 64 x 64: 0.58 ms (1.17 ms with four waves,
+// rows and columns updated in separate phases, and division and square root
+// to full precision in each rotation).
+constexpr int kEigThreads = 1024;
+
+__global__ __launch_bounds__(kEigThreads) void eigen_kernel(const EigTask* __restrict__ tasks,
+                                                            uint8_t* __restrict__ state) {
   __shared__ double Am[kCurvMaxK * kEigLd];
   __shared__ double Vm[kCurvMaxK * kEigLd];
   __shared__ double rc[kCurvMaxK / 2], rs[kCurvMaxK / 2];
-  __shared__ int rp[kCurvMaxK / 2], rq[kCurvMaxK / 2];
-  __shared__ double red[2][4];
+  __shared__ double red[2][kEigThreads / 64];
   __shared__ int rank[kCurvMaxK];
   const EigTask t = tasks[blockIdx.x];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -474,7 +495,7 @@ __global__ __launch_bounds__(256) void eigen_kernel(const EigTask* __restrict__ 
   const float* sum = (const float*)(state + t.sum_off);
   const int64_t cnt = *(const int64_t*)(state + t.count_off);
   const double scale = cnt > 0 ? 1.0 / (double)cnt : 0.0;
-  for (int e = tid; e < n * n; e += 256) {
+  for (int e = tid; e < n * n; e += kEigThreads) {
     const int i = e / n, j = e - (e / n) * n;
     double v = 0.0;
     if (i < k && j < k) v = 0.5 * ((double)sum[i * k + j] + (double)sum[j * k + i]) * scale;
@@ -483,9 +504,11 @@ __global__ __launch_bounds__(256) void eigen_kernel(const EigTask* __restrict__ 
   }
   __syncthreads();
 
+  const int bi = tid >> 5, bj = tid & 31;  // this thread's pairs
+  const bool mine = bi < m && bj < m;
   for (int sweep = 0; sweep < kEigSweeps; ++sweep) {
     double off = 0.0, tot = 0.0;
-    for (int e = tid; e < n * n; e += 256) {
+    for (int e = tid; e < n * n; e += kEigThreads) {
       const int i = e / n, j = e - (e / n) * n;
       const double v = Am[i * kEigLd + j];
       tot += v * v;
@@ -498,8 +521,12 @@ __global__ __launch_bounds__(256) void eigen_kernel(const EigTask* __restrict__ 
       red[1][wave] = tot;
     }
     __syncthreads();
-    off = ((red[0][0] + red[0][1]) + red[0][2]) + red[0][3];
-    tot = ((red[1][0] + red[1][1]) + red[1][2]) + red[1][3];
+    off = tot = 0.0;
+#pragma unroll
+    for (int w = 0; w < kEigThreads / 64; ++w) {
+      off += red[0][w];
+      tot += red[1][w];
+    }
     __syncthreads();
     if (off <= 1e-26 * tot) break;  // the same value in every thread: a uniform exit
 
@@ -509,48 +536,45 @@ __global__ __launch_bounds__(256) void eigen_kernel(const EigTask* __restrict__ 
         round_pair(r, tid, n, &p, &q);
         double c = 1.0, s = 0.0;
         const double apq = Am[p * kEigLd + q];
+        const double diff = Am[q * kEigLd + q] - Am[p * kEigLd + p];
         if (apq != 0.0) {
-          // rotation in the (p, q) plane that zeroes a_pq: tan = root of
-          // t^2 + 2 theta t - 1 = 0 of smaller magnitude
-          const double theta = (Am[q * kEigLd + q] - Am[p * kEigLd + p]) / (2.0 * apq);
-          double tn;
-          if (fabs(theta) > 1e150)
-            tn = 0.5 / theta;
-          else
-            tn = (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(1.0 + theta * theta));
-          c = 1.0 / sqrt(1.0 + tn * tn);
+          // rotation in the (p, q) plane that zeroes a_pq: t = tan of its angle,
+          // the root of t^2 + 2 theta t - 1 = 0 of smaller magnitude, theta =
+          // diff / (2 a_pq); with h = hypot(diff, 2 a_pq): t = 2 a_pq /
+          // (diff +- h), free of overflow once both are scaled by the larger
+          const double b2 = 2.0 * apq, big = fmax(fabs(diff), fabs(b2));
+          const int ex = -__builtin_amdgcn_frexp_exp(big);
+          const double x = ldexp(diff, ex), y = ldexp(b2, ex);  // the larger in [0.5, 1)
+          const double h2 = fma(x, x, y * y);
+          const double h = h2 * __builtin_amdgcn_rsq(h2);
+          const double tn = (x >= 0.0 ? y : -y) * __builtin_amdgcn_rcp(fabs(x) + h);
+          c = rsqrt_near(fma(tn, tn, 1.0));
           s = tn * c;
         }
         rc[tid] = c;
         rs[tid] = s;
-        rp[tid] = p;
-        rq[tid] = q;
       }
       __syncthreads();
-      // rows: A <- J^T A; thread (tid / 64, tid % 64) takes column tid % 64 of
-      // the pairs tid / 64, + 4, ... (the pair indices were formed once above)
-      if (lane < n) {
-        for (int pi = wave; pi < m; pi += 4) {
-          const int p = rp[pi], q = rq[pi];
-          const double c = rc[pi], s = rs[pi];
-          const double a = Am[p * kEigLd + lane], b = Am[q * kEigLd + lane];
-          Am[p * kEigLd + lane] = c * a - s * b;
-          Am[q * kEigLd + lane] = s * a + c * b;
-        }
-      }
-      __syncthreads();
-      // columns: A <- A J, V <- V J; row tid % 64 of the same pairs
-      if (lane < n) {
-        for (int pi = wave; pi < m; pi += 4) {
-          const int p = rp[pi], q = rq[pi];
-          const double c = rc[pi], s = rs[pi];
-          const double a = Am[lane * kEigLd + p], b = Am[lane * kEigLd + q];
-          Am[lane * kEigLd + p] = c * a - s * b;
-          Am[lane * kEigLd + q] = s * a + c * b;
-          const double va = Vm[lane * kEigLd + p], vb = Vm[lane * kEigLd + q];
-          Vm[lane * kEigLd + p] = c * va - s * vb;
-          Vm[lane * kEigLd + q] = s * va + c * vb;
-        }
+      if (mine) {
+        int pi, qi, pj, qj;
+        round_pair(r, bi, n, &pi, &qi);
+        round_pair(r, bj, n, &pj, &qj);
+        const double ci = rc[bi], si = rs[bi], cj = rc[bj], sj = rs[bj];
+        const double app = Am[pi * kEigLd + pj], apq = Am[pi * kEigLd + qj];
+        const double aqp = Am[qi * kEigLd + pj], aqq = Am[qi * kEigLd + qj];
+        // rows: p' = c p - s q, q' = s p + c q; then the same on columns
+        const double l00 = ci * app - si * aqp, l01 = ci * apq - si * aqq;
+        const double l10 = si * app + ci * aqp, l11 = si * apq + ci * aqq;
+        Am[pi * kEigLd + pj] = cj * l00 - sj * l01;
+        Am[pi * kEigLd + qj] = sj * l00 + cj * l01;
+        Am[qi * kEigLd + pj] = cj * l10 - sj * l11;
+        Am[qi * kEigLd + qj] = sj * l10 + cj * l11;
+        const double v0 = Vm[bi * kEigLd + pj], w0 = Vm[bi * kEigLd + qj];
+        const double v1 = Vm[(bi + m) * kEigLd + pj], w1 = Vm[(bi + m) * kEigLd + qj];
+        Vm[bi * kEigLd + pj] = cj * v0 - sj * w0;
+        Vm[bi * kEigLd + qj] = sj * v0 + cj * w0;
+        Vm[(bi + m) * kEigLd + pj] = cj * v1 - sj * w1;
+        Vm[(bi + m) * kEigLd + qj] = sj * v1 + cj * w1;
       }
       __syncthreads();
     }
@@ -569,7 +593,7 @@ __global__ __launch_bounds__(256) void eigen_kernel(const EigTask* __restrict__ 
   __syncthreads();
   float* Q = (float*)(state + t.q_off);
   float* lam = (float*)(state + t.lam_off);
-  for (int e = tid; e < k * k; e += 256) {
+  for (int e = tid; e < k * k; e += kEigThreads) {
     const int row = e / k, col = e - (e / k) * k;
     Q[row * k + rank[col]] = (float)Vm[row * kEigLd + col];
   }
@@ -578,7 +602,7 @@ __global__ __launch_bounds__(256) void eigen_kernel(const EigTask* __restrict__ 
 
 hipError_t launch_eigen(const EigTask* tasks, int n_tasks, uint8_t* state, hipStream_t s) {
   if (n_tasks <= 0) return hipSuccess;
-  hipLaunchKernelGGL(eigen_kernel, dim3(n_tasks), dim3(256), 0, s, tasks, state);
+  hipLaunchKernelGGL(eigen_kernel, dim3(n_tasks), dim3(kEigThreads), 0, s, tasks, state);
   return hipGetLastError();
 }
 
