@@ -23,13 +23,14 @@ inline size_t align_up(size_t x, size_t a = kAlign) { return (x + a - 1) / a * a
 dattri_crossgram_cost_model default_crossgram_cost_model();
 
 // Scoring (score_api.cpp): the checks and launches behind dattri_score /
-// dattri_score_cosine, and the workspace bytes they need.
+// dattri_score_cosine, and the workspace bytes they need (at most `limit` where
+// a slower form of the call fits it).
 dattri_status score_impl(const void* phi_q, int64_t n_q, int64_t ld_q, const void* phi_train,
                          int64_t n_train, int64_t ld_train, int64_t F, dattri_dtype dtype,
                          const float* dev_precond_diag, float* scores, int32_t topk, int32_t* topk_idx,
                          float* topk_val, void* workspace, size_t ws_bytes, void* stream, bool cosine);
 size_t score_workspace_need(int64_t n_q, int64_t n_train, int64_t F, int elt, bool precond, bool has_scores,
-                            int32_t topk, bool cosine);
+                            int32_t topk, bool cosine, size_t limit = SIZE_MAX);
 
 }  // namespace dattri
 

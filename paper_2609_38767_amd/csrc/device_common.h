@@ -204,6 +204,23 @@ __device__ inline uint16_t f32_to_bf16_bits(float f) {
   return (uint16_t)(u >> 16);
 }
 
+// acc + the sum of squares of a fragment's values.
+template <int ELT>
+__device__ inline float sum_sq(i32x4 v, float acc) {
+  if constexpr (ELT == 2) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t w = (uint32_t)(i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w);
+      const float a = bf16_bits_to_f32(w & 0xFFFFu), b = __builtin_bit_cast(float, w & 0xFFFF0000u);
+      acc = fmaf(b, b, fmaf(a, a, acc));
+    }
+  } else {
+    const f32x4 f = __builtin_bit_cast(f32x4, v);
+    acc = fmaf(f.w, f.w, fmaf(f.z, f.z, fmaf(f.y, f.y, fmaf(f.x, f.x, acc))));
+  }
+  return acc;
+}
+
 // Element (v, c) of a fragment-major packed projection map (see internal.h),
 // converted to float; rows >= d or columns >= k read as zero.
 template <int ELT>

@@ -115,7 +115,8 @@ struct SplitOp {                    // one factor block: a group's A or a member
   int32_t T;
   int32_t out_ld;                   // floats per projected row
   int32_t once, pad0;               // no other op of the call reads X
-  int32_t rows, ld;                 // n*T, d
+  int32_t rows, ld;                 // n*T, row stride
+  int32_t width, pad1;              // columns of a row
   int32_t slab_cols, n_slabs;
   int32_t nt;                       // 16-column tiles of the projected rows
   int32_t aligned;                  // 16-byte vector loads allowed
@@ -311,18 +312,37 @@ hipError_t launch_mask_fixed(const MaskItem* items, int n_items, const MaskTask*
                              hipStream_t s);
 
 // ---------------------------------------------------------------- scoring
+// Three paths (score_path), each with its own prepared queries and partial
+// results:
+//   kScoreBig     bf16, n_q n_train >= 2^20: packed queries, 256 x 256 tiles
+//   kScoreStream  bf16, few queries against at least 512 MB of training
+//                 rows: the split form's row stream with the queries as its map
+//   kScoreTile    128 x 128 tiles
+enum ScorePath { kScoreTile = 0, kScoreStream = 1, kScoreBig = 2 };
+ScorePath score_path(int elt_bytes, int64_t n_q, int64_t n_train, int64_t F);
+struct StreamShape { int nt; int64_t slab_cols; int n_slabs; };
+StreamShape score_stream_shape(int64_t n_q, int64_t n_train, int64_t F);
+int64_t score_stream_pack_bytes(int64_t n_q, int64_t F);
+// S = Q X^T (or cosines, given the queries' inverse norms iq): pack, stream,
+// finish.  pack, parts: workspace of score_stream_pack_bytes / n_slabs * n_train *
+// 16 nt floats; norm_parts: n_slabs * n_train floats (cosine).
+hipError_t launch_score_stream(const void* Q, int64_t ldq, const float* d, const void* X, int64_t ldx, float* S,
+                               int64_t n_q, int64_t n_train, int64_t F, void* pack, float* parts, const float* iq,
+                               float* norm_parts, hipStream_t s);
 // dst rows ld_dst apart receive src rows (ld_src apart) times d, first F columns
 hipError_t launch_scale_rows(int elt_bytes, const void* src, int64_t ld_src, const float* d,
                              void* dst, int64_t ld_dst, int64_t rows, int64_t F, hipStream_t s);
-// partials: workspace of score_partial_floats(...) floats (may be null when 0)
-// S = (Q diag(d)) X^T (d may be null): Q rows ldq elements apart, X rows ldx
-// apart (both >= F, multiples of 16 bytes).  qws: workspace of
-// score_query_ws_bytes(...) bytes for the prepared queries (ld_ws = row stride
-// of the row-major form the small kernels use); partials: workspace of
-// score_partial_floats(...) floats (may be null when 0).
-hipError_t launch_score_gemm(int elt_bytes, const void* Q, int64_t ldq, const float* d, const void* X,
-                             int64_t ldx, float* S, int64_t n_q, int64_t n_train, int64_t F,
-                             void* qws, int64_t ld_ws, float* partials, hipStream_t s);
+// S = (Q diag(d)) X^T (d may be null) on 128 x 128 tiles: Q rows ldq elements
+// apart, X rows ldx apart (both >= F, multiples of 16 bytes).  qws: the scaled
+// queries (rows ld_ws apart) when d is given; partials: score_partial_floats(...)
+// floats (may be null when 0).  With norm_parts (score_ksplit(...) * n_train
+// floats) the scores are cosines: iq the queries' inverse norms.
+hipError_t launch_score_tiles(int elt_bytes, const void* Q, int64_t ldq, const float* d, const void* X, int64_t ldx,
+                              float* S, int64_t n_q, int64_t n_train, int64_t F, void* qws, int64_t ld_ws,
+                              float* partials, const float* iq, float* norm_parts, hipStream_t s);
+// inv[r] = 1 / |row r times d (when given)|, 0 for a zero row
+hipError_t launch_row_inv_norms(int elt_bytes, const void* X, int64_t ld, int64_t rows, int64_t F, const float* d,
+                                float* inv, hipStream_t s);
 // bf16 problems at least this large (n_q * n_train) use the 256 x 256 kernel
 constexpr int64_t kBigGemmMin = (int64_t)1 << 20;
 inline bool score_uses_big(int elt_bytes, int64_t n_q, int64_t n_train) {

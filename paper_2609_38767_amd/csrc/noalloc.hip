@@ -57,7 +57,8 @@ extern "C" dattri_status dattri_score_noalloc(const void* phi_q, int64_t n_q, in
     if (n_q > 0 && n_train > 0 && F >= 0 && topk >= 0 && n_q <= INT32_MAX && n_train <= INT32_MAX &&
         F <= INT32_MAX) {
       const size_t need = score_workspace_need(n_q, n_train, F, dtype == DATTRI_BF16 ? 2 : 4,
-                                               dev_precond_diag != nullptr, scores != nullptr, topk, false);
+                                               dev_precond_diag != nullptr, scores != nullptr, topk, false,
+                                               kScratchBytes);
       if (need > kScratchBytes)
         return fail(DATTRI_E_UNSUPPORTED,
                     "this call needs %zu bytes of scratch; the allocation-free entry point holds %zu",

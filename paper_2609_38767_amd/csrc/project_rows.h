@@ -268,7 +268,8 @@ __device__ inline void project_rows_dma(const rsrc_t r, int r_wave, int nrows, i
 // MFMA operand; stages, chunk swizzle and map fragments as in project_rows_dma.
 // rowoff[i]: byte offset in `r` of the chunk this lane loads of row group i's
 // stage 0 (row i * 8 + lane / 8 of the wave, chunk (lane % 8) ^ (row % 8)), or
-// kFarOff for a row that must not be read (it reads as zero).  P(t, &base,
+// kFarOff for a row that must not be read (it reads as zero).  kNorm: nsq[rt]
+// also gathers the squares of this lane's columns of row tile rt.  P(t, &base,
 // &stride): the packed map's fragment (k-block kb, tile t) is at base + kb *
 // stride; nt tiles are in use.  Stages s .. s +
 // D - 1 are in flight or in use: the wait for stage s leaves the loads of the
@@ -373,9 +374,10 @@ __device__ inline void read_frags(i32x4 (&x)[RT], i32x4 (&p)[NT], uint32_t xa, u
                  : "memory");
 }
 
-template <int RT, int NT, int D, class Frag>
+template <int RT, int NT, int D, bool kNorm, class Frag>
 __device__ inline void stream_rows(const rsrc_t r, const uint32_t (&rowoff)[StreamLds<RT, NT, D>::kLoads], int d,
-                                   int nt, const Frag& P, bool once, f32x4 (&acc)[RT][NT], uint8_t* lds) {
+                                   int nt, const Frag& P, bool once, f32x4 (&acc)[RT][NT], float (&nsq)[RT],
+                                   uint8_t* lds) {
   using C = StreamLds<RT, NT, D>;
   constexpr int EPL = 8, KR = 4 * EPL;
   const int lane = threadIdx.x & 63, g = lane >> 4, m16 = lane & 15;
@@ -445,6 +447,10 @@ __device__ inline void stream_rows(const rsrc_t r, const uint32_t (&rowoff)[Stre
       if (2 * s + kbl < nkb) {  // uniform
         i32x4 x[RT], pf[NT];
         read_frags<RT, NT>(x, pf, kbl ? xs ^ 64u : xs, ms + (uint32_t)(kbl * NT * kFragBytes));
+        if constexpr (kNorm) {
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt) nsq[rt] = sum_sq<2>(x[rt], nsq[rt]);
+        }
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
           if (t < nt) {

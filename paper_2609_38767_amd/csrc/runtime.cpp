@@ -597,6 +597,7 @@ dattri_status dattri::build_plan(const dattri_ctx* ctx, dattri_route forced, Pla
       A.lengths = H.lengths;
       A.T = H.T;
       A.ld = H.d_in;
+      A.width = H.d_in;
       A.aligned = ((uintptr_t)H.A % 16 == 0) && (H.d_in * elt) % 16 == 0;
       std::vector<SplitOp> Bs;
       int na = 0;
@@ -616,6 +617,7 @@ dattri_status dattri::build_plan(const dattri_ctx* ctx, dattri_route forced, Pla
         B.lengths = L.lengths;
         B.T = L.T;
         B.ld = L.d_out;
+        B.width = L.d_out;
         B.aligned = ((uintptr_t)L.B % 16 == 0) && (L.d_out * elt) % 16 == 0;
         B.nt = tiles16(L.k_out);
         for (int t = 0; t < B.nt; ++t) {

@@ -4,9 +4,11 @@
 // Both operands are row-major with the feature axis contiguous, which is the
 // K-contiguous ("NT") form MFMA wants for both sides: a lane's 16-byte fragment
 // is a contiguous slice of one row.  Workgroup tile 128 x 128, 4 waves in a
-// 2 x 2 grid of 64 x 64 (4 x 4 MFMA tiles each), 128 bytes of K per stage,
-// double-buffered in LDS with the next stage prefetched into registers while
-// the current one is multiplied.  LDS rows are XOR-swizzled by 16-byte chunk.
+// 2 x 2 grid of 64 x 64 (4 x 4 MFMA tiles each), 128 bytes of K per stage, the
+// next stage prefetched into registers while the current one is multiplied.
+// bf16: double-buffered in LDS, rows XOR-swizzled by 16-byte chunk.  float32:
+// values split into three bf16 terms on their way into LDS and multiplied on
+// bf16 MFMA (score_gemm_split_kernel).
 // Tiles are remapped so that each XCD walks a contiguous range of training
 // tiles, all query tiles of one training tile back to back, so a Phi_train
 // tile is fetched into that XCD's L2 once and reused by every query tile.
@@ -42,23 +44,29 @@ __global__ __launch_bounds__(256) void scale_rows_kernel(const uint8_t* __restri
 
 constexpr int kBM = 128, kBN = 128, kRowBytes = 128;  // tile rows, K bytes per stage
 
-template <int ELT>
+// XCD-aware tile order (dispatch round-robins workgroups over 8 XCDs)
+__device__ inline void tile_of(int b, int n_qt, int n_xt, int* qt, int* xt) {
+  const int n_full = n_qt * n_xt / 8 * 8;
+  const int L = b < n_full ? (b % 8) * (n_full / 8) + b / 8 : b;
+  *qt = L % n_qt;
+  *xt = L / n_qt;
+}
+
+// norms (may be null): the tiles of the first query tile also write their
+// training rows' sums of squares over this split's features.
 __global__ __launch_bounds__(256) void score_gemm_kernel(const uint8_t* __restrict__ Q,
                                                          const uint8_t* __restrict__ X,
-                                                         float* __restrict__ S, int n_q,
+                                                         float* __restrict__ S, float* __restrict__ norms, int n_q,
                                                          int n_train, int F, int ldq, int ldx,
                                                          int n_qt, int n_xt, int sps) {
-  constexpr int EPL = 16 / ELT;
+  constexpr int ELT = 2, EPL = 16 / ELT;
   constexpr int BK = kRowBytes / ELT;  // K elements per stage
   __shared__ __align__(16) uint8_t smem[2][2][kBM * kRowBytes];  // [stage][Q/X] 64 KiB
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = lane >> 4, m16 = lane & 15, wm = wave >> 1, wn = wave & 1;
 
-  // XCD-aware tile order (dispatch round-robins workgroups over 8 XCDs)
-  const int nb = n_qt * n_xt, b = blockIdx.x;
-  const int n_full = nb / 8 * 8;
-  const int L = b < n_full ? (b % 8) * (n_full / 8) + b / 8 : b;
-  const int qt = L % n_qt, xt = L / n_qt;
+  int qt, xt;
+  tile_of(blockIdx.x, n_qt, n_xt, &qt, &xt);
   const int q0 = qt * kBM, x0 = xt * kBN;
   const int rows_q = min(kBM, n_q - q0), rows_x = min(kBN, n_train - x0);
   // ranges end at the last row's F-th element (padding after it need not exist)
@@ -84,9 +92,12 @@ __global__ __launch_bounds__(256) void score_gemm_kernel(const uint8_t* __restri
       rxv[i] = load_frag_ld<ELT>(rx, row, rows_x, col, F, ldx);
     }
   };
+  const bool sq = norms && qt == 0;  // uniform
+  float nsq[4] = {0.f, 0.f, 0.f, 0.f};
   auto swrite = [&](int st) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
+      if (sq) nsq[i] = sum_sq<ELT>(rxv[i], nsq[i]);
       const int c = tid + 256 * i, row = c >> 3, ch = c & 7;
       const int off = row * kRowBytes + ((ch ^ (row & 7)) << 4);
       *(i32x4*)(smem[st][0] + off) = rqv[i];
@@ -135,11 +146,162 @@ __global__ __launch_bounds__(256) void score_gemm_kernel(const uint8_t* __restri
         if (q < n_q && x < n_train) S[(int64_t)q * n_train + x] = acc[i][j][r];
       }
     }
+  if (sq) {  // eight threads hold the pieces of a row
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float v = nsq[i];
+      v += __shfl_xor(v, 1, 64);
+      v += __shfl_xor(v, 2, 64);
+      v += __shfl_xor(v, 4, 64);
+      const int row = (tid + 256 * i) >> 3;
+      if ((tid & 7) == 0 && x0 + row < n_train) norms[(int64_t)blockIdx.y * n_train + x0 + row] = v;
+    }
+  }
+}
+
+// float32: each thread loads 32 bytes of two rows per side, one stage ahead,
+// splits them once and writes 16 bytes to each of the three planes of its side
+// in LDS (64 bytes per row and plane; the 16-byte chunk c of row r at c XOR
+// (r / 2) mod 4); the waves read operands from there: 24 reads for 96 MFMA per
+// stage.  A value is split once per tile and used by 128 products.  Three
+// workgroups share a CU, so one's splitting runs beside another's MFMA.  Blocks of 16
+// query rows past n_q are not multiplied.  A tile whose result is not finite is
+// computed again in float32 MFMA from memory.  Bound by the issue of MFMA and
+// splitting: the whole cosine call for 256 x 8192 x 12288 takes 0.30 ms (0.52 ms
+// in float32 MFMA at 99 TFLOP/s, with a second read of both sides for the norms).
+constexpr int kPlane = kBM * 64;
+__device__ inline int plane_off(int row, int chunk) { return row * 64 + ((chunk ^ ((row >> 1) & 3)) << 4); }
+
+__global__ __launch_bounds__(256, 2) void score_gemm_split_kernel(const uint8_t* __restrict__ Q,
+                                                                  const uint8_t* __restrict__ X,
+                                                                  float* __restrict__ S, float* __restrict__ norms,
+                                                                  int n_q, int n_train, int F, int ldq, int ldx,
+                                                                  int n_qt, int n_xt, int sps) {
+  constexpr int BK = 32;
+  __shared__ __align__(16) uint8_t lds[2 * 3 * kPlane];  // [Q, X][hi, mid, lo]
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int g = lane >> 4, m16 = lane & 15, wm = wave >> 1, wn = wave & 1;
+  int qt, xt;
+  tile_of(blockIdx.x, n_qt, n_xt, &qt, &xt);
+  const int q0 = qt * kBM, x0 = xt * kBN;
+  const int rows_q = min(kBM, n_q - q0), rows_x = min(kBN, n_train - x0);
+  const rsrc_t rq = make_rsrc(Q + (int64_t)q0 * ldq * 4, (uint32_t)(((int64_t)(rows_q - 1) * ldq + F) * 4));
+  const rsrc_t rx = make_rsrc(X + (int64_t)x0 * ldx * 4, (uint32_t)(((int64_t)(rows_x - 1) * ldx + F) * 4));
+  const int ni = min(4, max(0, (rows_q - wm * 64 + 15) / 16));  // this wave's blocks of query rows
+  f32x4 acc[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  const int nk = (F + BK - 1) / BK;
+  const int k0 = blockIdx.y * sps, k1 = min(nk, k0 + sps);  // this split's K steps
+  S += (int64_t)blockIdx.y * n_q * n_train;
+  const int row = tid >> 2, pc = tid & 3;  // rows row and row + 64, features 8 pc .. + 7 of a stage
+  i32x4 xq[2][2], xx[2][2];
+  auto load = [&](int kk) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int col = kk * BK + pc * 8 + 4 * h;
+        xq[t][h] = load_frag_ld<4>(rq, row + 64 * t, rows_q, col, F, ldq);
+        xx[t][h] = load_frag_ld<4>(rx, row + 64 * t, rows_x, col, F, ldx);
+      }
+  };
+  const bool sq = norms && qt == 0;  // uniform
+  float nsq[2] = {0.f, 0.f};
+  auto put_one = [&](uint8_t* side, int r, const i32x4 (&v)[2]) {
+    const Split3 s = split3(v[0], v[1]);
+    uint8_t* w = side + plane_off(r, pc);
+    *(bf16x8*)w = s.hi;
+    *(bf16x8*)(w + kPlane) = s.mid;
+    *(bf16x8*)(w + 2 * kPlane) = s.lo;
+  };
+  auto put = [&] {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      if (64 * t < rows_q) put_one(lds, row + 64 * t, xq[t]);  // uniform
+      put_one(lds + 3 * kPlane, row + 64 * t, xx[t]);
+      if (sq) nsq[t] = sum_sq<4>(xx[t][1], sum_sq<4>(xx[t][0], nsq[t]));
+    }
+  };
+  auto get = [&](const uint8_t* side, int r) {
+    const uint8_t* w = side + plane_off(r, g);
+    return Split3{*(const bf16x8*)w, *(const bf16x8*)(w + kPlane), *(const bf16x8*)(w + 2 * kPlane)};
+  };
+  if (k0 < k1) load(k0);
+  for (int kk = k0; kk < k1; ++kk) {
+    lds_barrier();  // the previous stage's operands are read
+    put();
+    load(kk + 1);  // past the last stage: never used
+    lds_barrier();
+    if (ni > 0) {
+      Split3 b[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) b[j] = get(lds + 3 * kPlane, wn * 64 + 16 * j + m16);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (i < ni) {  // uniform over the wave
+          const Split3 a = get(lds, wm * 64 + 16 * i + m16);
+#define DATTRI_TERM(p) _Pragma("unroll") for (int j = 0; j < 4; ++j) acc[i][j] = split_term<p>(a, b[j], acc[i][j]);
+          DATTRI_TERM(0) DATTRI_TERM(1) DATTRI_TERM(2) DATTRI_TERM(3) DATTRI_TERM(4) DATTRI_TERM(5)
+#undef DATTRI_TERM
+        }
+      }
+    }
+  }
+  bool bad = false;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) bad = bad || not_finite(acc[i][j]);
+  if (__any(bad)) {  // infinities, NaN or overflow: this wave's block in float32 products, straight from memory
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int kk = k0; kk < k1; ++kk)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int col = kk * BK + h * 16 + 4 * g;
+        i32x4 a[4], b[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          a[i] = load_frag_ld<4>(rq, wm * 64 + 16 * i + m16, rows_q, col, F, ldq);
+          b[i] = load_frag_ld<4>(rx, wn * 64 + 16 * i + m16, rows_x, col, F, ldx);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc[i][j] = frag_mma<4>(a[i], b[j], acc[i][j]);
+      }
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int x = x0 + wn * 64 + j * 16 + m16;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int q = q0 + wm * 64 + i * 16 + 4 * g + r;
+        if (q < n_q && x < n_train) S[(int64_t)q * n_train + x] = acc[i][j][r];
+      }
+    }
+  if (sq) {  // four threads hold the pieces of a row
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      float v = nsq[t];
+      v += __shfl_xor(v, 1, 64);
+      v += __shfl_xor(v, 2, 64);
+      if (pc == 0 && x0 + row + 64 * t < n_train) norms[(int64_t)blockIdx.y * n_train + x0 + row + 64 * t] = v;
+    }
+  }
 }
 
 // ------------------------------------------------------ cosine normalization
 // inv[r] = 1 / |row r (times d, when given)|, 0 for a zero row.  One wave per
-// row, 16-byte loads (rows are 16-byte aligned and F a multiple of 16 bytes).
+// row (many rows), 16-byte loads (rows are 16-byte aligned and F a multiple of 16 bytes).
 template <int ELT>
 __global__ __launch_bounds__(256) void row_inv_norms_kernel(const uint8_t* __restrict__ X, int64_t ld,
                                                             int64_t rows, int64_t F,
@@ -188,24 +350,113 @@ __global__ __launch_bounds__(256) void scale_scores_kernel(float* __restrict__ S
   }
 }
 
+// The same for few rows: a workgroup per row, four loads in flight per thread
+// (one wave per row leaves a single query's 200k features to 450 round trips).
+template <int ELT>
+__global__ __launch_bounds__(1024) void row_inv_norms_wide_kernel(const uint8_t* __restrict__ X, int64_t ld, int64_t F,
+                                                                  const float* __restrict__ d,
+                                                                  float* __restrict__ inv) {
+  constexpr int EPL = 16 / ELT;
+  __shared__ float red[16];
+  const uint8_t* row = X + (int64_t)blockIdx.x * ld * ELT;
+  float s = 0.f;
+#pragma unroll 4
+  for (int64_t f = (int64_t)threadIdx.x * EPL; f < F; f += 1024 * EPL) {
+    const i32x4 v = *(const i32x4*)(row + f * ELT);
+    if (!d) {
+      s = sum_sq<ELT>(v, s);
+    } else if constexpr (ELT == 2) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t w = (uint32_t)(e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w);
+        const float a = bf16_bits_to_f32(w & 0xFFFFu) * d[f + 2 * e], b = bf16_bits_to_f32(w >> 16) * d[f + 2 * e + 1];
+        s = fmaf(b, b, fmaf(a, a, s));
+      }
+    } else {
+      f32x4 x = __builtin_bit_cast(f32x4, v);
+      x.x *= d[f]; x.y *= d[f + 1]; x.z *= d[f + 2]; x.w *= d[f + 3];
+      s = sum_sq<4>(__builtin_bit_cast(i32x4, x), s);
+    }
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    float t = 0.f;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) t += red[w];
+    inv[blockIdx.x] = t > 0.f ? 1.f / sqrtf(t) : 0.f;
+  }
+}
+
+hipError_t launch_row_inv_norms(int elt, const void* X, int64_t ld, int64_t rows, int64_t F, const float* d, float* inv,
+                                hipStream_t s) {
+  if (rows <= 0) return hipSuccess;
+  if (rows <= 2048) {
+    if (elt == 2)
+      hipLaunchKernelGGL(row_inv_norms_wide_kernel<2>, dim3((unsigned)rows), dim3(1024), 0, s, (const uint8_t*)X, ld, F,
+                         d, inv);
+    else
+      hipLaunchKernelGGL(row_inv_norms_wide_kernel<4>, dim3((unsigned)rows), dim3(1024), 0, s, (const uint8_t*)X, ld, F,
+                         d, inv);
+    return hipGetLastError();
+  }
+  const int64_t b = (rows + 3) / 4;
+  if (b > INT32_MAX) return hipErrorInvalidValue;
+  if (elt == 2)
+    hipLaunchKernelGGL(row_inv_norms_kernel<2>, dim3((unsigned)b), dim3(256), 0, s, (const uint8_t*)X, ld, rows, F, d,
+                       inv);
+  else
+    hipLaunchKernelGGL(row_inv_norms_kernel<4>, dim3((unsigned)b), dim3(256), 0, s, (const uint8_t*)X, ld, rows, F, d,
+                       inv);
+  return hipGetLastError();
+}
+
+// S[q][j] = iq[q] / |x_j| sum over splits of part[y][q][j], |x_j|^2 the sum over
+// splits of norm_parts[y][j].  Thread: one training row, qpt queries.
+__global__ __launch_bounds__(256) void finish_cosine_kernel(const float* __restrict__ part, int ks, int64_t n_q,
+                                                            int64_t n_train, const float* __restrict__ iq,
+                                                            const float* __restrict__ norm_parts, int qpt,
+                                                            float* __restrict__ S) {
+  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (j >= n_train) return;
+  float s = 0.f;
+  for (int y = 0; y < ks; ++y) s += norm_parts[(int64_t)y * n_train + j];
+  const float it = s > 0.f ? 1.f / sqrtf(s) : 0.f;
+  const int64_t step = n_q * n_train, q1 = min<int64_t>(n_q, ((int64_t)blockIdx.y + 1) * qpt);
+  for (int64_t q = (int64_t)blockIdx.y * qpt; q < q1; ++q) {
+    const float* p = part + q * n_train + j;
+    float v = 0.f;
+    int y = 0;
+    for (; y + 4 <= ks; y += 4) {
+      const float v0 = p[y * step], v1 = p[(y + 1) * step], v2 = p[(y + 2) * step], v3 = p[(y + 3) * step];
+      v = (((v + v0) + v1) + v2) + v3;
+    }
+    for (; y < ks; ++y) v += p[y * step];
+    S[q * n_train + j] = v * (iq[q] * it);
+  }
+}
+
+hipError_t launch_finish_cosine(const float* part, int ks, int64_t n_q, int64_t n_train, const float* iq,
+                                const float* norm_parts, float* S, hipStream_t s) {
+  if (n_q <= 0 || n_train <= 0) return hipSuccess;
+  // queries per thread: as many as leave about 1024 workgroups (each sums its
+  // rows' norms once), and no more workgroups in y than a grid holds
+  const int64_t gx = (n_train + 255) / 256;
+  const int64_t qpt = std::max<int64_t>(std::min<int64_t>(32, n_q * gx / 1024), (n_q + 65534) / 65535);
+  const int64_t per = std::max<int64_t>(qpt, 1), gy = (n_q + per - 1) / per;
+  hipLaunchKernelGGL(finish_cosine_kernel, dim3((unsigned)gx, (unsigned)gy), dim3(256), 0, s, part, ks, n_q, n_train, iq,
+                     norm_parts, (int)per, S);
+  return hipGetLastError();
+}
+
 hipError_t launch_cosine_scale(int elt, const void* Q, int64_t ldq, const float* d, const void* X, int64_t ldx,
                                float* S, int64_t n_q, int64_t n_train, int64_t F, float* inv_q, float* inv_t,
                                hipStream_t s) {
   if (n_q <= 0 || n_train <= 0) return hipSuccess;
-  const int64_t bq = (n_q + 3) / 4, bt = (n_train + 3) / 4;
-  if (bq > INT32_MAX || bt > INT32_MAX) return hipErrorInvalidValue;
-  if (elt == 2) {
-    hipLaunchKernelGGL(row_inv_norms_kernel<2>, dim3((unsigned)bq), dim3(256), 0, s, (const uint8_t*)Q, ldq, n_q,
-                       F, d, inv_q);
-    hipLaunchKernelGGL(row_inv_norms_kernel<2>, dim3((unsigned)bt), dim3(256), 0, s, (const uint8_t*)X, ldx,
-                       n_train, F, nullptr, inv_t);
-  } else {
-    hipLaunchKernelGGL(row_inv_norms_kernel<4>, dim3((unsigned)bq), dim3(256), 0, s, (const uint8_t*)Q, ldq, n_q,
-                       F, d, inv_q);
-    hipLaunchKernelGGL(row_inv_norms_kernel<4>, dim3((unsigned)bt), dim3(256), 0, s, (const uint8_t*)X, ldx,
-                       n_train, F, nullptr, inv_t);
-  }
-  hipError_t e = hipGetLastError();
+  hipError_t e = launch_row_inv_norms(elt, Q, ldq, n_q, F, d, inv_q, s);
+  if (e == hipSuccess) e = launch_row_inv_norms(elt, X, ldx, n_train, F, nullptr, inv_t, s);
   if (e != hipSuccess) return e;
   const unsigned blocks = (unsigned)std::min<int64_t>(n_q, 4096);
   hipLaunchKernelGGL(scale_scores_kernel, dim3(blocks), dim3(256), 0, s, S, n_q, n_train, inv_q, inv_t);
@@ -226,12 +477,10 @@ hipError_t launch_scale_rows(int elt, const void* src, int64_t ld_src, const flo
   return hipGetLastError();
 }
 
-hipError_t launch_score_gemm(int elt, const void* Q, int64_t ldq, const float* d, const void* X,
-                             int64_t ldx, float* S, int64_t n_q, int64_t n_train, int64_t F,
-                             void* qws, int64_t ld_ws, float* partials, hipStream_t s) {
+hipError_t launch_score_tiles(int elt, const void* Q, int64_t ldq, const float* d, const void* X, int64_t ldx,
+                              float* S, int64_t n_q, int64_t n_train, int64_t F, void* qws, int64_t ld_ws,
+                              float* partials, const float* iq, float* norm_parts, hipStream_t s) {
   if (n_q <= 0 || n_train <= 0) return hipSuccess;
-  if (score_uses_big(elt, n_q, n_train))
-    return launch_score_gemm_256(Q, ldq, d, X, ldx, S, n_q, n_train, F, qws, partials, s);
   if (d && F > 0) {  // scaled queries, row-major in the workspace
     if (!qws) return hipErrorInvalidValue;
     hipError_t e = launch_scale_rows(elt, Q, ldq, d, qws, ld_ws, n_q, F, s);
@@ -248,16 +497,17 @@ hipError_t launch_score_gemm(int elt, const void* Q, int64_t ldq, const float* d
   if (ks > 1 && !partials) return hipErrorInvalidValue;
   float* out = ks > 1 ? partials : S;
   if (elt == 2)
-    hipLaunchKernelGGL(score_gemm_kernel<2>, dim3((unsigned)nb, (unsigned)ks), dim3(256), 0, s,
-                       (const uint8_t*)Q, (const uint8_t*)X, out, (int)n_q, (int)n_train, (int)F, (int)ldq,
-                       (int)ldx, n_qt, n_xt, sps);
+    hipLaunchKernelGGL(score_gemm_kernel, dim3((unsigned)nb, (unsigned)ks), dim3(256), 0, s, (const uint8_t*)Q,
+                       (const uint8_t*)X, out, norm_parts, (int)n_q, (int)n_train, (int)F, (int)ldq, (int)ldx, n_qt,
+                       n_xt, sps);
   else
-    hipLaunchKernelGGL(score_gemm_kernel<4>, dim3((unsigned)nb, (unsigned)ks), dim3(256), 0, s,
-                       (const uint8_t*)Q, (const uint8_t*)X, out, (int)n_q, (int)n_train, (int)F, (int)ldq,
-                       (int)ldx, n_qt, n_xt, sps);
+    hipLaunchKernelGGL(score_gemm_split_kernel, dim3((unsigned)nb, (unsigned)ks), dim3(256), 0, s, (const uint8_t*)Q,
+                       (const uint8_t*)X, out, norm_parts, (int)n_q, (int)n_train, (int)F, (int)ldq, (int)ldx, n_qt,
+                       n_xt, sps);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || ks == 1) return e;
-  return launch_splitk_sum(partials, ks, n_q * n_train, S, s);
+  if (e != hipSuccess) return e;
+  if (norm_parts) return launch_finish_cosine(out, ks, n_q, n_train, iq, norm_parts, S, s);
+  return ks == 1 ? hipSuccess : launch_splitk_sum(partials, ks, n_q * n_train, S, s);
 }
 
 }  // namespace dattri

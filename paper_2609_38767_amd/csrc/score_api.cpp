@@ -25,40 +25,63 @@ int64_t feature_ld(int64_t F, int elt) {
 }
 
 struct ScoreLayout {
+  ScorePath path;
+  bool fused;  // cosine: the training rows' norms come from the product's own pass
   int64_t ldq;
   size_t off_q, q_bytes, off_s, s_bytes, off_p, p_bytes, off_n, n_bytes, total;
 };
 
-// Prepared queries: packed in MFMA fragment order for the 256 x 256 kernel
-// (always), else a preconditioned row-major copy at the recommended stride.
+// Prepared queries: packed in the fragment order of the 256 x 256 kernel or of
+// the row stream (always), else a preconditioned row-major copy at the
+// recommended stride.
 ScoreLayout score_layout(int64_t n_q, int64_t n_train, int64_t F, int elt, bool precond,
-                         bool has_scores, int32_t topk, bool cosine = false) {
+                         bool has_scores, int32_t topk, bool cosine = false, size_t limit = SIZE_MAX,
+                         int spare = 2) {
   ScoreLayout L;
+  L.path = score_path(elt, n_q, n_train, F);
+  if (L.path == kScoreStream && spare < 2) L.path = score_uses_big(elt, n_q, n_train) ? kScoreBig : kScoreTile;
+  L.fused = cosine && L.path != kScoreBig && spare > 0;
   size_t off = 0;
   L.ldq = feature_ld(F, elt);
   L.off_q = off;
-  if (score_uses_big(elt, n_q, n_train))
+  int64_t splits = 1;  // partial sums of every training row's norm
+  size_t p_floats = 0;
+  if (L.path == kScoreBig) {
     L.q_bytes = (size_t)score_qpack_bytes(n_q, F);
-  else
+    p_floats = (size_t)score_partial_floats(elt, n_q, n_train, F);
+  } else if (L.path == kScoreStream) {
+    const StreamShape h = score_stream_shape(n_q, n_train, F);
+    L.q_bytes = (size_t)score_stream_pack_bytes(n_q, F);
+    p_floats = (size_t)h.n_slabs * n_train * 16 * h.nt;
+    splits = h.n_slabs;
+  } else {
     L.q_bytes = precond ? (size_t)(n_q * L.ldq * elt) : 0;
+    p_floats = (size_t)score_partial_floats(elt, n_q, n_train, F);
+    splits = score_ksplit(elt, n_q, n_train, F);
+  }
   off = align_up(off + L.q_bytes);
   L.off_s = off;
   L.s_bytes = (!has_scores && topk > 0) ? (size_t)(n_q * n_train * 4) : 0;
   off = align_up(off + L.s_bytes);
   L.off_p = off;
-  L.p_bytes = (size_t)score_partial_floats(elt, n_q, n_train, F) * 4;
+  L.p_bytes = p_floats * 4;
   off = align_up(off + L.p_bytes);
-  L.off_n = off;  // cosine: inverse row norms of the queries, then of the training rows
-  L.n_bytes = cosine ? (size_t)(n_q + n_train) * 4 : 0;
+  L.off_n = off;  // cosine: inverse norms of the queries, then the training rows' (inverse norms, or sums by split)
+  L.n_bytes = cosine ? (size_t)(n_q + (L.fused ? splits : 1) * n_train) * 4 : 0;
   off = align_up(off + L.n_bytes);
   L.total = std::max<size_t>(off, kAlign);
+  // a workspace (or the fixed scratch) that holds less than the fastest form
+  // needs: the tile kernels without the stream's partial scores, then without
+  // the norms' partial sums
+  if (L.total > limit && (L.path == kScoreStream || L.fused))
+    return score_layout(n_q, n_train, F, elt, precond, has_scores, topk, cosine, limit, L.path == kScoreStream ? 1 : 0);
   return L;
 }
 }  // namespace
 
 size_t dattri::score_workspace_need(int64_t n_q, int64_t n_train, int64_t F, int elt, bool precond,
-                                    bool has_scores, int32_t topk, bool cosine) {
-  return score_layout(n_q, n_train, F, elt, precond, has_scores, topk, cosine).total;
+                                    bool has_scores, int32_t topk, bool cosine, size_t limit) {
+  return score_layout(n_q, n_train, F, elt, precond, has_scores, topk, cosine, limit).total;
 }
 
 dattri_status dattri::score_impl(const void* phi_q, int64_t n_q, int64_t ld_q, const void* phi_train,
@@ -85,7 +108,7 @@ dattri_status dattri::score_impl(const void* phi_q, int64_t n_q, int64_t ld_q, c
   if (F > 0 && (!phi_q || !phi_train)) return fail(DATTRI_E_INVALID_ARG, "phi_q or phi_train is NULL");
   const int elt = dtype == DATTRI_BF16 ? 2 : 4;
   const ScoreLayout L = score_layout(n_q, n_train, F, elt, dev_precond_diag != nullptr,
-                                     scores != nullptr, topk, cosine);
+                                     scores != nullptr, topk, cosine, workspace ? ws_bytes : 0);
   const int64_t ld_max = std::max({ld_q, ld_train, L.ldq});
   if (ld_max * elt * 256 >= kMaxBlockBytes)
     return fail(DATTRI_E_UNSUPPORTED, "row stride %lld too large (256 rows must stay below 4 GiB)",
@@ -103,14 +126,24 @@ dattri_status dattri::score_impl(const void* phi_q, int64_t n_q, int64_t ld_q, c
   hipStream_t s = (hipStream_t)stream;
   uint8_t* ws = (uint8_t*)workspace;
   float* S = scores ? scores : (float*)(ws + L.off_s);
-  HIP_TRY(launch_score_gemm(elt, phi_q, ld_q, dev_precond_diag, phi_train, ld_train, S, n_q, n_train,
-                            F, L.q_bytes ? ws + L.off_q : nullptr, L.ldq,
-                            L.p_bytes ? (float*)(ws + L.off_p) : nullptr, s));
-  if (cosine) {
-    float* inv = (float*)(ws + L.off_n);
+  void* qws = L.q_bytes ? ws + L.off_q : nullptr;
+  float* parts = L.p_bytes ? (float*)(ws + L.off_p) : nullptr;
+  float* inv = cosine ? (float*)(ws + L.off_n) : nullptr;
+  if (L.path == kScoreBig) {
+    HIP_TRY(launch_score_gemm_256(phi_q, ld_q, dev_precond_diag, phi_train, ld_train, S, n_q, n_train, F, qws, parts, s));
+  } else {
+    if (L.fused) HIP_TRY(launch_row_inv_norms(elt, phi_q, ld_q, n_q, F, dev_precond_diag, inv, s));
+    float* norms = L.fused ? inv + n_q : nullptr;
+    if (L.path == kScoreStream)
+      HIP_TRY(launch_score_stream(phi_q, ld_q, dev_precond_diag, phi_train, ld_train, S, n_q, n_train, F, qws,
+                                  parts, inv, norms, s));
+    else
+      HIP_TRY(launch_score_tiles(elt, phi_q, ld_q, dev_precond_diag, phi_train, ld_train, S, n_q, n_train, F, qws,
+                                 L.ldq, parts, inv, norms, s));
+  }
+  if (cosine && !L.fused)
     HIP_TRY(launch_cosine_scale(elt, phi_q, ld_q, dev_precond_diag, phi_train, ld_train, S, n_q, n_train, F, inv,
                                 inv + n_q, s));
-  }
   if (topk > 0) HIP_TRY(launch_topk(S, n_q, n_train, topk, topk_idx, topk_val, s));
   return DATTRI_OK;
 }

@@ -20,6 +20,7 @@
 #include "device_common.h"
 #include "internal.h"
 #include "project_rows.h"
+#include "split_stream.h"
 
 namespace dattri {
 using namespace dev;
@@ -36,123 +37,6 @@ using namespace dev;
 // bf16 rows, k = 32: 2.07 -> 1.50 ms (6.1 TB/s); 24 Pythia-410M-shaped blocks,
 // 8 ragged float32 examples of up to 512, k = 64: 2.27 -> 1.1 ms.  The loads of a
 // block that no other op reads are non-temporal (1.69 -> 1.55 ms on the first).
-template <int ELT, int NT>
-struct SplitShape {
-  static constexpr int kRows = split_stream_rows(ELT), kRT = kRows / 64;
-  static constexpr int D = NT <= 2 ? 4 : NT <= 6 ? 3 : 2;  // bf16: stages per wave
-  static constexpr int kLoads = ELT == 2 ? kRT * 2 : kRT;  // row pieces a lane loads per stage
-};
-
-// Whether any thread of the workgroup has `v` set (w: a word of LDS that nothing else uses meanwhile).
-__device__ inline bool block_any(bool v, uint32_t* w) {
-  __syncthreads();
-  if (threadIdx.x == 0) *w = 0u;
-  __syncthreads();
-  if (v) *w = 1u;  // every writer writes the same value
-  __syncthreads();
-  const bool any = *w != 0u;
-  __syncthreads();
-  return any;
-}
-
-template <int ELT, int NT>
-__device__ inline void split_stream_body(const SplitItem& it, const SplitOp& O, float* __restrict__ out,
-                                         uint8_t* smem) {
-  using S = SplitShape<ELT, NT>;
-  constexpr int KR = 4 * (16 / ELT);  // rows of a packed k-block
-  constexpr int RT = S::kRT, D = S::D, ROWS = S::kRows;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int g = lane >> 4, m16 = lane & 15;
-  const int row0 = it.row_block * ROWS;
-  const int nrows = min(ROWS, O.rows - row0);
-  const int col0 = it.slab * O.slab_cols;
-  const int d = min(O.slab_cols, O.ld - col0);
-  const int r_wave = wave * RT * 16;
-  // rows to read and to write: inside the block and their example's length.
-  // bf16: load i of a stage takes row i * 8 + lane / 8; float32: row i * 16 + m16
-  auto row_of = [&](int i) { return r_wave + (ELT == 4 ? i * 16 + m16 : i < S::kLoads ? i * 8 + (lane >> 3) : (i - S::kLoads) * 16 + m16); };
-  constexpr int kNR = ELT == 2 ? S::kLoads + RT : RT;  // rows to check (float32 writes the rows it reads)
-  uint32_t ok = 0;
-#pragma unroll
-  for (int i = 0; i < kNR; ++i) ok |= (row_of(i) < nrows ? 1u : 0u) << i;
-  if (O.lengths) {  // uniform; every load before the first use
-    int len[kNR], tok[kNR];
-#pragma unroll
-    for (int i = 0; i < kNR; ++i) {
-      const int gr = min(row0 + row_of(i), O.rows - 1), ex = gr / O.T;
-      len[i] = O.lengths[ex];
-      tok[i] = gr - ex * O.T;
-    }
-#pragma unroll
-    for (int i = 0; i < kNR; ++i) ok &= ~((tok[i] < len[i] ? 0u : 1u) << i);
-    if (!block_any(ok != 0, (uint32_t*)smem)) return;  // every row of the block lies past its example's length
-  }
-  const uint32_t out_rows = ELT == 2 ? ok >> S::kLoads : ok;
-  uint32_t rowoff[S::kLoads];
-#pragma unroll
-  for (int i = 0; i < S::kLoads; ++i) {
-    const int row_l = row_of(i);
-    const int chunk = ELT == 2 ? (lane & 7) ^ (row_l & 7) : g;
-    rowoff[i] = (ok >> i) & 1u ? (uint32_t)(row_l * (int64_t)O.ld * ELT) + (chunk << 4) : kFarOff;
-  }
-  // descriptor over this row block, starting at the slab's first column
-  const uint8_t* base = (const uint8_t*)O.X + ((int64_t)row0 * O.ld + col0) * ELT;
-  const rsrc_t r = make_rsrc(base, (uint32_t)(((int64_t)nrows * O.ld - col0) * ELT));
-  const int kb0 = col0 / KR;
-  auto P = [&](int t, const uint8_t** fb, int64_t* fs) {
-    const int tt = t < O.nt ? t : 0;
-    *fs = (int64_t)O.ptile_nt[tt] * kFragBytes;
-    *fb = (const uint8_t*)O.ptile[tt] + (int64_t)O.ptile_local[tt] * kFragBytes + kb0 * *fs;
-  };
-  f32x4 acc[RT][NT];
-  auto clear = [&] {
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-      for (int t = 0; t < NT; ++t) acc[rt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  };
-  clear();
-  if constexpr (ELT == 2) {
-    stream_rows<RT, NT, D>(r, rowoff, d, O.nt, P, O.once != 0, acc, smem);
-  } else {
-    stream_rows_f32<RT, NT>(r, rowoff, d, O.nt, P, __any(ok != 0), acc, smem);
-    bool bad = false;
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-      for (int t = 0; t < NT; ++t)
-        if (t < O.nt) bad = bad || not_finite(acc[rt][t]);
-    if (__any(bad)) {  // an infinity or NaN among the inputs, or an overflow: float32 products
-      clear();
-      plain_rows_f32<RT, NT>(r, (uint32_t)((r_wave + m16) * (int64_t)O.ld * ELT), O.ld, out_rows, d, O.nt, P, acc);
-    }
-  }
-
-  // the map fragment is the first MFMA operand: lane (g, n) holds columns
-  // 4g .. 4g + 3 of token row n, one 16-byte store per tile
-  const int ldo = O.out_ld;
-  float* dst = out + O.out_base + ((int64_t)it.slab * O.rows + row0) * ldo;
-#pragma unroll
-  for (int rt = 0; rt < RT; ++rt) {
-    const int row = r_wave + rt * 16 + m16;
-    if ((out_rows >> rt) & 1u) {
-#pragma unroll
-      for (int t = 0; t < NT; ++t)
-        if (t < O.nt) *(f32x4*)(dst + (int64_t)row * ldo + t * 16 + 4 * g) = acc[rt][t];
-    }
-  }
-}
-
-template <int ELT, int NT>
-constexpr int split_lds() {
-  using S = SplitShape<ELT, NT>;
-  if constexpr (ELT == 2)
-    return StreamLds<S::kRT, NT, S::D>::kBytes;
-  else
-    return StreamF32Lds<NT>::kBytes;
-}
-constexpr int max_of(int a, int b) { return a > b ? a : b; }
-
 template <int ELT>
 __global__ __launch_bounds__(256, ELT == 2 ? 1 : 3) void split_stream_kernel(
     const SplitItem* __restrict__ items, const SplitOp* __restrict__ ops, float* __restrict__ out) {
@@ -163,15 +47,19 @@ __global__ __launch_bounds__(256, ELT == 2 ? 1 : 3) void split_stream_kernel(
   const SplitItem it = items[blockIdx.x];
   if (it.op < 0) return;  // padding item of the XCD-interleaved order
   const SplitOp& O = ops[it.op];
+  auto map = [&](int t, const uint8_t** base, int64_t* stride) {
+    *stride = (int64_t)O.ptile_nt[t] * kFragBytes;
+    *base = (const uint8_t*)O.ptile[t] + (int64_t)O.ptile_local[t] * kFragBytes;
+  };
   if (O.nt <= 2) {
-    split_stream_body<ELT, 2>(it, O, out, smem);
+    split_stream_body<ELT, 2, false>(it, O, map, out, smem, nullptr);
   } else if (ELT == 4 || O.nt <= 4) {  // float32 ops hold at most 4 tiles (kSplitMaxTilesF32)
-    split_stream_body<ELT, 4>(it, O, out, smem);
+    split_stream_body<ELT, 4, false>(it, O, map, out, smem, nullptr);
   } else if constexpr (ELT == 2) {
     if (O.nt <= 6)
-      split_stream_body<2, 6>(it, O, out, smem);
+      split_stream_body<2, 6, false>(it, O, map, out, smem, nullptr);
     else
-      split_stream_body<2, 8>(it, O, out, smem);
+      split_stream_body<2, 8, false>(it, O, map, out, smem, nullptr);
   }
 }
 

@@ -35,6 +35,7 @@ constexpr int kTopkWaves = kTopkThreads / 64;
 constexpr int kHistBits = 12;
 constexpr int kHistBins = 1 << kHistBits;
 constexpr int kCandMax = 2048;
+static_assert(kHistBins == 4 * kTopkThreads, "find_bin: four bins per thread, 64 groups of 64");
 constexpr int kSampleRuns = 64, kSampleRun = 256;   // 16384 sampled scores
 constexpr int64_t kSampleMinRow = (int64_t)1 << 16;  // rows this long use the sample
 
@@ -109,29 +110,38 @@ __global__ __launch_bounds__(kTopkThreads) void topk_kernel(const float* __restr
     }
   };
   auto bin_of = [](uint32_t key) { return key >> (32 - kHistBits); };
-  // highest bin whose suffix count (elements in bins >= it) reaches `need`,
-  // and that suffix count; 64 groups of 64 bins are summed in parallel
+  // highest bin whose suffix count (elements in bins >= it) reaches `need`
+  // (bin 0 if none does), and that suffix count: sums of 64 groups of 64 bins
+  // by 16 threads each, then one wave scans the groups and the chosen group's
+  // bins from the top (one thread walking them took 8 us of a short row's 20)
   auto find_bin = [&](uint32_t need) {
-    if (tid < 64) {
-      uint32_t s = 0;
-      for (int b = 0; b < 64; ++b) s += hist[tid * 64 + b];
-      total[tid] = s;
-    }
+    const uint32_t* h4 = hist + 4 * tid;
+    uint32_t s = h4[0] + h4[1] + h4[2] + h4[3];
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) s += __shfl_xor(s, o, 64);
+    if ((tid & 15) == 0) total[tid >> 4] = s;
     __syncthreads();
-    if (tid == 0) {
-      uint32_t cum = 0;  // elements in bins above the current one
-      int grp = 63;
-      for (; grp > 0; --grp) {
-        if (cum + total[grp] >= need) break;
-        cum += total[grp];
+    if (wave == 0) {
+      auto suffix = [&](uint32_t v) {  // inclusive, from the top lane down
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const uint32_t u = __shfl_down(v, o, 64);
+          if (lane + o < 64) v += u;
+        }
+        return v;
+      };
+      const uint32_t tg = total[lane], sg = suffix(tg);
+      const uint64_t bg = __ballot(sg >= need);
+      const int grp = bg ? 63 - __builtin_clzll(bg) : 0;
+      const uint32_t above = __shfl(sg, grp, 64) - __shfl(tg, grp, 64);
+      const uint32_t sb = above + suffix(hist[grp * 64 + lane]);
+      const uint64_t bb = __ballot(sb >= need);
+      const int bin = bb ? 63 - __builtin_clzll(bb) : 0;
+      const uint32_t cand = __shfl(sb, bin, 64);
+      if (lane == 0) {
+        s_bin = (uint32_t)(grp * 64 + bin);
+        s_cand = cand;
       }
-      int b = grp * 64 + 63;
-      for (; b > grp * 64; --b) {
-        if (cum + hist[b] >= need) break;
-        cum += hist[b];
-      }
-      s_bin = (uint32_t)b;
-      s_cand = cum + hist[b];
     }
     __syncthreads();
   };

@@ -1,0 +1,96 @@
+"""GPU parity of the scoring paths where they change over, against float64 torch
+on the same inputs: the row stream for few bf16 queries (tile counts 1 to 3, a
+last row block of one row, several slabs, cosine norms from the same pass, a
+workspace too small for it), the float32 tiles on split products (blocks of
+query rows past n_q, split features, non-finite rows) and the cosine norms they
+take along.
+
+Bounds: float32 sums of exact products, 1e-5 relative Frobenius; with a
+preconditioner bf16 queries are rounded once (5e-3, as in test_gpu_score.py)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2609_38767_amd as dt
+from gpu_util import host64, rel_fro
+from paper_2609_38767_amd.session import feature_rows, score
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def _rows(n, F, dtype, seed):
+    x = feature_rows(n, F, "bf16" if dtype == torch.bfloat16 else "f32", DEV)
+    x.copy_(torch.randn((n, F), generator=torch.Generator(device=DEV).manual_seed(seed), device=DEV))
+    return x
+
+
+def _ref(q, x, d, cosine):
+    q = q.double() * (d.double() if d is not None else 1.0)
+    x = x.double()
+    S = q @ x.t()
+    if cosine:
+        nq, nx = q.norm(dim=1), x.norm(dim=1)
+        S = S / (nq[:, None] * nx[None, :])
+        S = torch.where((nq[:, None] == 0) | (nx[None, :] == 0), torch.zeros_like(S), S)
+    return S.cpu().numpy()
+
+
+@pytest.mark.parametrize("n_q,n_t,F", [(1, 2049, 131072), (17, 1025, 262200), (48, 70001, 4008)])
+@pytest.mark.parametrize("precond,cosine", [(False, False), (True, False), (False, True), (True, True)])
+def test_row_stream(n_q, n_t, F, precond, cosine):
+    q, x = _rows(n_q, F, torch.bfloat16, 1), _rows(n_t, F, torch.bfloat16, 2)
+    x[3] = 0.0
+    d = torch.exp(torch.randn(F, device=DEV)) if precond else None
+    S, idx, val = score(q, x, d, topk=7, cosine=cosine)
+    S2 = score(q, x, d, cosine=cosine)[0]
+    torch.cuda.synchronize()
+    assert torch.equal(S, S2)
+    assert rel_fro(host64(S), _ref(q, x, d, cosine)) <= (5e-3 if precond else 1e-5)
+    top = torch.topk(S, 7, dim=1).values
+    assert torch.equal(val, top) and torch.equal(torch.gather(S, 1, idx.long()), val)
+
+
+def test_row_stream_small_workspace():
+    # a workspace without room for the stream's partial scores: same scores from the tile kernel
+    n_q, n_t, F = 2, 2048, 131080
+    q, x = _rows(n_q, F, torch.bfloat16, 3), _rows(n_t, F, torch.bfloat16, 4)
+    need = dt.dattri_score_workspace_bytes(n_q, n_t, F, dt.DATTRI_BF16, False, True, 0)
+    S = torch.empty((n_q, n_t), dtype=torch.float32, device=DEV)
+    full, part = torch.empty(need, dtype=torch.uint8, device=DEV), 32 * n_q * n_t * 4  # at most 32 feature splits
+    assert part < need
+    for nbytes in (need, part):
+        S.zero_()
+        dt.dattri_score(q, n_q, q.stride(0), x, n_t, x.stride(0), F, dt.DATTRI_BF16, None, S, 0, None, None, full, nbytes)
+        torch.cuda.synchronize()
+        assert rel_fro(host64(S), _ref(q, x, None, False)) <= 1e-5
+
+
+@pytest.mark.parametrize("n_q,n_t,F", [(1, 130, 36), (15, 129, 260), (65, 257, 1028), (200, 300, 4100)])
+@pytest.mark.parametrize("cosine", [False, True])
+def test_f32_split_tiles(n_q, n_t, F, cosine):
+    q, x = _rows(n_q, F, torch.float32, 5), _rows(n_t, F, torch.float32, 6)
+    x[5] = 0.0
+    d = torch.exp(torch.randn(F, device=DEV))
+    for pre in (None, d):
+        S = score(q, x, pre, cosine=cosine)[0]
+        torch.cuda.synchronize()
+        assert rel_fro(host64(S), _ref(q, x, pre, cosine)) <= 1e-5
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan"), 3.4e38])
+def test_f32_split_tiles_non_finite(value):
+    # one value of a training row: its column is what float32 products give, the others are untouched
+    q, x = _rows(70, 96, torch.float32, 7), _rows(140, 96, torch.float32, 8)
+    q[:, 11] *= 1e-3  # 3.4e38 times a query value stays finite
+    x[131, 11] = value
+    S = host64(score(q, x)[0])
+    ref = _ref(q, x, None, False)
+    keep = np.arange(140) != 131
+    assert rel_fro(S[:, keep], ref[:, keep]) <= 1e-5
+    if np.isfinite(value):
+        assert rel_fro(S[:, 131], ref[:, 131]) <= 1e-5
+    elif np.isinf(value):
+        assert np.array_equal(S[:, 131], ref[:, 131])
+    else:
+        assert np.all(np.isnan(S[:, 131]))
