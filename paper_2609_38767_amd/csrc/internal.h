@@ -81,7 +81,8 @@ struct ReduceTask {
 
 // Items with example < 0 are padding (the workgroup exits at once); they keep
 // the XCD-interleaved order exact.
-hipError_t launch_factored(int elt_bytes, int na, int nb, int aligned, const FactItem* items,
+// once: no two groups of the launch read the same input block.
+hipError_t launch_factored(int elt_bytes, int na, int nb, int aligned, int once, const FactItem* items,
                            int n_items, const FactGroup* groups, const FactMember* members,
                            float* partials, hipStream_t s);
 void factored_instance(int elt_bytes, int na_req, int nb_req, int aligned, int* na_inst,

@@ -88,7 +88,7 @@ __global__ __launch_bounds__(256, 2) void fsum_kernel(const FsumItem* __restrict
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[rt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
       if constexpr (kDma)
-        project_rows_dma<RT, NT>(r, r_wave, rows_valid, d, d, P, acc, smem);
+        project_rows_dma<RT, NT, true>(r, r_wave, rows_valid, d, d, P, acc, smem);
       else
         project_rows<ELT, AL, RT, NT, NT, PD>(r, r_wave, rows_valid, d, d, P, acc, pan);
 #pragma unroll
@@ -423,8 +423,13 @@ __global__ __launch_bounds__(256, QS == 1 ? 2 : 1) void token_kernel(const TokTa
 hipError_t launch_token_scores(const TokTask* tasks, int n_tasks, const void* phi_q, int q_bf16, int64_t ld_q,
                                int64_t n_q, int64_t n, int T, float* out, hipStream_t s) {
   if (n_tasks <= 0 || n_q <= 0 || n <= 0 || T <= 0) return hipSuccess;
-  const int QS = n_q >= kTokQueries ? kTokQueries : (n_q >= 2 ? 2 : 1);  // query slots per workgroup
-  const int64_t gx = (T + kTokTokens - 1) / kTokTokens, gz = (n_q + QS - 1) / QS;
+  // query slots per workgroup: fewer when the workgroups would leave CUs idle
+  // (each walks every layer, so its time hardly depends on the slots: 28 layers,
+  // 16 x 512 tokens, 4 queries: 64 workgroups 0.36 ms, 256 workgroups 0.15 ms)
+  const int64_t gx = (T + kTokTokens - 1) / kTokTokens;
+  int QS = n_q >= kTokQueries ? kTokQueries : (n_q >= 2 ? 2 : 1);
+  while (QS > 1 && gx * n * ((n_q + QS - 1) / QS) < 256) QS /= 2;
+  const int64_t gz = (n_q + QS - 1) / QS;
   if (n > 65535 || gz > 65535) return hipErrorInvalidValue;
   const dim3 grid((unsigned)gx, (unsigned)n, (unsigned)gz);
   if (QS == 4)

@@ -168,7 +168,9 @@ struct DmaLds {
   static constexpr int kBytes = kMapOff + 3 * kMapStage;
 };
 
-template <int RT, int NT>
+// kOnce: no other workgroup reads these rows, so they are streamed past L2's
+// other lines (nt).
+template <int RT, int NT, bool kOnce>
 __device__ inline void project_rows_dma(const rsrc_t r, int r_wave, int nrows, int d, int64_t ld,
                                         const FragSrc<NT>& P, f32x4 (&acc)[RT][NT], uint8_t* lds) {
   using C = DmaLds<RT, NT>;
@@ -209,7 +211,7 @@ __device__ inline void project_rows_dma(const rsrc_t r, int r_wave, int nrows, i
       const int c = (lane & 7) ^ (row_l & 7);  // the logical chunk that lands in this lane's slot
       const int row = r_wave + row_l, col = s * 64 + c * 8;
       const uint32_t off = (row < nrows && col < d) ? (uint32_t)(((int64_t)row * ld + col) * 2) : kOOB;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, DATTRI_LDS_PTR(xs + i * 1024), 16, off, 0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, DATTRI_LDS_PTR(xs + i * 1024), 16, off, 0, 0, kOnce ? 2 : 0);
     }
 #pragma unroll
     for (int i = 0; i < C::kMapLoads; ++i) {

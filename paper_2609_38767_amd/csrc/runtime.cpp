@@ -521,6 +521,8 @@ dattri_status dattri::build_plan(const dattri_ctx* ctx, dattri_route forced, Pla
       units[u].push_back(g);
       unit_cost[u] += group_cost[g];
     }
+    int once = 1;  // every input block of the launch belongs to one group
+    for (const auto& u : units) once = once && u.size() == 1;
     std::vector<int> order(units.size());
     for (size_t u = 0; u < units.size(); ++u) order[u] = (int)u;
     if (units.size() < (size_t)4 * kXcds) {
@@ -533,7 +535,7 @@ dattri_status dattri::build_plan(const dattri_ctx* ctx, dattri_route forced, Pla
           for (int c = 0; c < H.n_chunks; ++c)
             for (int g : units[u]) P.items.push_back({g, e, c, 0});
       }
-      P.launches.push_back({elt, I.na, I.nb, I.aligned, first, (int)P.items.size() - first});
+      P.launches.push_back({elt, I.na, I.nb, I.aligned, once, first, (int)P.items.size() - first});
       continue;
     }
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return unit_cost[a] > unit_cost[b]; });
@@ -553,7 +555,7 @@ dattri_status dattri::build_plan(const dattri_ctx* ctx, dattri_route forced, Pla
     for (size_t s = 0; s < len; ++s)
       for (int x = 0; x < kXcds; ++x)
         P.items.push_back(s < q[x].size() ? q[x][s] : FactItem{0, -1, 0, 0});
-    P.launches.push_back({elt, I.na, I.nb, I.aligned, first, (int)P.items.size() - first});
+    P.launches.push_back({elt, I.na, I.nb, I.aligned, once, first, (int)P.items.size() - first});
   }
 
   // ---- split form: one stage-1 op per factor block (a group's A, each
@@ -1349,7 +1351,7 @@ dattri_status dattri::run_plan(dattri_ctx* ctx, const Plan& P, void* phi, dattri
   float* fpart = (float*)(ws + P.off_fpart);
   const int phi_bf16 = phi_dtype == DATTRI_BF16;
   for (const Plan::Launch& L : P.launches)
-    HIP_TRY(launch_factored(L.elt, L.na, L.nb, L.aligned, d_items + L.first, L.count, d_groups,
+    HIP_TRY(launch_factored(L.elt, L.na, L.nb, L.aligned, L.once, d_items + L.first, L.count, d_groups,
                             d_members, fpart, s));
   if (P.n_fact_tasks)
     HIP_TRY(launch_reduce(d_tasks, P.n_fact_tasks, n, P.fact_max_out, fpart, phi, phi_bf16, ld_phi, s));
