@@ -73,18 +73,19 @@ __global__ __launch_bounds__(256) void pack_queries_kernel(const uint16_t* __res
     const int64_t blk = i >> 6;
     const int rb = (int)(blk / nks), ks = (int)(blk % nks);
     const int row = rb * 32 + (lane & 31), k = ks * 16 + 8 * (lane >> 5);
-    uint32_t h[8];
+    i32x4 w = {0, 0, 0, 0};
+    if (row < n_q && k < F) {  // rows are 16-byte aligned and F whole 16-byte chunks
+      w = *(const i32x4*)(Q + (int64_t)row * ldq + k);
+      if (d) {
+        const uint32_t h[4] = {(uint32_t)w.x, (uint32_t)w.y, (uint32_t)w.z, (uint32_t)w.w};
+        uint32_t r[4];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      uint32_t v = 0;
-      if (row < n_q && k + e < F) {
-        v = Q[(int64_t)row * ldq + k + e];
-        if (d) v = f32_to_bf16_bits(bf16_bits_to_f32(v) * d[k + e]);
+        for (int e = 0; e < 4; ++e)
+          r[e] = (uint32_t)f32_to_bf16_bits(bf16_bits_to_f32(h[e] & 0xFFFFu) * d[k + 2 * e]) |
+                 ((uint32_t)f32_to_bf16_bits(bf16_bits_to_f32(h[e] >> 16) * d[k + 2 * e + 1]) << 16);
+        w = i32x4{(int)r[0], (int)r[1], (int)r[2], (int)r[3]};
       }
-      h[e] = v;
     }
-    const i32x4 w = {(int)(h[0] | (h[1] << 16)), (int)(h[2] | (h[3] << 16)), (int)(h[4] | (h[5] << 16)),
-                     (int)(h[6] | (h[7] << 16))};
     *(i32x4*)(out + i * 16) = w;
   }
 }

@@ -87,23 +87,22 @@ __global__ __launch_bounds__(kTopkThreads) void topk_kernel(const float* __restr
   const int n = (int)n_train;
   const bool vec = ((uintptr_t)row & 15) == 0;  // uniform over the workgroup
 
-  // f(i, score) for every score of the row, 16-byte loads (two in flight per
+  // f(i, score) for every score of the row, 16-byte loads (four in flight per
   // thread) where the row is aligned
   auto for_row = [&](auto&& f) {
     if (vec) {
       const f32x4* r4 = (const f32x4*)row;
       const int n4 = n >> 2;
+      auto four = [&](int j, f32x4 a) { f(4 * j, a[0]); f(4 * j + 1, a[1]); f(4 * j + 2, a[2]); f(4 * j + 3, a[3]); };
       int j = tid;
-      for (; j + kTopkThreads < n4; j += 2 * kTopkThreads) {
-        const f32x4 a = r4[j], b = r4[j + kTopkThreads];
-        f(4 * j, a[0]); f(4 * j + 1, a[1]); f(4 * j + 2, a[2]); f(4 * j + 3, a[3]);
-        const int jb = j + kTopkThreads;
-        f(4 * jb, b[0]); f(4 * jb + 1, b[1]); f(4 * jb + 2, b[2]); f(4 * jb + 3, b[3]);
+      for (; j + 3 * kTopkThreads < n4; j += 4 * kTopkThreads) {
+        const f32x4 a = r4[j], b = r4[j + kTopkThreads], c = r4[j + 2 * kTopkThreads], d = r4[j + 3 * kTopkThreads];
+        four(j, a);
+        four(j + kTopkThreads, b);
+        four(j + 2 * kTopkThreads, c);
+        four(j + 3 * kTopkThreads, d);
       }
-      if (j < n4) {
-        const f32x4 a = r4[j];
-        f(4 * j, a[0]); f(4 * j + 1, a[1]); f(4 * j + 2, a[2]); f(4 * j + 3, a[3]);
-      }
+      for (; j < n4; j += kTopkThreads) four(j, r4[j]);
       for (int i = 4 * n4 + tid; i < n; i += kTopkThreads) f(i, row[i]);
     } else {
       for (int i = tid; i < n; i += kTopkThreads) f(i, row[i]);
