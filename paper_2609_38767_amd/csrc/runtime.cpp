@@ -53,8 +53,10 @@ dattri_cost_model default_cost_model() {
   // Fitted on MI355X (bf16 inputs; the calibration script's sweep of 28
   // single-layer shapes: transformer, adapter-shaped and narrow layers,
   // T = 16..4096, both forced routes timed with launch plans kept on the
-  // device), every rate held below its bound: AUTO picks the faster route on
-  // all 28 shapes, root-mean-square log error of the predictions 0.15.
+  // device), every rate held below its bound: AUTO picked the faster route on
+  // all 28 shapes, root-mean-square log error of the predictions 0.15; with
+  // the split form's row stream, which these rates do not price, on 21 of
+  // them (mean regret 5%, largest 32%: 8 -> 4096, T = 32, 64 examples).
   // gproject_gbs and gproject_tflops serve only the staged-G route, which
   // that sweep does not run.
   dattri_cost_model m;
