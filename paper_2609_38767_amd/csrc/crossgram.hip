@@ -200,11 +200,12 @@ __device__ inline void ghost_tile_dma(const GhostEntry& E, const GhostTile& tl, 
 // split once per tile and used by 128 products.  Two workgroups share a CU, so
 // one's splitting runs beside the other's MFMA.  live: this wave's 64 x 64
 // block has rows of both sides inside their lengths (others only stage).
+// Returns whether a Gram of this lane needs float32 products (split_unsafe).
 // Bound by the issue of 96 MFMA and about 220 vector instructions per stage
 // and wave.
 constexpr int kGhPlane = kGhRows * 64;  // bytes of one side's plane
 
-__device__ inline void ghost_tile_split(const GhostEntry& E, const GhostTile& tl, bool live, uint8_t* lds,
+__device__ inline bool ghost_tile_split(const GhostEntry& E, const GhostTile& tl, bool live, uint8_t* lds,
                                         f32x4 (&acc)[2][4][4]) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = lane >> 4, m16 = lane & 15, wm = wave >> 1, wn = wave & 1;
@@ -252,12 +253,14 @@ __device__ inline void ghost_tile_split(const GhostEntry& E, const GhostTile& tl
                                         : kOOB);
     }
   };
+  float big[2][2] = {{0.f, 0.f}, {0.f, 0.f}};  // largest magnitude of this thread's share of each row
   auto put = [&] {
 #pragma unroll
     for (int side = 0; side < 2; ++side)
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         const int row = (tid >> 2) + 64 * t;
+        big[side][t] = max_abs(max_abs(big[side][t], x[side][t][0]), x[side][t][1]);
         const Split3 v = split3(x[side][t][0], x[side][t][1]);
         uint8_t* w = lds + side * 3 * kGhPlane + row * 64 + ((pc ^ gswz16(row)) << 4);
         *(bf16x8*)w = v.hi;
@@ -289,13 +292,52 @@ __device__ inline void ghost_tile_split(const GhostEntry& E, const GhostTile& tl
     lds_barrier();
     if (live) multiply(c);
   };
+  float* line = (float*)(lds + 6 * kGhPlane);  // [Gram][side][128]: largest magnitude of each row
+  auto put_big = [&](int p) {
+#pragma unroll
+    for (int side = 0; side < 2; ++side)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {  // four threads hold the pieces of a row
+        float m = big[side][t];
+        m = fmaxf(m, __shfl_xor(m, 1, 64));
+        m = fmaxf(m, __shfl_xor(m, 2, 64));
+        if (pc == 0) line[(2 * p + side) * kGhRows + (tid >> 2) + 64 * t] = m;
+        big[side][t] = 0.f;
+      }
+  };
   for (int st = 0; st < nk0; ++st) stage(st, acc[0]);
+  put_big(0);
   for (int st = nk0; st < ns; ++st) stage(st, acc[1]);
+  put_big(1);
+  lds_barrier();
+  bool bad = false;
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    const float* l0 = line + 2 * p * kGhRows + wm * 64;
+    const float* l1 = line + (2 * p + 1) * kGhRows + wn * 64;
+    const float K = (float)(p ? E.d_out : E.d_in);
+    float mc[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      mc[j] = l1[16 * j + m16];
+      bad = bad || tiny_line(mc[j]);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const f32x4 mr = *(const f32x4*)(l0 + 16 * i + 4 * g);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        bad = bad || tiny_line(mr[r]);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) bad = bad || split_unsafe(acc[p][i][j][r], K, mr[r], mc[j]);
+      }
+    }
+  }
+  return bad;
 }
 
 // Register-staged form (unaligned rows; float32 tiles whose split products are
-// not finite): stages of 128 bytes
-// of features per row are double-buffered in LDS (rows XOR-swizzled by
+// unsafe): stages of 128 bytes of features per row are double-buffered in LDS (rows XOR-swizzled by
 // 16-byte chunk) and the next stage is prefetched into registers while the
 // current one is multiplied.  smem: 2 x 2 x 128 x 128 bytes.
 template <int ELT>
@@ -430,14 +472,7 @@ __global__ __launch_bounds__(256, 2) void ghost_kernel(const GhostEntry* __restr
     if (ELT == 2 && E.dma) {
       ghost_tile_dma(E, tl, &smem[0][0][0], acc);
     } else if (ELT == 4 && E.dma) {
-      ghost_tile_split(E, tl, any[0][wm] && any[1][wn], &smem[0][0][0], acc);
-      bool bad = false;
-#pragma unroll
-      for (int p = 0; p < 2; ++p)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) bad = bad || not_finite(acc[p][i][j]);
+      const bool bad = ghost_tile_split(E, tl, any[0][wm] && any[1][wn], &smem[0][0][0], acc);
       uint32_t* w = (uint32_t*)&smem[0][0][0];
       __syncthreads();
       if (threadIdx.x == 0) *w = 0u;
@@ -446,7 +481,7 @@ __global__ __launch_bounds__(256, 2) void ghost_kernel(const GhostEntry* __restr
       __syncthreads();
       const bool redo = *w != 0u;
       __syncthreads();
-      if (redo) {  // infinities or NaN among the inputs, or an overflow: float32 products
+      if (redo) {  // infinities, NaN, overflow or values too small to split: float32 products
 #pragma unroll
         for (int p = 0; p < 2; ++p)
 #pragma unroll

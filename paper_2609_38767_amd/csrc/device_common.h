@@ -131,12 +131,15 @@ __device__ inline f32x4 frag_mma<4>(i32x4 a, i32x4 b, f32x4 c) {
 
 // A float32 value as three bf16 terms, hi + mid + lo = v exactly (hi and mid
 // rounded to nearest: |v - hi| <= 2^-9 |v|, and the remainder left for lo has at
-// most 8 significant bits), for finite v whose rounded hi is finite and away
-// from the subnormals.  Products of two split values keep the six terms down
-// to 2^-18: the three left out are at most 2^-26 of the product together, below
+// most 8 significant bits), for finite v whose rounded hi is finite and
+// |v| >= 2^-103.  Products of two split values keep the six terms down to
+// 2^-18: the three left out are at most 2^-26 of the product together, below
 // the float32 rounding of the sum they are added to.  Non-finite values do not
-// survive the split (inf - inf): kernels that use it recompute in float32
-// wherever a result is not finite.
+// survive the split (inf - inf), and of smaller values up to 2^-125 is lost
+// (mid and lo fall among the bf16 subnormals).  Kernels that use it therefore
+// keep the largest magnitude of every row and column they split and recompute
+// in float32 wherever split_unsafe says that a result may miss more than its
+// own float32 rounding.
 struct Split3 {
   bf16x8 hi, mid, lo;
 };
@@ -181,11 +184,25 @@ __device__ inline f32x4 split_term(const Split3& a, const Split3& b, f32x4 c) {
   if constexpr (p == 4) return mfma_bf16_16(a.hi, b.mid, c);
   return mfma_bf16_16(a.hi, b.hi, c);
 }
-// Whether any element is infinite or NaN.
-__device__ inline bool not_finite(f32x4 v) {
-  const float s = (v.x - v.x) + (v.y - v.y) + (v.z - v.z) + (v.w - v.w);  // 0, or NaN
-  return !(s == 0.f);
+// max(m, |v.x|, |v.y|, |v.z|, |v.w|), NaN ignored: one instruction per two
+// values (written out: fmaxf would first quiet each loaded value).
+__device__ inline float max_abs(float m, i32x4 v) {
+  asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(v.x), "v"(v.y));
+  asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(v.z), "v"(v.w));
+  return m;
 }
+// Whether s, a sum of K split products of a row of largest magnitude mr and a
+// column of largest magnitude mc, may be off by more than 2^-24 of itself:
+// each of its values lost up to 2^-125, together K 2^-125 (mr + mc) at most,
+// and sums of products below 2^-126 round at 2^-150 in each of six terms.  An
+// exact zero stands (rows with zeros and disjoint rows are common) unless
+// tiny_line says otherwise; infinities and NaN are unsafe.
+__device__ inline bool split_unsafe(float s, float K, float mr, float mc) {
+  const float a = fabsf(s), least = K * fmaf(0x1p-101f, mr + mc, 0x1p-123f);
+  return !(a == 0.f || (a >= least && a <= 0x1.fffffep127f));
+}
+// A row or column of nothing but zeros and values too small to split.
+__device__ inline bool tiny_line(float m) { return m > 0.f && m < 0x1p-101f; }
 
 // Workgroup barrier that orders LDS accesses only.  __syncthreads() also
 // fences global memory, which makes the compiler wait for every outstanding

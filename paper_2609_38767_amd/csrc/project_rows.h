@@ -484,14 +484,16 @@ template <int NT>
 struct StreamF32Lds {
   static_assert(NT <= kWaves, "one map tile per wave is split");
   static constexpr int kPlane = NT * kFragBytes;  // hi, mid, lo planes of NT fragments
-  static constexpr int kBytes = 2 * 3 * kPlane;
+  static constexpr int kColMax = 2 * 3 * kPlane;  // largest magnitude of each map column, floats
+  static constexpr int kBytes = kColMax + NT * 16 * 4;
 };
 
 // rowoff[rt]: byte offset in `r` of this lane's 16 bytes of stage 0 in row
 // m16 of row tile rt (chunk lane / 16), or kFarOff for a row not to be read.
 // P, nt as for stream_rows; live: the wave has a row to read (uniform).
+// Returns whether a result of this lane needs float32 products (split_unsafe).
 template <int RT, int NT, class Frag>
-__device__ inline void stream_rows_f32(const rsrc_t r, const uint32_t (&rowoff)[RT], int d, int nt, const Frag& P,
+__device__ inline bool stream_rows_f32(const rsrc_t r, const uint32_t (&rowoff)[RT], int d, int nt, const Frag& P,
                                        bool live, f32x4 (&acc)[RT][NT], uint8_t* lds) {
   using C = StreamF32Lds<NT>;
   const int lane = threadIdx.x & 63, g = lane >> 4;
@@ -517,8 +519,12 @@ __device__ inline void stream_rows_f32(const rsrc_t r, const uint32_t (&rowoff)[
 #pragma unroll
     for (int h = 0; h < 2; ++h) m[h] = load16(rm, 2 * s + h < nkb ? (uint32_t)((2 * s + h) * m_stride + lane * 16) : kFarOff);
   };
+  float mcol = 0.f, mrow[RT];  // largest magnitudes of this lane's share of map column m16 and of its rows
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) mrow[rt] = 0.f;
   auto put_planes = [&](int buf, const i32x4 (&m)[2]) {
     if (splits) {
+      mcol = max_abs(max_abs(mcol, m[0]), m[1]);
       const Split3 v = split3(m[0], m[1]);
       uint8_t* w = lds + buf * 3 * C::kPlane + wave * kFragBytes + lane * 16;
       *(bf16x8*)w = v.hi;
@@ -553,6 +559,7 @@ __device__ inline void stream_rows_f32(const rsrc_t r, const uint32_t (&rowoff)[
         }
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
+          mrow[rt] = max_abs(max_abs(mrow[rt], x[q][rt][0]), x[q][rt][1]);
           const Split3 xv = split3(x[q][rt][0], x[q][rt][1]);
 #define DATTRI_TERM(p) _Pragma("unroll") for (int t = 0; t < NT; ++t) acc[rt][t] = split_term<p>(pv[t], xv, acc[rt][t]);
           DATTRI_TERM(0) DATTRI_TERM(1) DATTRI_TERM(2) DATTRI_TERM(3) DATTRI_TERM(4) DATTRI_TERM(5)
@@ -562,10 +569,42 @@ __device__ inline void stream_rows_f32(const rsrc_t r, const uint32_t (&rowoff)[
       load_x(s + 2, x[q]);
     }
   }
+  // lanes 16 apart hold the four pieces of a row, or of a map column
+  auto quad_max = [](float v) {
+    v = fmaxf(v, __shfl_xor(v, 16, 64));
+    return fmaxf(v, __shfl_xor(v, 32, 64));
+  };
+  float* cm = (float*)(lds + C::kColMax);
+  if (splits) {
+    mcol = quad_max(mcol);
+    if (g == 0) cm[wave * 16 + lane] = mcol;
+  }
+  lds_barrier();
+  bool bad = false;
+  if (live) {
+    const float K = (float)d;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      mrow[rt] = quad_max(mrow[rt]);
+      bad = bad || tiny_line(mrow[rt]);
+    }
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+      if (t < nt) {
+        const f32x4 c = *(const f32x4*)(cm + t * 16 + 4 * g);  // acc: columns 4g .. 4g + 3 of row m16
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          bad = bad || tiny_line(c[e]);
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt) bad = bad || split_unsafe(acc[rt][t][e], K, mrow[rt], c[e]);
+        }
+      }
+  }
+  return bad;
 }
 
 // The same product with float32 MFMA and operands loaded straight into
-// registers: for blocks whose split product is not finite.  row0: byte offset
+// registers: for blocks whose split products are unsafe.  row0: byte offset
 // in `r` of this lane's row of row tile 0 (rows 16 ld floats apart per tile),
 // rows: bit rt set where that row may be read.
 template <int RT, int NT, class Frag>

@@ -165,8 +165,8 @@ __global__ __launch_bounds__(256) void score_gemm_kernel(const uint8_t* __restri
 // (r / 2) mod 4); the waves read operands from there: 24 reads for 96 MFMA per
 // stage.  A value is split once per tile and used by 128 products.  Three
 // workgroups share a CU, so one's splitting runs beside another's MFMA.  Blocks of 16
-// query rows past n_q are not multiplied.  A tile whose result is not finite is
-// computed again in float32 MFMA from memory.  Bound by the issue of MFMA and
+// query rows past n_q are not multiplied.  A wave's block with a result that
+// the split may have cost bits (split_unsafe) is computed again in float32 MFMA from memory.  Bound by the issue of MFMA and
 // splitting: the whole cosine call for 256 x 8192 x 12288 takes 0.30 ms (0.52 ms
 // in float32 MFMA at 99 TFLOP/s, with a second read of both sides for the norms).
 constexpr int kPlane = kBM * 64;
@@ -211,7 +211,9 @@ __global__ __launch_bounds__(256, 2) void score_gemm_split_kernel(const uint8_t*
   };
   const bool sq = norms && qt == 0;  // uniform
   float nsq[2] = {0.f, 0.f};
-  auto put_one = [&](uint8_t* side, int r, const i32x4 (&v)[2]) {
+  float big[2][2] = {{0.f, 0.f}, {0.f, 0.f}};  // [Q, X][row, row + 64]: largest magnitude of this thread's share
+  auto put_one = [&](uint8_t* side, int r, const i32x4 (&v)[2], float& m) {
+    m = max_abs(max_abs(m, v[0]), v[1]);
     const Split3 s = split3(v[0], v[1]);
     uint8_t* w = side + plane_off(r, pc);
     *(bf16x8*)w = s.hi;
@@ -221,8 +223,8 @@ __global__ __launch_bounds__(256, 2) void score_gemm_split_kernel(const uint8_t*
   auto put = [&] {
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      if (64 * t < rows_q) put_one(lds, row + 64 * t, xq[t]);  // uniform
-      put_one(lds + 3 * kPlane, row + 64 * t, xx[t]);
+      if (64 * t < rows_q) put_one(lds, row + 64 * t, xq[t], big[0][t]);  // uniform
+      put_one(lds + 3 * kPlane, row + 64 * t, xx[t], big[1][t]);
       if (sq) nsq[t] = sum_sq<4>(xx[t][1], sum_sq<4>(xx[t][0], nsq[t]));
     }
   };
@@ -251,12 +253,39 @@ __global__ __launch_bounds__(256, 2) void score_gemm_split_kernel(const uint8_t*
       }
     }
   }
+  lds_barrier();  // the last stage's operands are read
+  float* line = (float*)lds;  // [Q, X][128]: largest magnitude of each row
+#pragma unroll
+  for (int side = 0; side < 2; ++side)
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {  // four threads hold the pieces of a row
+      float m = big[side][t];
+      m = fmaxf(m, __shfl_xor(m, 1, 64));
+      m = fmaxf(m, __shfl_xor(m, 2, 64));
+      if (pc == 0) line[side * kBM + row + 64 * t] = m;
+    }
+  lds_barrier();
   bool bad = false;
+  const float K = (float)((k1 - k0) * BK);
+  float mx[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int j = 0; j < 4; ++j) {
+    mx[j] = line[kBM + wn * 64 + 16 * j + m16];
+    bad = bad || tiny_line(mx[j]);
+  }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) bad = bad || not_finite(acc[i][j]);
-  if (__any(bad)) {  // infinities, NaN or overflow: this wave's block in float32 products, straight from memory
+  for (int i = 0; i < 4; ++i) {
+    const f32x4 mq = *(const f32x4*)(line + wm * 64 + 16 * i + 4 * g);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      bad = bad || tiny_line(mq[r]);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) bad = bad || split_unsafe(acc[i][j][r], K, mq[r], mx[j]);
+    }
+  }
+  // infinities, NaN, overflow or values too small to split: this wave's block
+  // in float32 products, straight from memory
+  if (__any(bad)) {
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll

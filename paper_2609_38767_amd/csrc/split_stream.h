@@ -96,14 +96,8 @@ __device__ inline void split_stream_body(const SplitItem& it, const SplitOp& O, 
   if constexpr (ELT == 2) {
     stream_rows<RT, NT, D, kNorm>(r, rowoff, d, O.nt, P, O.once != 0, acc, nsq, smem);
   } else {
-    stream_rows_f32<RT, NT>(r, rowoff, d, O.nt, P, __any(ok != 0), acc, smem);
-    bool bad = false;
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-      for (int t = 0; t < NT; ++t)
-        if (t < O.nt) bad = bad || not_finite(acc[rt][t]);
-    if (__any(bad)) {  // an infinity or NaN among the inputs, or an overflow: float32 products
+    const bool bad = stream_rows_f32<RT, NT>(r, rowoff, d, O.nt, P, __any(ok != 0), acc, smem);
+    if (__any(bad)) {  // infinities, NaN, overflow or values too small to split: float32 products
       clear();
       plain_rows_f32<RT, NT>(r, (uint32_t)(m16 * (int64_t)O.ld * ELT), O.ld, out_rows, d, O.nt, P, acc);
     }

@@ -94,3 +94,32 @@ def test_f32_split_tiles_non_finite(value):
         assert np.array_equal(S[:, 131], ref[:, 131])
     else:
         assert np.all(np.isnan(S[:, 131]))
+
+
+@pytest.mark.parametrize("n_q,q_scale", [(3, 1.0), (70, 1e18)])
+def test_f32_split_tiles_small_magnitudes(n_q, q_scale):
+    # training rows from ordinary size down to float32 subnormals in one tile:
+    # every column meets the float32 bound (scores of subnormal size, here from
+    # the unscaled queries, round at 2^-150: below 1e-2 of 1e-40 over 132 sums)
+    scales = [1.0, 1e-30, 1e-34, 1e-36, 1e-37, 1e-40, 0.0] * 20
+    q, x = _rows(n_q, 132, torch.float32, 9), _rows(140, 132, torch.float32, 10)
+    q *= q_scale
+    x *= torch.tensor(scales, dtype=torch.float32, device=DEV)[:, None]
+    S, ref = host64(score(q, x)[0]), _ref(q, x, None, False)
+    err = np.linalg.norm(S - ref, axis=0) / np.maximum(np.linalg.norm(ref, axis=0), 1e-300)
+    bound = np.array([1e-5 if s * q_scale >= 1e-37 or s == 0.0 else 1e-2 for s in scales])
+    assert np.all(err <= bound), dict(zip(scales, err))
+
+
+def test_f32_split_tiles_small_products():
+    # ordinary values whose products are not: scores of about 1e-35
+    q, x = _rows(20, 64, torch.float32, 11), _rows(130, 64, torch.float32, 12)
+    q *= 1e-18
+    x *= 1e-18
+    assert rel_fro(host64(score(q, x)[0]), _ref(q, x, None, False)) <= 1e-5
+    # rows of ordinary size whose smallest values meet the queries' largest
+    q, x = _rows(20, 64, torch.float32, 13), _rows(130, 64, torch.float32, 14)
+    q[:, :32] *= 1e30
+    q[:, 32:] *= 1e-10
+    x[:, :32] *= 1e-37
+    assert rel_fro(host64(score(q, x)[0]), _ref(q, x, None, False)) <= 1e-5

@@ -113,3 +113,41 @@ def test_split_stream_non_finite(value):
     host = [(host64(X), host64(Y)) for X, Y in inputs]
     clean = oracle_phi_rows(layers, oracle_maps(5, layers, "f32"), host, [0, 2], None)
     assert max(per_layer_errors(got[[0, 2]], clean, layers)) <= TOL
+
+
+def test_split_stream_small_magnitudes():
+    # examples of one token, from ordinary size down to float32 subnormals, side
+    # by side in one row block (the other side scaled so that phi stays normal):
+    # each block meets the float32 bound.  Sums of subnormal results round at
+    # 2^-150: 96 of them in a result of about 1e-40 stay below 1e-3 of it.
+    scales = [1.0, 1e-30, 1e-34, 1e-36, 1e-37, 1e-40, 0.0, 1.0]
+    layers = _layers([(96, 160, 32, 48)])
+
+    def edit(inputs):
+        for i, s in enumerate(scales):
+            inputs[0][0][i] *= s
+            inputs[0][1][i] *= 1e15 if 0.0 < s < 1e-20 else 1.0
+
+    inputs, got = _run(layers, len(scales), 1, "f32", edit=edit)
+    host = [(host64(A), host64(B)) for A, B in inputs]
+    ref = oracle_phi_rows(layers, oracle_maps(5, layers, "f32"), host, list(range(len(scales))), None)
+    errs = {s: np.linalg.norm(got[i] - ref[i]) / max(np.linalg.norm(ref[i]), 1e-300) for i, s in enumerate(scales)}
+    assert all(e <= (TOL if s == 0.0 or s > 1e-38 else 1e-3) for s, e in errs.items()), errs
+
+
+@pytest.mark.parametrize("side", [0, 1])
+def test_split_stream_small_maps(side):
+    # a map column too small to split beside ordinary ones
+    shape, seed, n, T = dict(d_in=64, d_out=96, k_in=16, k_out=16), 7, 3, 20
+    maps = [np.random.default_rng(seed).standard_normal((d, 16)).astype(np.float32) for d in (64, 96)]
+    maps[side][:, 5] *= 1e-36
+    s = ProjectionSession([shape], dtype="f32", seed=seed, form=dt.DATTRI_FORM_SPLIT, overrides={0: tuple(maps)})
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    A, B = (torch.randn((n, T, d), generator=g, device=DEV) * 1e2 for d in (64, 96))
+    s.capture(0, A, B)
+    got = host64(s.project(n, route=dt.DATTRI_ROUTE_FACTORED)).reshape(n, 16, 16)
+    a, b = (X.double().cpu().numpy() @ m.astype(np.float64) for X, m in zip((A, B), maps))
+    ref = np.einsum("itc,itr->icr", a, b)
+    for c in (5, 6):  # the small column and an ordinary one
+        x, y = (got[:, c], ref[:, c]) if side == 0 else (got[:, :, c], ref[:, :, c])
+        assert np.linalg.norm(x - y) <= TOL * np.linalg.norm(y)

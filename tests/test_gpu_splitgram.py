@@ -53,3 +53,22 @@ def test_cross_gram_non_finite(value):
     assert np.array_equal(np.isfinite(K[1]), fits)
     if fits.all():
         assert rel_fro(K[1], ref[1]) <= 1e-5
+
+
+@pytest.mark.parametrize("side", [0, 1])
+def test_cross_gram_small_magnitudes(side):
+    # one side's inputs (A or B) from ordinary size down to float32 subnormals,
+    # example by example in one tile, against rows scaled up so that K stays
+    # normal: every row meets the float32 bound
+    scales = [1.0, 1e-30, 1e-34, 1e-36, 1e-37, 1e-40]
+    dims = [(64, 40)]
+    a_blocks, _ = _batch(dims, len(scales), 20, "f32", 5)
+    b_blocks, _ = _batch(dims, 3, 20, "f32", 6)
+    for i, s in enumerate(scales):
+        a_blocks[0][side][i] *= s
+    b_blocks[0][side].mul_(1e15)
+    sa, sb = _session(dims, a_blocks, None, "f32"), _session(dims, b_blocks, None, "f32")
+    K = host64(cross_gram(sa, sb, dt.DATTRI_ROUTE_FACTORED))
+    ref = ocg.cross_gram(_oracle_batch(a_blocks, None), _oracle_batch(b_blocks, None))
+    err = np.linalg.norm(K - ref, axis=1) / np.linalg.norm(ref, axis=1)
+    assert np.all(err <= 1e-5), dict(zip(scales, err))
