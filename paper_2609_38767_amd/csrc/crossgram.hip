@@ -260,13 +260,18 @@ __device__ inline bool ghost_tile_split(const GhostEntry& E, const GhostTile& tl
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         const int row = (tid >> 2) + 64 * t;
-        big[side][t] = max_abs(max_abs(big[side][t], x[side][t][0]), x[side][t][1]);
         const Split3 v = split3(x[side][t][0], x[side][t][1]);
         uint8_t* w = lds + side * 3 * kGhPlane + row * 64 + ((pc ^ gswz16(row)) << 4);
         *(bf16x8*)w = v.hi;
         *(bf16x8*)(w + kGhPlane) = v.mid;
         *(bf16x8*)(w + 2 * kGhPlane) = v.lo;
       }
+  };
+  auto track = [&] {
+#pragma unroll
+    for (int side = 0; side < 2; ++side)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) big[side][t] = max_abs(max_abs(big[side][t], x[side][t][0]), x[side][t][1]);
   };
   auto get = [&](int side, int row) {
     const uint8_t* w = lds + side * 3 * kGhPlane + row * 64 + ((g ^ gswz16(row)) << 4);
@@ -288,6 +293,7 @@ __device__ inline bool ghost_tile_split(const GhostEntry& E, const GhostTile& tl
   auto stage = [&](int st, f32x4 (&c)[4][4]) {
     lds_barrier();  // the previous stage's operands are read
     put();
+    track();  // while the planes are written
     load(st + 1);  // past the last stage: columns past d, zeros never used
     lds_barrier();
     if (live) multiply(c);
@@ -310,30 +316,11 @@ __device__ inline bool ghost_tile_split(const GhostEntry& E, const GhostTile& tl
   for (int st = nk0; st < ns; ++st) stage(st, acc[1]);
   put_big(1);
   lds_barrier();
-  bool bad = false;
-#pragma unroll
-  for (int p = 0; p < 2; ++p) {
-    const float* l0 = line + 2 * p * kGhRows + wm * 64;
-    const float* l1 = line + (2 * p + 1) * kGhRows + wn * 64;
-    const float K = (float)(p ? E.d_out : E.d_in);
-    float mc[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      mc[j] = l1[16 * j + m16];
-      bad = bad || tiny_line(mc[j]);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const f32x4 mr = *(const f32x4*)(l0 + 16 * i + 4 * g);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        bad = bad || tiny_line(mr[r]);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) bad = bad || split_unsafe(acc[p][i][j][r], K, mr[r], mc[j]);
-      }
-    }
-  }
-  return bad;
+  const float* rows = line + wm * 64;
+  const float* cols = line + kGhRows + wn * 64;
+  const bool bad0 = block_unsafe(acc[0], (float)E.d_in, rows, cols);
+  const bool bad1 = block_unsafe(acc[1], (float)E.d_out, rows + 2 * kGhRows, cols + 2 * kGhRows);
+  return bad0 || bad1;
 }
 
 // Register-staged form (unaligned rows; float32 tiles whose split products are

@@ -191,18 +191,63 @@ __device__ inline float max_abs(float m, i32x4 v) {
   asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(v.z), "v"(v.w));
   return m;
 }
-// Whether s, a sum of K split products of a row of largest magnitude mr and a
-// column of largest magnitude mc, may be off by more than 2^-24 of itself:
-// each of its values lost up to 2^-125, together K 2^-125 (mr + mc) at most,
-// and sums of products below 2^-126 round at 2^-150 in each of six terms.  An
-// exact zero stands (rows with zeros and disjoint rows are common) unless
-// tiny_line says otherwise; infinities and NaN are unsafe.
-__device__ inline bool split_unsafe(float s, float K, float mr, float mc) {
-  const float a = fabsf(s), least = K * fmaf(0x1p-101f, mr + mc, 0x1p-123f);
-  return !(a == 0.f || (a >= least && a <= 0x1.fffffep127f));
+// The magnitude from which a sum of K split products of a row of largest
+// magnitude mr and a column of largest magnitude mc is safe, that is off by at
+// most 2^-24 of itself: each of its values lost up to 2^-125, together K 2^-125
+// (mr + mc) at most, and sums of products below 2^-126 round at 2^-150 in each
+// of six terms.  An exact zero stands (zero rows and disjoint rows are common)
+// unless a line is below kTinyLine: nothing but zeros and values too small to
+// split.
+constexpr float kTinyLine = 0x1p-101f;
+__device__ inline float split_safe(float K, float mr, float mc) { return K * fmaf(0x1p-101f, mr + mc, 0x1p-123f); }
+__device__ inline uint32_t split_unsafe(float s, float least) {
+  const float a = fabsf(s);
+  return a == 0.f || (a >= least && a <= 0x1.fffffep127f) ? 0u : 1u;
 }
-// A row or column of nothing but zeros and values too small to split.
-__device__ inline bool tiny_line(float m) { return m > 0.f && m < 0x1p-101f; }
+// The smallest nonzero magnitude among the values added, and the largest (NaN
+// if any is): the test of a whole block against its largest split_safe in four
+// instructions per two values, before any value is looked at by itself.
+struct NonzeroRange {
+  uint32_t lo = 0xFFFFFFFFu;  // 2 bits - 1 without the sign: zero comes out largest
+  float hi = 0.f;
+  __device__ void add(float a, float b) {
+    lo = min(min(lo, 2u * __builtin_bit_cast(uint32_t, a) - 1u), 2u * __builtin_bit_cast(uint32_t, b) - 1u);
+    asm("v_maximum3_f32 %0, |%1|, |%2|, %0" : "+v"(hi) : "v"(a), "v"(b));
+  }
+  __device__ void add(f32x4 v) { add(v.x, v.y); add(v.z, v.w); }
+  __device__ bool unsafe(float least) const {
+    return lo < 2u * __builtin_bit_cast(uint32_t, least) - 1u || !(hi <= 0x1.fffffep127f);
+  }
+};
+// Whether a wave's 64 x 64 block of sums of K split products (4 x 4 tiles;
+// rows, cols: the largest magnitudes of its 64 rows and 64 columns, in LDS) has
+// an unsafe one among this lane's.
+__device__ inline bool block_unsafe(const f32x4 (&acc)[4][4], float K, const float* rows, const float* cols) {
+  const int lane = threadIdx.x & 63, g = lane >> 4, m16 = lane & 15;
+  NonzeroRange lines, sums;
+  float mr = 0.f, mc = 0.f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const f32x4 r = *(const f32x4*)(rows + 16 * i + 4 * g);  // acc[i]: rows 16 i + 4 g .. + 3, column m16
+    const float c = cols[16 * i + m16];
+    mr = max_abs(mr, __builtin_bit_cast(i32x4, r));
+    mc = fmaxf(mc, c);
+    lines.add(r);
+    lines.add(c, c);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) sums.add(acc[i][j]);
+  }
+  uint32_t bad = lines.unsafe(kTinyLine) ? 1u : 0u;
+  if (__any(sums.unsafe(split_safe(K, mr, mc))))
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          bad |= split_unsafe(acc[i][j][r], split_safe(K, rows[16 * i + 4 * g + r], cols[16 * j + m16]));
+  return bad != 0u;
+}
 
 // Workgroup barrier that orders LDS accesses only.  __syncthreads() also
 // fences global memory, which makes the compiler wait for every outstanding

@@ -580,27 +580,36 @@ __device__ inline bool stream_rows_f32(const rsrc_t r, const uint32_t (&rowoff)[
     if (g == 0) cm[wave * 16 + lane] = mcol;
   }
   lds_barrier();
-  bool bad = false;
-  if (live) {
-    const float K = (float)d;
+  if (!live) return false;
+  const float K = (float)d;
+  NonzeroRange lines, sums;
+  float mr = 0.f, mc = 0.f;
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-      mrow[rt] = quad_max(mrow[rt]);
-      bad = bad || tiny_line(mrow[rt]);
+  for (int rt = 0; rt < RT; ++rt) {
+    mrow[rt] = quad_max(mrow[rt]);
+    mr = fmaxf(mr, mrow[rt]);
+    lines.add(mrow[rt], mrow[rt]);
+  }
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+    if (t < nt) {
+      const f32x4 c = *(const f32x4*)(cm + t * 16 + 4 * g);  // acc: columns 4g .. 4g + 3 of row m16
+      mc = max_abs(mc, __builtin_bit_cast(i32x4, c));
+      lines.add(c);
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) sums.add(acc[rt][t]);
     }
+  uint32_t bad = lines.unsafe(kTinyLine) ? 1u : 0u;
+  if (__any(sums.unsafe(split_safe(K, mr, mc))))
 #pragma unroll
     for (int t = 0; t < NT; ++t)
-      if (t < nt) {
-        const f32x4 c = *(const f32x4*)(cm + t * 16 + 4 * g);  // acc: columns 4g .. 4g + 3 of row m16
+      if (t < nt)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          bad = bad || tiny_line(c[e]);
+        for (int e = 0; e < 4; ++e)
 #pragma unroll
-          for (int rt = 0; rt < RT; ++rt) bad = bad || split_unsafe(acc[rt][t][e], K, mrow[rt], c[e]);
-        }
-      }
-  }
-  return bad;
+          for (int rt = 0; rt < RT; ++rt)
+            bad |= split_unsafe(acc[rt][t][e], split_safe(K, mrow[rt], cm[t * 16 + 4 * g + e]));
+  return bad != 0u;
 }
 
 // The same product with float32 MFMA and operands loaded straight into

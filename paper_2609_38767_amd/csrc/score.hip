@@ -212,8 +212,7 @@ __global__ __launch_bounds__(256, 2) void score_gemm_split_kernel(const uint8_t*
   const bool sq = norms && qt == 0;  // uniform
   float nsq[2] = {0.f, 0.f};
   float big[2][2] = {{0.f, 0.f}, {0.f, 0.f}};  // [Q, X][row, row + 64]: largest magnitude of this thread's share
-  auto put_one = [&](uint8_t* side, int r, const i32x4 (&v)[2], float& m) {
-    m = max_abs(max_abs(m, v[0]), v[1]);
+  auto put_one = [&](uint8_t* side, int r, const i32x4 (&v)[2]) {
     const Split3 s = split3(v[0], v[1]);
     uint8_t* w = side + plane_off(r, pc);
     *(bf16x8*)w = s.hi;
@@ -223,9 +222,14 @@ __global__ __launch_bounds__(256, 2) void score_gemm_split_kernel(const uint8_t*
   auto put = [&] {
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      if (64 * t < rows_q) put_one(lds, row + 64 * t, xq[t], big[0][t]);  // uniform
-      put_one(lds + 3 * kPlane, row + 64 * t, xx[t], big[1][t]);
+      if (64 * t < rows_q) put_one(lds, row + 64 * t, xq[t]);  // uniform
+      put_one(lds + 3 * kPlane, row + 64 * t, xx[t]);
       if (sq) nsq[t] = sum_sq<4>(xx[t][1], sum_sq<4>(xx[t][0], nsq[t]));
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {  // while the planes are written; query rows past the tile's are zero
+      big[0][t] = max_abs(max_abs(big[0][t], xq[t][0]), xq[t][1]);
+      big[1][t] = max_abs(max_abs(big[1][t], xx[t][0]), xx[t][1]);
     }
   };
   auto get = [&](const uint8_t* side, int r) {
@@ -265,24 +269,7 @@ __global__ __launch_bounds__(256, 2) void score_gemm_split_kernel(const uint8_t*
       if (pc == 0) line[side * kBM + row + 64 * t] = m;
     }
   lds_barrier();
-  bool bad = false;
-  const float K = (float)((k1 - k0) * BK);
-  float mx[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    mx[j] = line[kBM + wn * 64 + 16 * j + m16];
-    bad = bad || tiny_line(mx[j]);
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const f32x4 mq = *(const f32x4*)(line + wm * 64 + 16 * i + 4 * g);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      bad = bad || tiny_line(mq[r]);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) bad = bad || split_unsafe(acc[i][j][r], K, mq[r], mx[j]);
-    }
-  }
+  const bool bad = block_unsafe(acc, (float)((k1 - k0) * BK), line + wm * 64, line + kBM + wn * 64);
   // infinities, NaN, overflow or values too small to split: this wave's block
   // in float32 products, straight from memory
   if (__any(bad)) {
