@@ -502,11 +502,12 @@ __global__ __launch_bounds__(256, 2) void ghost_kernel(const GhostEntry* __restr
 // K[I][J] (diag: out[I]) = sum over entries of the block sums of segment
 // (i, j) = (I - out0, J) (diag: (I - out0, I - out0)) of every entry holding
 // that pair: blocks [i*Tp1/16, (i+1)*Tp1/16) x [j*Tp2/16, ...).  One workgroup
-// of 16 waves per output: wave w sums the entries w, w + 16, ... in order, lane
-// t the blocks t, t + 64, ... of each, then a fixed tree over lanes and waves.
-// (A whole workgroup per entry, one entry after another, spent 0.12 ms on the
-// latencies of 48 entries; 0.01 ms with 16 entries at a time.)
-constexpr int kGhRedWaves = 16;
+// of 16 waves per output.  The blocks of every such entry are cut into runs of
+// 256 (four loads in flight per lane), and the runs, entry after entry, are
+// dealt to the waves in turn, so that one entry of a long sequence fills them
+// as well as 48 short ones; each wave finds the entries 64 at a time.  Every
+// lane adds its blocks in order, then a fixed tree over lanes and waves.
+constexpr int kGhRedWaves = 16, kGhRedRun = 4 * 64;
 
 __global__ __launch_bounds__(64 * kGhRedWaves) void ghost_reduce_kernel(const GhostEntry* __restrict__ entries,
                                                            int n_entries, const float* __restrict__ parts,
@@ -516,22 +517,36 @@ __global__ __launch_bounds__(64 * kGhRedWaves) void ghost_reduce_kernel(const Gh
   const int cell = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int I = diag ? cell : cell / n_cols, J = diag ? cell : cell % n_cols;
   float s = 0.f;
-  for (int e = wave; e < n_entries; e += kGhRedWaves) {
-    const GhostEntry& E = entries[e];
-    const int i = I - E.out0, j = diag ? i : J;
-    if (i < 0 || i >= E.n1 || j < 0 || j >= E.n2) continue;
-    const int rb = E.Tp1 / 16, cb = E.Tp2 / 16;
-    const int nblk = rb * cb;
-    const float* p = parts + E.part_off + (int64_t)i * rb * E.nbc + j * cb;
-    for (int b0 = lane; b0 < nblk; b0 += 4 * 64) {  // four loads in flight per lane
-      float v[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int b = b0 + 64 * u;
-        v[u] = b < nblk ? p[(int64_t)(b / cb) * E.nbc + b % cb] : 0.f;
+  int run0 = 0;  // runs dealt so far
+  for (int e0 = 0; e0 < n_entries; e0 += 64) {
+    int rb = 0, cb = 0, nbc = 0;
+    int64_t first = 0;  // the segment's first block
+    if (e0 + lane < n_entries) {
+      const GhostEntry& E = entries[e0 + lane];
+      const int i = I - E.out0, j = diag ? i : J;
+      if (i >= 0 && i < E.n1 && j >= 0 && j < E.n2) {
+        rb = E.Tp1 / 16;
+        cb = E.Tp2 / 16;
+        nbc = E.nbc;
+        first = E.part_off + (int64_t)i * rb * nbc + j * cb;
       }
+    }
+    for (uint64_t m = __ballot(rb * cb > 0); m; m &= m - 1) {
+      const int src = __builtin_ctzll(m);
+      const int c = __builtin_amdgcn_readlane(cb, src), n_c = __builtin_amdgcn_readlane(nbc, src);
+      const int nblk = __builtin_amdgcn_readlane(rb, src) * c, runs = (nblk + kGhRedRun - 1) / kGhRedRun;
+      const float* p = parts + __shfl(first, src, 64);
+      for (int r = (wave - run0) & (kGhRedWaves - 1); r < runs; r += kGhRedWaves) {
+        float v[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) s += v[u];
+        for (int u = 0; u < 4; ++u) {
+          const int b = r * kGhRedRun + 64 * u + lane;
+          v[u] = b < nblk ? p[(int64_t)(b / c) * n_c + b % c] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) s += v[u];
+      }
+      run0 += runs;
     }
   }
 #pragma unroll

@@ -72,3 +72,20 @@ def test_cross_gram_small_magnitudes(side):
     ref = ocg.cross_gram(_oracle_batch(a_blocks, None), _oracle_batch(b_blocks, None))
     err = np.linalg.norm(K - ref, axis=1) / np.linalg.norm(ref, axis=1)
     assert np.all(err <= 1e-5), dict(zip(scales, err))
+
+
+@pytest.mark.parametrize("n_layers,n,T", [(1, 2, 1040), (3, 17, 33), (70, 2, 20)])
+def test_cross_gram_block_sums(n_layers, n, T):
+    # block sums dealt to the reducing waves in runs of 256: one entry of many
+    # runs (65 x 65 blocks, the last run short), entries of one run, more
+    # entries than a wave looks up at a time, and single examples' entries
+    dims = [(16, 8)] * n_layers
+    a_blocks, La = _batch(dims, n, T, "f32", 7, lengths=[T - i % 3 for i in range(n)])
+    b_blocks, _ = _batch(dims, 2, T, "f32", 8)
+    sa, sb = _session(dims, a_blocks, La, "f32"), _session(dims, b_blocks, None, "f32")
+    K, N = cross_gram(sa, sb, dt.DATTRI_ROUTE_FACTORED), sq_norms(sa, dt.DATTRI_ROUTE_FACTORED)
+    ref = ocg.cross_gram(_oracle_batch(a_blocks, La), _oracle_batch(b_blocks, None))
+    assert rel_fro(host64(K), ref) <= 1e-5
+    oa = _oracle_batch(a_blocks, La)
+    one = [[(A[i:i + 1], B[i:i + 1], L[i:i + 1]) for A, B, L in oa] for i in range(n)]
+    assert rel_fro(host64(N), np.array([ocg.cross_gram(o, o)[0, 0] for o in one])) <= 1e-5
