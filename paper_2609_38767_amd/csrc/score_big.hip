@@ -242,19 +242,23 @@ __global__ __launch_bounds__(256, 1) void score_gemm_256_kernel(const uint8_t* _
     }
 }
 
-// Sum of the K-split partial tiles (fixed order, deterministic): the W waves of
-// a workgroup own 64 outputs, wave w adds splits w, w + W, ... with four loads
-// in flight, then the waves' sums are added in wave order.  (A thread per output
-// walking 448 splits of 32 scores took 0.10 ms, all latency.)
-constexpr int kSumWaves = 16;
-__global__ __launch_bounds__(64 * kSumWaves) void splitk_sum_kernel(const float* __restrict__ part, int ks, int64_t n,
-                                                                    float* __restrict__ S) {
-  __shared__ float red[kSumWaves][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, W = blockDim.x >> 6;
-  const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+// Sum of the K-split partial tiles (fixed order, deterministic): W waves own 64
+// outputs, wave w adds splits w, w + W, ... with four loads in flight, then the
+// waves' sums are added in wave order.  A thread per output walking 448 splits
+// of 32 scores takes 42 us, all latency; 16 waves 3.4.  Many outputs fill the
+// chip by themselves, and waves that add two or three splits each only add
+// launches and barriers: 16 splits of 2^20 scores take 13 us with a wave per 64
+// outputs, 11 with 4 waves, 22 with 8 and 40 with 16.
+template <int W>
+__global__ __launch_bounds__(64 * (W > 4 ? W : 4)) void splitk_sum_kernel(const float* __restrict__ part, int ks,
+                                                                          int64_t n, float* __restrict__ S) {
+  constexpr int kWgWaves = W > 4 ? W : 4;
+  __shared__ float red[kWgWaves][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, w0 = wave % W;
+  const int64_t i = ((int64_t)blockIdx.x * (kWgWaves / W) + wave / W) * 64 + lane;
   float s = 0.f;
   if (i < n) {
-    int y = wave;
+    int y = w0;
     for (; y + 3 * W < ks; y += 4 * W) {
       const float v0 = part[(int64_t)y * n + i], v1 = part[(int64_t)(y + W) * n + i],
                   v2 = part[(int64_t)(y + 2 * W) * n + i], v3 = part[(int64_t)(y + 3 * W) * n + i];
@@ -262,21 +266,32 @@ __global__ __launch_bounds__(64 * kSumWaves) void splitk_sum_kernel(const float*
     }
     for (; y < ks; y += W) s += part[(int64_t)y * n + i];
   }
-  red[wave][lane] = s;
-  __syncthreads();
-  if (wave == 0 && i < n) {
-    for (int w = 1; w < W; ++w) s += red[w][lane];
-    S[i] = s;
+  if constexpr (W > 1) {
+    red[wave][lane] = s;
+    __syncthreads();
+    if (w0 == 0)
+      for (int w = 1; w < W; ++w) s += red[wave + w][lane];
   }
+  if (w0 == 0 && i < n) S[i] = s;
+}
+
+template <int W>
+static hipError_t launch_sum(const float* part, int ks, int64_t n, float* S, hipStream_t s) {
+  constexpr int kWgWaves = W > 4 ? W : 4, kOut = kWgWaves / W * 64;
+  const int64_t blocks = (n + kOut - 1) / kOut;
+  if (blocks > INT32_MAX) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(splitk_sum_kernel<W>, dim3((unsigned)blocks), dim3(64 * kWgWaves), 0, s, part, ks, n, S);
+  return hipGetLastError();
 }
 
 hipError_t launch_splitk_sum(const float* part, int ks, int64_t n, float* S, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  const int64_t blocks = (n + 63) / 64;
-  if (blocks > INT32_MAX) return hipErrorInvalidValue;
-  const int W = std::max(1, std::min(kSumWaves, ks / 2));
-  hipLaunchKernelGGL(splitk_sum_kernel, dim3((unsigned)blocks), dim3(64 * W), 0, s, part, ks, n, S);
-  return hipGetLastError();
+  // four splits per wave and round.  16 waves while 64-output groups leave the
+  // chip room (16384 outputs x 400 splits: 3.8 us, 4 waves 6.4; 65536 x 64: 4.1
+  // and 3.0), 4 from 16 splits (65536 x 16: 2.9 us, 8 waves 4.8, one 6.1)
+  if (ks >= 32 && n <= 16384) return launch_sum<16>(part, ks, n, S, s);
+  if (ks >= 16) return launch_sum<4>(part, ks, n, S, s);
+  return launch_sum<1>(part, ks, n, S, s);
 }
 
 // 128 x 128 kernel: split K while its tiles number fewer than kSmallTarget, into

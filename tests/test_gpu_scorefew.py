@@ -123,3 +123,18 @@ def test_f32_split_tiles_small_products():
     q[:, 32:] *= 1e-10
     x[:, :32] *= 1e-37
     assert rel_fro(host64(score(q, x)[0]), _ref(q, x, None, False)) <= 1e-5
+
+
+@pytest.mark.parametrize("n_q,n_t,F", [
+    (2, 131, 12292),    # 48 splits of 262 scores: 16 waves per 64 outputs, splits not a multiple of 64
+    (130, 400, 12292),  # as many splits of 52000 scores: 4 waves
+    (7, 40, 4612),      # 18 splits: 4 waves, the last round short
+    (33, 70, 2052),     # 8 splits: one wave, outputs past the last group
+])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_split_feature_sums(n_q, n_t, F, dtype):
+    F = F if dtype == torch.float32 else 2 * F
+    q, x = _rows(n_q, F, dtype, 15), _rows(n_t, F, dtype, 16)
+    S = score(q, x)[0]
+    assert torch.equal(S, score(q, x)[0])
+    assert rel_fro(host64(S), _ref(q, x, None, False)) <= 1e-5
