@@ -317,7 +317,7 @@ __global__ __launch_bounds__(256, 2) void score_gemm_split_kernel(const uint8_t*
 
 // ------------------------------------------------------ cosine normalization
 // inv[r] = 1 / |row r (times d, when given)|, 0 for a zero row.  One wave per
-// row (many rows), 16-byte loads (rows are 16-byte aligned and F a multiple of 16 bytes).
+// row, 16-byte loads (rows are 16-byte aligned and F a multiple of 16 bytes).
 template <int ELT>
 __global__ __launch_bounds__(256) void row_inv_norms_kernel(const uint8_t* __restrict__ X, int64_t ld,
                                                             int64_t rows, int64_t F,
@@ -366,18 +366,19 @@ __global__ __launch_bounds__(256) void scale_scores_kernel(float* __restrict__ S
   }
 }
 
-// The same for few rows: a workgroup per row, four loads in flight per thread
-// (one wave per row leaves a single query's 200k features to 450 round trips).
-template <int ELT>
-__global__ __launch_bounds__(1024) void row_inv_norms_wide_kernel(const uint8_t* __restrict__ X, int64_t ld, int64_t F,
+// Inverse norms of few long rows: NW waves per row, four loads in flight per
+// thread (one wave per row leaves a single query's 200k features to 450 round
+// trips).
+template <int ELT, int NW>
+__global__ __launch_bounds__(64 * NW) void row_inv_norms_wide_kernel(const uint8_t* __restrict__ X, int64_t ld, int64_t F,
                                                                   const float* __restrict__ d,
                                                                   float* __restrict__ inv) {
   constexpr int EPL = 16 / ELT;
-  __shared__ float red[16];
+  __shared__ float red[NW];
   const uint8_t* row = X + (int64_t)blockIdx.x * ld * ELT;
   float s = 0.f;
 #pragma unroll 4
-  for (int64_t f = (int64_t)threadIdx.x * EPL; f < F; f += 1024 * EPL) {
+  for (int64_t f = (int64_t)threadIdx.x * EPL; f < F; f += 64 * NW * EPL) {
     const i32x4 v = *(const i32x4*)(row + f * ELT);
     if (!d) {
       s = sum_sq<ELT>(v, s);
@@ -401,32 +402,38 @@ __global__ __launch_bounds__(1024) void row_inv_norms_wide_kernel(const uint8_t*
   if (threadIdx.x == 0) {
     float t = 0.f;
 #pragma unroll
-    for (int w = 0; w < 16; ++w) t += red[w];
+    for (int w = 0; w < NW; ++w) t += red[w];
     inv[blockIdx.x] = t > 0.f ? 1.f / sqrtf(t) : 0.f;
   }
+}
+
+template <int ELT>
+static hipError_t launch_norms(const uint8_t* X, int64_t ld, int64_t rows, int64_t F, const float* d, float* inv,
+                               hipStream_t s) {
+  // Waves per row.  Short rows (up to 8 KB): one, as a workgroup each costs more
+  // than it reads (2048 rows of 256 floats: 2.7 us, 16 waves 5.0).  Up to 128 KB:
+  // four, one load each in flight (512 rows of 12288 floats: 3.1 us, one wave
+  // 14.1; 2048 rows: 15.6 and 18.9).  Longer: 16 (one row of 229376 floats: 7.9
+  // us, 4 waves 14.1, one 98.9).  More than 2048 rows fill the chip with a wave
+  // each (4096 rows of 12288: 28.8 us either way).
+  const int64_t bytes = F * ELT;
+  if (rows <= 2048 && bytes > 131072) {
+    hipLaunchKernelGGL((row_inv_norms_wide_kernel<ELT, 16>), dim3((unsigned)rows), dim3(1024), 0, s, X, ld, F, d, inv);
+  } else if (rows <= 2048 && bytes > 8192) {
+    hipLaunchKernelGGL((row_inv_norms_wide_kernel<ELT, 4>), dim3((unsigned)rows), dim3(256), 0, s, X, ld, F, d, inv);
+  } else {
+    const int64_t b = (rows + 3) / 4;
+    if (b > INT32_MAX) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(row_inv_norms_kernel<ELT>, dim3((unsigned)b), dim3(256), 0, s, X, ld, rows, F, d, inv);
+  }
+  return hipGetLastError();
 }
 
 hipError_t launch_row_inv_norms(int elt, const void* X, int64_t ld, int64_t rows, int64_t F, const float* d, float* inv,
                                 hipStream_t s) {
   if (rows <= 0) return hipSuccess;
-  if (rows <= 2048) {
-    if (elt == 2)
-      hipLaunchKernelGGL(row_inv_norms_wide_kernel<2>, dim3((unsigned)rows), dim3(1024), 0, s, (const uint8_t*)X, ld, F,
-                         d, inv);
-    else
-      hipLaunchKernelGGL(row_inv_norms_wide_kernel<4>, dim3((unsigned)rows), dim3(1024), 0, s, (const uint8_t*)X, ld, F,
-                         d, inv);
-    return hipGetLastError();
-  }
-  const int64_t b = (rows + 3) / 4;
-  if (b > INT32_MAX) return hipErrorInvalidValue;
-  if (elt == 2)
-    hipLaunchKernelGGL(row_inv_norms_kernel<2>, dim3((unsigned)b), dim3(256), 0, s, (const uint8_t*)X, ld, rows, F, d,
-                       inv);
-  else
-    hipLaunchKernelGGL(row_inv_norms_kernel<4>, dim3((unsigned)b), dim3(256), 0, s, (const uint8_t*)X, ld, rows, F, d,
-                       inv);
-  return hipGetLastError();
+  return elt == 2 ? launch_norms<2>((const uint8_t*)X, ld, rows, F, d, inv, s)
+                  : launch_norms<4>((const uint8_t*)X, ld, rows, F, d, inv, s);
 }
 
 // S[q][j] = iq[q] / |x_j| sum over splits of part[y][q][j], |x_j|^2 the sum over

@@ -138,3 +138,17 @@ def test_split_feature_sums(n_q, n_t, F, dtype):
     S = score(q, x)[0]
     assert torch.equal(S, score(q, x)[0])
     assert rel_fro(host64(S), _ref(q, x, None, False)) <= 1e-5
+
+
+@pytest.mark.parametrize("nbytes", [8192, 8208, 131072, 131088])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("precond", [False, True])
+def test_row_norm_waves(nbytes, dtype, precond):
+    # query rows on both sides of the lengths at which a row's norm takes 1, 4 and 16 waves
+    F = nbytes // (4 if dtype == torch.float32 else 2)
+    q, x = _rows(5, F, dtype, 17), _rows(140, F, dtype, 18)
+    q[2] = 0.0
+    d = torch.exp(torch.randn(F, device=DEV)) if precond else None
+    S = score(q, x, d, cosine=True)[0]
+    bound = 5e-3 if precond and dtype == torch.bfloat16 else 1e-5
+    assert rel_fro(host64(S), _ref(q, x, d, True)) <= bound
