@@ -438,10 +438,11 @@ hipError_t launch_row_inv_norms(int elt, const void* X, int64_t ld, int64_t rows
 
 // S[q][j] = iq[q] / |x_j| sum over splits of part[y][q][j], |x_j|^2 the sum over
 // splits of norm_parts[y][j].  Thread: one training row, qpt queries.
-__global__ __launch_bounds__(256) void finish_cosine_kernel(const float* __restrict__ part, int ks, int64_t n_q,
-                                                            int64_t n_train, const float* __restrict__ iq,
-                                                            const float* __restrict__ norm_parts, int qpt,
-                                                            float* __restrict__ S) {
+// part may be S itself (one split): every thread reads an element before it
+// writes that element, and no other thread touches it.
+__global__ __launch_bounds__(256) void finish_cosine_kernel(const float* part, int ks, int64_t n_q, int64_t n_train,
+                                                            const float* __restrict__ iq,
+                                                            const float* __restrict__ norm_parts, int qpt, float* S) {
   const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (j >= n_train) return;
   float s = 0.f;

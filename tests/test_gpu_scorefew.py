@@ -152,3 +152,13 @@ def test_row_norm_waves(nbytes, dtype, precond):
     S = score(q, x, d, cosine=True)[0]
     bound = 5e-3 if precond and dtype == torch.bfloat16 else 1e-5
     assert rel_fro(host64(S), _ref(q, x, d, True)) <= bound
+
+
+@pytest.mark.parametrize("n_q,n_t", [(3, 130), (150, 300)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_cosine_unsplit_features(n_q, n_t, dtype):
+    # too few features to split: the scores are scaled in place
+    F = 256 if dtype == torch.float32 else 512
+    q, x = _rows(n_q, F, dtype, 19), _rows(n_t, F, dtype, 20)
+    x[7] = 0.0
+    assert rel_fro(host64(score(q, x, cosine=True)[0]), _ref(q, x, None, True)) <= 1e-5
