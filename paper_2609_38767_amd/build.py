@@ -43,7 +43,7 @@ def sources():
 
 # Host-code sanitizers (each flag after -Xarch_host: host code only).
 SANITIZE = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined",
-            "-Xarch_host", "-fno-sanitize-recover=all", "-fno-omit-frame-pointer", "-g"]
+            "-Xarch_host", "-fsanitize=float-cast-overflow", "-Xarch_host", "-fno-sanitize-recover=all", "-fno-omit-frame-pointer", "-g"]
 
 
 def _compile(src, build_dir=BUILD, sanitize=False):

@@ -800,7 +800,7 @@ dattri_status dattri::build_plan(const dattri_ctx* ctx, dattri_route forced, Pla
           const SplitOp& O = P.sops[units[u][0]];
           const int rbs = (O.rows + rows_wg - 1) / rows_wg;
           const double cost = (double)O.ld * O.rows * (double)units[u].size();
-          const int cuts = (int)std::min<int64_t>(std::max(rbs, 1), (int64_t)std::ceil(cost / (total / 64.0)));
+          const int cuts = (int)std::min<int64_t>(std::max(rbs, 1), total > 0.0 ? (int64_t)std::ceil(cost / (total / 64.0)) : 1);
           for (int c = 0; c < cuts; ++c) {
             const int rb0 = (int)((int64_t)rbs * c / cuts), rb1 = (int)((int64_t)rbs * (c + 1) / cuts);
             if (rb1 > rb0) pieces.push_back({u, rb0, rb1, cost * (rb1 - rb0) / rbs, (double)O.slab_cols});
@@ -826,12 +826,12 @@ dattri_status dattri::build_plan(const dattri_ctx* ctx, dattri_route forced, Pla
         const int first = (int)P.sitems.size();
         P.sitems.resize(P.sitems.size() + len * kXcds, SplitItem{-1, 0, 0, 0});
         for (int x = 0; x < kXcds; ++x) {
-          SplitItem* at = P.sitems.data() + first + x;
+          size_t at = (size_t)first + x;
           for (const Piece& p : q[x])
             for (int rb = p.rb0; rb < p.rb1; ++rb)
               for (int sl = 0; sl < P.sops[units[p.unit][0]].n_slabs; ++sl)
                 for (size_t o : units[p.unit]) {
-                  *at = {(int)o, rb, sl, 0};
+                  P.sitems[at] = {(int)o, rb, sl, 0};
                   at += kXcds;
                 }
         }

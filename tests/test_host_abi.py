@@ -130,6 +130,23 @@ def test_factored_limits_and_auto_route(ctx):
     assert dt.dattri_workspace_bytes(ctx, dt.DATTRI_ROUTE_MATERIALIZED) > 0
 
 
+@pytest.mark.parametrize("n,T", [(4, 0), (0, 16), (0, 0)])
+@pytest.mark.parametrize("dtype", [dt.DATTRI_F32, dt.DATTRI_BF16])
+def test_plans_of_empty_captures(dtype, n, T):
+    # no token rows: every form plans without a division by the (zero) work,
+    # which the sanitizer build of these tests would report
+    fake = 1 << 40
+    for form in (dt.DATTRI_FORM_AUTO, dt.DATTRI_FORM_FUSED, dt.DATTRI_FORM_SPLIT):
+        c = dt.dattri_create(dtype, 0)
+        for l, (d_in, d_out) in enumerate([(64, 96), (65, 33), (256, 4096)]):
+            dt.dattri_register_layer(c, d_in, d_out, 16, 64)
+            dt.dattri_capture_layer(c, l, fake, fake + (1 << 36), n, T)
+        dt.dattri_set_factored_form(c, form)
+        for route in (dt.DATTRI_ROUTE_AUTO, dt.DATTRI_ROUTE_FACTORED, dt.DATTRI_ROUTE_MATERIALIZED):
+            assert dt.dattri_workspace_bytes(c, route) > 0
+        dt.dattri_destroy(c)
+
+
 def test_score_argument_errors():
     fake = 1 << 40
     f32 = dt.DATTRI_F32
