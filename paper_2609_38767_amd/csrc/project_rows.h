@@ -168,8 +168,11 @@ struct DmaLds {
   static constexpr int kBytes = kMapOff + 3 * kMapStage;
 };
 
-// kOnce: no other workgroup reads these rows, so they are streamed past L2's
-// other lines (nt).
+// kOnce: rows are streamed past L2's other lines (nt): right where no other
+// workgroup of the same XCD reads them about the same time.  (The factor sums
+// set it always: layers that share an input are separate ops there, mostly on
+// different XCDs.  4 Qwen-shaped blocks with shared inputs, 32 x 512 rows: k =
+// 64 1.95 ms with, 1.96 without; k = 16 2.20 both.)
 template <int RT, int NT, bool kOnce>
 __device__ inline void project_rows_dma(const rsrc_t r, int r_wave, int nrows, int d, int64_t ld,
                                         const FragSrc<NT>& P, f32x4 (&acc)[RT][NT], uint8_t* lds) {
@@ -301,42 +304,8 @@ struct StreamLds {
 // reads, draining the ring each stage.
 template <int RT, int NT>
 __device__ inline void read_frags(i32x4 (&x)[RT], i32x4 (&p)[NT], uint32_t xa, uint32_t pa) {
-  static_assert((RT == 2 || RT == 4) && (NT == 2 || NT == 4 || NT == 6 || NT == 8), "row and map tiles");
-  if constexpr (RT == 2 && NT == 2)
-    asm volatile("ds_read_b128 %0, %[xa] offset:0\n\t" "ds_read_b128 %1, %[xa] offset:2048\n\t"
-                 "ds_read_b128 %2, %[pa] offset:0\n\t" "ds_read_b128 %3, %[pa] offset:1024\n\t"
-                 "s_waitcnt lgkmcnt(0)"
-                 : "=&v"(x[0]), "=&v"(x[1]), "=&v"(p[0]), "=&v"(p[1])
-                 : [xa] "v"(xa), [pa] "v"(pa)
-                 : "memory");
-  else if constexpr (RT == 2 && NT == 4)
-    asm volatile("ds_read_b128 %0, %[xa] offset:0\n\t" "ds_read_b128 %1, %[xa] offset:2048\n\t"
-                 "ds_read_b128 %2, %[pa] offset:0\n\t" "ds_read_b128 %3, %[pa] offset:1024\n\t"
-                 "ds_read_b128 %4, %[pa] offset:2048\n\t" "ds_read_b128 %5, %[pa] offset:3072\n\t"
-                 "s_waitcnt lgkmcnt(0)"
-                 : "=&v"(x[0]), "=&v"(x[1]), "=&v"(p[0]), "=&v"(p[1]), "=&v"(p[2]), "=&v"(p[3])
-                 : [xa] "v"(xa), [pa] "v"(pa)
-                 : "memory");
-  else if constexpr (RT == 2 && NT == 6)
-    asm volatile("ds_read_b128 %0, %[xa] offset:0\n\t" "ds_read_b128 %1, %[xa] offset:2048\n\t"
-                 "ds_read_b128 %2, %[pa] offset:0\n\t" "ds_read_b128 %3, %[pa] offset:1024\n\t"
-                 "ds_read_b128 %4, %[pa] offset:2048\n\t" "ds_read_b128 %5, %[pa] offset:3072\n\t"
-                 "ds_read_b128 %6, %[pa] offset:4096\n\t" "ds_read_b128 %7, %[pa] offset:5120\n\t"
-                 "s_waitcnt lgkmcnt(0)"
-                 : "=&v"(x[0]), "=&v"(x[1]), "=&v"(p[0]), "=&v"(p[1]), "=&v"(p[2]), "=&v"(p[3]), "=&v"(p[4]), "=&v"(p[5])
-                 : [xa] "v"(xa), [pa] "v"(pa)
-                 : "memory");
-  else if constexpr (RT == 2 && NT == 8)
-    asm volatile("ds_read_b128 %0, %[xa] offset:0\n\t" "ds_read_b128 %1, %[xa] offset:2048\n\t"
-                 "ds_read_b128 %2, %[pa] offset:0\n\t" "ds_read_b128 %3, %[pa] offset:1024\n\t"
-                 "ds_read_b128 %4, %[pa] offset:2048\n\t" "ds_read_b128 %5, %[pa] offset:3072\n\t"
-                 "ds_read_b128 %6, %[pa] offset:4096\n\t" "ds_read_b128 %7, %[pa] offset:5120\n\t"
-                 "ds_read_b128 %8, %[pa] offset:6144\n\t" "ds_read_b128 %9, %[pa] offset:7168\n\t"
-                 "s_waitcnt lgkmcnt(0)"
-                 : "=&v"(x[0]), "=&v"(x[1]), "=&v"(p[0]), "=&v"(p[1]), "=&v"(p[2]), "=&v"(p[3]), "=&v"(p[4]), "=&v"(p[5]), "=&v"(p[6]), "=&v"(p[7])
-                 : [xa] "v"(xa), [pa] "v"(pa)
-                 : "memory");
-  else if constexpr (RT == 4 && NT == 2)
+  static_assert(RT == 4 && (NT == 2 || NT == 4 || NT == 6 || NT == 8), "row and map tiles");
+  if constexpr (NT == 2)
     asm volatile("ds_read_b128 %0, %[xa] offset:0\n\t" "ds_read_b128 %1, %[xa] offset:2048\n\t"
                  "ds_read_b128 %2, %[xa] offset:4096\n\t" "ds_read_b128 %3, %[xa] offset:6144\n\t"
                  "ds_read_b128 %4, %[pa] offset:0\n\t" "ds_read_b128 %5, %[pa] offset:1024\n\t"
@@ -344,7 +313,7 @@ __device__ inline void read_frags(i32x4 (&x)[RT], i32x4 (&p)[NT], uint32_t xa, u
                  : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(p[0]), "=&v"(p[1])
                  : [xa] "v"(xa), [pa] "v"(pa)
                  : "memory");
-  else if constexpr (RT == 4 && NT == 4)
+  else if constexpr (NT == 4)
     asm volatile("ds_read_b128 %0, %[xa] offset:0\n\t" "ds_read_b128 %1, %[xa] offset:2048\n\t"
                  "ds_read_b128 %2, %[xa] offset:4096\n\t" "ds_read_b128 %3, %[xa] offset:6144\n\t"
                  "ds_read_b128 %4, %[pa] offset:0\n\t" "ds_read_b128 %5, %[pa] offset:1024\n\t"
@@ -353,7 +322,7 @@ __device__ inline void read_frags(i32x4 (&x)[RT], i32x4 (&p)[NT], uint32_t xa, u
                  : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(p[0]), "=&v"(p[1]), "=&v"(p[2]), "=&v"(p[3])
                  : [xa] "v"(xa), [pa] "v"(pa)
                  : "memory");
-  else if constexpr (RT == 4 && NT == 6)
+  else if constexpr (NT == 6)
     asm volatile("ds_read_b128 %0, %[xa] offset:0\n\t" "ds_read_b128 %1, %[xa] offset:2048\n\t"
                  "ds_read_b128 %2, %[xa] offset:4096\n\t" "ds_read_b128 %3, %[xa] offset:6144\n\t"
                  "ds_read_b128 %4, %[pa] offset:0\n\t" "ds_read_b128 %5, %[pa] offset:1024\n\t"
@@ -363,7 +332,7 @@ __device__ inline void read_frags(i32x4 (&x)[RT], i32x4 (&p)[NT], uint32_t xa, u
                  : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(p[0]), "=&v"(p[1]), "=&v"(p[2]), "=&v"(p[3]), "=&v"(p[4]), "=&v"(p[5])
                  : [xa] "v"(xa), [pa] "v"(pa)
                  : "memory");
-  else if constexpr (RT == 4 && NT == 8)
+  else if constexpr (NT == 8)
     asm volatile("ds_read_b128 %0, %[xa] offset:0\n\t" "ds_read_b128 %1, %[xa] offset:2048\n\t"
                  "ds_read_b128 %2, %[xa] offset:4096\n\t" "ds_read_b128 %3, %[xa] offset:6144\n\t"
                  "ds_read_b128 %4, %[pa] offset:0\n\t" "ds_read_b128 %5, %[pa] offset:1024\n\t"
