@@ -653,19 +653,23 @@ dattri_status dattri::build_plan(const dattri_ctx* ctx, dattri_route forced, Pla
     // slots + s / 2 behind its start (half an item of tail), and every item
     // adds a fixed cost c, in bytes of streaming: its prologue and its
     // projected rows written and read again.  The sum is least at s =
-    // sqrt(2 c W / slots).
+    // sqrt(2 c W / slots).  A block of fewer rows than its map has columns
+    // streams the map for longer than its rows and is counted by those (24
+    // layers of 1024 -> 4096, k = 64, 32 rows: 39 us a call with whole-width
+    // items, 27 with four slabs).
     double work = 0.0, fixed = 0.0;
+    auto stream_rows_of = [](const SplitOp& O, int r) { return (double)std::max(r, O.nt * 16); };
     const int srows = split_stream_rows(elt), slots = elt == 2 ? kCus : 3 * kCus;
     for (size_t o = op0; o < P.sops.size(); ++o) {
       const SplitOp& O = P.sops[o];
-      const double bytes = (double)O.rows * O.ld * elt;
+      const double bytes = stream_rows_of(O, O.rows) * O.ld * elt;
       work += bytes;
-      fixed += bytes * ((elt == 2 ? 65536.0 : 24576.0) + 2.0 * srows * O.nt * 16 * 4);
+      fixed += bytes * ((elt == 2 ? 65536.0 : 24576.0) + 2.0 * std::min(O.rows, srows) * O.nt * 16 * 4);
     }
     const double item_bytes = work > 0 ? std::sqrt(2.0 * (fixed / work) * work / slots) : 1.0;
     for (size_t o = op0; o < P.sops.size(); ++o) {
       SplitOp& O = P.sops[o];
-      const double row_bytes = (double)std::min(O.rows, srows) * O.ld * elt;
+      const double row_bytes = stream_rows_of(O, std::min(O.rows, srows)) * O.ld * elt;
       const int64_t cap = std::max<int64_t>(1, O.ld / kSplitSlabQuantum);
       const int64_t want = std::min<int64_t>(cap, std::max<int64_t>(1, std::llround(row_bytes / item_bytes)));
       O.slab_cols = (int32_t)(((O.ld + want - 1) / want + kSplitSlabQuantum - 1) / kSplitSlabQuantum * kSplitSlabQuantum);

@@ -68,6 +68,8 @@ def _check(layers, inputs, got, n, dtype, lengths=None, seed=5):
     ([(136, 520, 64, 32)], 5, 300, [0, 300, 1, 17, 256], False),
     # few workgroups over long sequences: token chunks and their reduction; several slabs
     ([(4104, 64, 16, 16)], 2, 1100, [1100, 513], False),
+    # fewer rows than map columns: slabs set by the map's width
+    ([(4104, 1032, 64, 64), (4104, 2056, 16, 16)], 1, 20, [17], False),
 ])
 def test_split_stream_edges(dtype, shapes, n, T, lengths, shared):
     layers = _layers(shapes, shared)
