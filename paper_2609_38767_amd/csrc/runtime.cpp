@@ -682,12 +682,19 @@ dattri_status dattri::build_plan(const dattri_ctx* ctx, dattri_route forced, Pla
       O.out_ld = O.nt * 16;
       proj_floats += (size_t)O.n_slabs * O.rows * O.out_ld;
     }
-    // Contraction: one workgroup per (layer, example) unless that leaves most
-    // CUs idle over long sequences (then chunks of 512 tokens), and at most
-    // 65536 tokens per chunk (byte offsets inside a chunk stay below 2 GiB).
-    // It adds the slabs on load; where few workgroups would each add many, or
-    // projected rows are kept for a later pass, they are added into slab 0 by
-    // a launch of their own first.
+    // Contraction: one workgroup per (layer, example) unless that leaves half
+    // the CUs idle over more than two rounds of its eight waves (128 tokens
+    // each): a round is a chain of loads, 3.5 to 5 us whatever the chip does
+    // besides.  Then the tokens are cut into as many chunks as there are rounds,
+    // up to one workgroup per CU, for a reduction of their partial blocks (1
+    // layer of 1024 -> 4096, k = 64, 8 x 1024 tokens: 64 -> 40 us a call; one
+    // example of 768 -> 64: 47 -> 21).  At most 65536 tokens per chunk (byte
+    // offsets inside a chunk stay below 2 GiB).
+    // It adds the slabs on load; where few workgroups would each add many (more
+    // than 8: 4 Pythia-shaped float32 layers, 512 tokens, 59 us without a launch
+    // of their own, 46 with; between 4 and 8 both take the same), or projected
+    // rows are kept for a later pass, they are added into slab 0 by a launch of
+    // their own first.
     const int64_t con_wgs = (int64_t)pend.size() * std::max(n, 1);
     size_t spart_floats = 0;
     std::vector<char> sum_op(P.sops.size(), 0);
@@ -699,7 +706,8 @@ dattri_status dattri::build_plan(const dattri_ctx* ctx, dattri_route forced, Pla
       if (pre) sum_op[pend[i].a_op] = sum_op[pend[i].b_op] = 1;
       C.a_base = A.out_base; C.a_ld = A.out_ld; C.a_slabs = A.n_slabs;
       C.b_base = B.out_base; C.b_ld = B.out_ld; C.b_slabs = B.n_slabs;
-      C.tok_chunk = con_wgs < kCus / 2 && C.T > 1024 ? 512 : std::max(std::min(C.T, 65536), 1);
+      const int64_t chunks = con_wgs < kCus / 2 && C.T > 256 ? std::min<int64_t>((C.T + 127) / 128, kCus / con_wgs) : 1;
+      C.tok_chunk = chunks > 1 ? (int32_t)(((C.T + chunks - 1) / chunks + 127) / 128 * 128) : std::max(std::min(C.T, 65536), 1);
       C.n_tchunks = std::max(1, (C.T + C.tok_chunk - 1) / C.tok_chunk);
       P.split_max_tchunks = std::max(P.split_max_tchunks, C.n_tchunks);
       P.split_na = std::max(P.split_na, tiles16(C.k_in));

@@ -68,6 +68,9 @@ def _check(layers, inputs, got, n, dtype, lengths=None, seed=5):
     ([(136, 520, 64, 32)], 5, 300, [0, 300, 1, 17, 256], False),
     # few workgroups over long sequences: token chunks and their reduction; several slabs
     ([(4104, 64, 16, 16)], 2, 1100, [1100, 513], False),
+    # the first length that is cut into chunks: the last one of a single token, an example ending in each chunk
+    ([(64, 96, 32, 64)], 3, 257, [257, 128, 129], False),
+    ([(72, 64, 128, 64)], 2, 520, None, False),
     # fewer rows than map columns: slabs set by the map's width
     ([(4104, 1032, 64, 64), (4104, 2056, 16, 16)], 1, 20, [17], False),
 ])
