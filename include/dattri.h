@@ -397,7 +397,9 @@ dattri_status dattri_layer_costs(const dattri_ctx* ctx, int32_t layer, int32_t T
  * the call is factored, the factored launches are paid and shared anyway, so a
  * layer decided MATERIALIZED joins the factored route if its predicted
  * factored time without launch costs is no more than its materialized time
- * (each materialized layer adds launches of its own).  A layer whose k
+ * (each materialized layer adds launches of its own).  Where no layer is
+ * factored by itself, those layers join together if what they gain is no less
+ * than the largest launch cost among them.  A layer whose k
  * exceeds the factored kernel's limits (k_in > 128 or k_out > 64) always
  * routes MATERIALIZED (its predicted factored time is infinite).
  * Errors: INVALID_ARG (bad layer), STATE (layer not captured). */

@@ -147,6 +147,27 @@ def test_plans_of_empty_captures(dtype, n, T):
         dt.dattri_destroy(c)
 
 
+def _stack_routes(dtype, n_layers, shape, T, n):
+    fake = 1 << 40
+    c = dt.dattri_create(dtype, 0)
+    for l in range(n_layers):
+        dt.dattri_register_layer(c, *shape)
+        dt.dattri_capture_layer(c, l, fake + (2 * l << 36), fake + (2 * l + 1 << 36), n, T)
+    routes = [dt.dattri_layer_route(c, l)[0] for l in range(n_layers)]
+    dt.dattri_destroy(c)
+    return routes
+
+
+@pytest.mark.parametrize("dtype,shape,T,n", [
+    (dt.DATTRI_BF16, (1024, 4096, 64, 64), 32, 1),  # 404 us materialized one after another, 27 factored
+    (dt.DATTRI_BF16, (1024, 4096, 64, 64), 32, 8),  # 640 and 33
+])
+def test_auto_routes_of_a_stack(dtype, shape, T, n):
+    # layers that each alone would be materialized share the factored launches
+    # in one call: the stack is factored
+    assert set(_stack_routes(dtype, 24, shape, T, n)) == {dt.DATTRI_ROUTE_FACTORED}
+
+
 def test_score_argument_errors():
     fake = 1 << 40
     f32 = dt.DATTRI_F32
