@@ -311,12 +311,15 @@ dattri_status dattri_materialize_gradient(dattri_ctx* ctx, int32_t layer, int32_
  * the cheaper exact route is taken per layer).  For one layer captured with n
  * examples, in microseconds:
  *   factored      = call_us + max(F_f / factored_tflops, B_f / factored_gbs)
- *                   + launches_f * launch_us
- * with the exact FLOP and byte counts of dattri_layer_costs times n, and
+ *                   + launches_f * launch_us + chain_f
+ * with the exact FLOP and byte counts of dattri_layer_costs times n,
  * launches_f the number of kernels the factored route runs for this layer
- * alone: 2 in the fused form (projection + reduction), 3 to 5 in the split
- * form (stage 1 per map width, slab sum, contraction, reduction), as the
- * launch plan decides.  The materialized route has two implementations:
+ * alone: 2 in the fused form (projection + reduction), 2 to 6 in the split
+ * form (stage 1 for aligned blocks and per map width for others, slab sum,
+ * contraction, reduction), as the launch plan decides, and chain_f (split
+ * form) the contraction's rounds one after another: 0.28 us times the 16 x 16
+ * tiles of the layer's block per 128 tokens of a workgroup (64 above 16
+ * tiles).  The materialized route has two implementations:
  *   - one pass (bf16 blocks with 16-byte aligned rows, k_in <= 128): each
  *     workgroup forms 128 rows of G over a token chunk, 128 columns at a
  *     time, and projects every tile from its accumulators, so G never goes
@@ -341,6 +344,9 @@ dattri_status dattri_materialize_gradient(dattri_ctx* ctx, int32_t layer, int32_
  *       materialized = call_us + max(F_g / gradient_tflops, B_g / gradient_gbs)
  *                      + max(F_p / gproject_tflops, B_p / gproject_gbs)
  *                      + 3 * chunks_m * launch_us
+ *     (float32 or unaligned rows: F_g at no more than gproject_tflops, and the
+ *     first maximum at least 0.038 us times T, the tokens a tile of G walks in
+ *     turn)
  *     with F_g, B_g the G = B^T A kernel (2T d_in d_out FLOP, factor blocks
  *     read and G written) and F_p, B_p the projection of G (the rest of the
  *     materialized FLOPs, G read).

@@ -50,25 +50,26 @@ bool factored_supported(const Layer& L) {
 }
 
 dattri_cost_model default_cost_model() {
-  // Fitted on MI355X (bf16 inputs; the calibration script's sweep of 28
-  // single-layer shapes: transformer, adapter-shaped and narrow layers,
-  // T = 16..4096, both forced routes timed with launch plans kept on the
-  // device), every rate held below its bound: AUTO picked the faster route on
-  // all 28 shapes, root-mean-square log error of the predictions 0.15; with
-  // the split form's row stream, which these rates do not price, on 21 of
-  // them (mean regret 5%, largest 32%: 8 -> 4096, T = 32, 64 examples).
-  // gproject_gbs and gproject_tflops serve only the staged-G route, which
-  // that sweep does not run.
+  // Fitted on MI355X with the split form's row stream: the calibration script's
+  // sweep of 28 single-layer bf16 shapes (transformer, adapter-shaped and narrow
+  // layers, T = 16..4096, launch plans kept on the device) and a grid of 564
+  // more (widths 64..4096, k = 8, 16, 64, T = 16..2048, 1 to 64 examples, calls
+  // among others), both forced routes timed, every rate held below its bound.
+  // AUTO picks the faster route on all 28 shapes (21 with the rates fitted
+  // before that stream, largest regret 32%); over the grid the route it takes is
+  // 2.6% slower than the faster one on average (9.2% before), at most 9 us.  The
+  // gproject rates serve the staged-G route: fitted to the same grid in float32
+  // (0.3% on average, 37% before).
   dattri_cost_model m;
-  m.factored_tflops = 175.9;
+  m.factored_tflops = 296.4;
   m.factored_gbs = 6450.0;
-  m.gradient_tflops = 837.2;
+  m.gradient_tflops = 870.6;
   m.gradient_gbs = 6450.0;
-  m.gproject_tflops = 157.3;
-  m.gproject_gbs = 5000.0;
-  m.launch_us = 10.74;
-  m.call_us = 0.0;
-  m.round_us = 0.674;
+  m.gproject_tflops = 80.0;
+  m.gproject_gbs = 2000.0;
+  m.launch_us = 3.253;
+  m.call_us = 2.625;
+  m.round_us = 0.567;
   return m;
 }
 
@@ -116,24 +117,31 @@ Counts layer_counts(const Layer& L, int64_t T, int elt) {
   return c;
 }
 
-// Kernel launches of a layer's factored route if it were projected alone: the
-// launch plan of a one-layer context decides fused or split form and stages.
-// `memo` (optional) keeps the counts of the sizes already planned in this
-// call: a model's blocks repeat a few layer shapes.
-using LaunchMemo = std::vector<std::pair<std::array<int32_t, 7>, int>>;
-int plan_launches(const dattri_ctx* ctx, const Layer& L);
-int factored_launches(const dattri_ctx* ctx, const Layer& L, LaunchMemo* memo) {
-  if (!memo) return plan_launches(ctx, L);
+// What a layer's factored route costs beside its work if it were projected
+// alone: kernel launches, and in the split form the contraction's chain of
+// rounds.  The launch plan of a one-layer context decides fused or split form
+// and stages.  `memo` (optional) keeps the sizes already planned in this call:
+// a model's blocks repeat a few layer shapes.
+struct Fixed { int launches; double chain_us; };
+using LaunchMemo = std::vector<std::pair<std::array<int32_t, 7>, Fixed>>;
+// Time of one contraction round per pair of output tiles: a wave's round is a
+// chain of loads and its products, which no other workgroup shortens (64 -> 64
+// layers of one example, k = 64, sixteen pairs: 5 us at 64 tokens, one round,
+// 10 at 256, two; k = 16, one pair: under 1).
+constexpr double kContractRoundUs = 0.28;
+Fixed plan_fixed(const dattri_ctx* ctx, const Layer& L);
+Fixed factored_fixed(const dattri_ctx* ctx, const Layer& L, LaunchMemo* memo) {
+  if (!memo) return plan_fixed(ctx, L);
   const int32_t al = (((uintptr_t)L.A % 16 == 0) ? 1 : 0) | (((uintptr_t)L.B % 16 == 0) ? 2 : 0) |
                      (L.A == L.B ? 4 : 0);  // all a one-layer plan reads of the captures besides their sizes
   const std::array<int32_t, 7> key = {L.d_in, L.d_out, L.k_in, L.k_out, L.n, L.T, al};
   for (const auto& m : *memo)
     if (m.first == key) return m.second;
-  const int count = plan_launches(ctx, L);
-  memo->push_back({key, count});
-  return count;
+  const Fixed f = plan_fixed(ctx, L);
+  memo->push_back({key, f});
+  return f;
 }
-int plan_launches(const dattri_ctx* ctx, const Layer& L) {
+Fixed plan_fixed(const dattri_ctx* ctx, const Layer& L) {
   dattri_ctx one;
   one.dtype = ctx->dtype;
   one.elt = ctx->elt;
@@ -150,10 +158,19 @@ int plan_launches(const dattri_ctx* ctx, const Layer& L) {
   Plan P;
   if (build_plan(&one, DATTRI_ROUTE_FACTORED, P, false) != DATTRI_OK) {
     reset_error();  // not a failure of the caller's request: count the fused form
-    return 2;
+    return {2, 0.0};
   }
-  return (int)(P.launches.size() + (P.n_fact_tasks ? 1 : 0) + P.slaunches.size() + (P.slabsum.empty() ? 0 : 1) +
-               (P.ctasks.empty() ? 0 : 1) + (P.stasks.empty() ? 0 : 1));
+  Fixed f;
+  f.launches = (int)(P.launches.size() + (P.n_fact_tasks ? 1 : 0) + P.slaunches.size() + (P.slabsum.empty() ? 0 : 1) +
+                     (P.ctasks.empty() ? 0 : 1) + (P.stasks.empty() ? 0 : 1));
+  f.chain_us = 0.0;
+  if (!P.ctasks.empty()) {
+    const ContractTask& C = P.ctasks[0];
+    const int pairs = tiles16(L.k_in) * tiles16(L.k_out);
+    const int per_round = pairs > 16 ? 64 : 128;  // tokens of a workgroup's round
+    f.chain_us = kContractRoundUs * pairs * ((std::min(C.tok_chunk, C.T) + per_round - 1) / per_round);
+  }
+  return f;
 }
 
 // Example chunks of the materialized route: G of a chunk fits the staging budget.
@@ -164,9 +181,12 @@ int64_t materialized_chunk(const Layer& L, int64_t n) {
 
 // The one-pass materialized kernel serves bf16 layers with 16-byte aligned
 // rows and k_in <= 128; others stage G in the workspace.
+bool rows_aligned(const Layer& L, int elt) {
+  return (uintptr_t)L.A % 16 == 0 && (uintptr_t)L.B % 16 == 0 && ((int64_t)L.d_in * elt) % 16 == 0 &&
+         ((int64_t)L.d_out * elt) % 16 == 0;
+}
 bool fused_materialized(const Layer& L, int elt) {
-  return elt == 2 && (uintptr_t)L.A % 16 == 0 && (uintptr_t)L.B % 16 == 0 && (L.d_in * 2) % 16 == 0 &&
-         (L.d_out * 2) % 16 == 0 && tiles16(L.k_in) <= kGFusedMaxTilesIn;
+  return elt == 2 && rows_aligned(L, elt) && tiles16(L.k_in) <= kGFusedMaxTilesIn;
 }
 
 // Launch shape of the one-pass kernel and its predicted time.  A workgroup
@@ -213,8 +233,14 @@ FusedShape fused_shape(const Layer& L, int64_t n, const dattri_cost_model& m) {
   return best;
 }
 
+// Time per token of a 64 x 64 tile of G, which one workgroup forms (float32 64 x
+// 64 layers, one example: 46 us at 1024 tokens, 85 at 2048; bf16 100 x 60, whose
+// rows are not 16-byte multiples: 44 and 80).
+constexpr double kGradTokenUs = 0.038;
+
 // Predicted times (us) of both routes for the layer's capture (n, T).
-// f_launch_us (optional) receives the launch part of the factored time.
+// f_launch_us (optional) receives the part of the factored time that many
+// layers in one call share: launches and the contraction's chain.
 void predict(const dattri_ctx* ctx, const Layer& L, double* f_us, double* m_us, double* f_launch_us = nullptr,
              LaunchMemo* memo = nullptr) {
   const dattri_cost_model& m = ctx->cost;
@@ -224,7 +250,11 @@ void predict(const dattri_ctx* ctx, const Layer& L, double* f_us, double* m_us, 
     return std::max(flops / (tflops * 1e6), bytes / (gbs * 1e3));  // microseconds
   };
   *f_us = m.call_us + t((double)c.f_flops * n, m.factored_tflops, (double)c.f_bytes * n, m.factored_gbs);
-  const double fl = n > 0 ? factored_launches(ctx, L, memo) * m.launch_us : 0.0;
+  double fl = 0.0;
+  if (n > 0) {
+    const Fixed f = factored_fixed(ctx, L, memo);
+    fl = f.launches * m.launch_us + f.chain_us;
+  }
   *f_us += fl;
   if (f_launch_us) *f_launch_us = fl;
   if (fused_materialized(L, ctx->elt)) {
@@ -240,7 +270,11 @@ void predict(const dattri_ctx* ctx, const Layer& L, double* f_us, double* m_us, 
     return;
   }
   const int64_t chunks = n > 0 ? (n + materialized_chunk(L, n) - 1) / materialized_chunk(L, n) : 0;
-  *m_us = m.call_us + t((double)c.g_flops * n, m.gradient_tflops, (double)c.g_bytes * n, m.gradient_gbs) +
+  // G of float32 or unaligned blocks: 64 x 64 tiles at the float32 kernels' rate, each walking its tokens in turn
+  const bool small = ctx->elt == 4 || !rows_aligned(L, ctx->elt);
+  const double g_us = t((double)c.g_flops * n, small ? std::min(m.gradient_tflops, m.gproject_tflops) : m.gradient_tflops,
+                        (double)c.g_bytes * n, m.gradient_gbs);
+  *m_us = m.call_us + std::max(g_us, small && n > 0 ? kGradTokenUs * L.T : 0.0) +
           t((double)c.p_flops * n, m.gproject_tflops, (double)c.p_bytes * n, m.gproject_gbs) +
           3.0 * chunks * m.launch_us;
 }

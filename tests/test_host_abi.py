@@ -168,6 +168,26 @@ def test_auto_routes_of_a_stack(dtype, shape, T, n):
     assert set(_stack_routes(dtype, 24, shape, T, n)) == {dt.DATTRI_ROUTE_FACTORED}
 
 
+@pytest.mark.parametrize("dtype,shape,T,n,factored_us,materialized_us", [
+    # the contraction's chain of rounds: few workgroups, k = 64
+    (dt.DATTRI_BF16, (768, 64, 64, 64), 1024, 1, 21, 14),
+    (dt.DATTRI_BF16, (64, 64, 64, 64), 256, 1, 18, 10),
+    (dt.DATTRI_BF16, (128, 128, 64, 64), 2048, 8, 24, 22),
+    # the split form's stream at few rows
+    (dt.DATTRI_BF16, (8, 4096, 8, 64), 32, 64, 22, 29),
+    (dt.DATTRI_BF16, (768, 512, 64, 64), 1024, 64, 69, 132),
+    # G of float32 and of unaligned blocks: a tile walks the tokens
+    (dt.DATTRI_F32, (1024, 4096, 16, 16), 1024, 1, 21, 150),
+    (dt.DATTRI_F32, (64, 64, 64, 64), 2048, 1, 19, 91),
+    (dt.DATTRI_BF16, (100, 60, 16, 16), 1024, 1, 17, 44),
+    (dt.DATTRI_BF16, (30, 2000, 8, 8), 64, 1, 17, 13),
+])
+def test_default_rates_pick_the_faster_route(dtype, shape, T, n, factored_us, materialized_us):
+    # measured times of both forced routes on MI355X, calls among others
+    want = dt.DATTRI_ROUTE_FACTORED if factored_us < materialized_us else dt.DATTRI_ROUTE_MATERIALIZED
+    assert _stack_routes(dtype, 1, shape, T, n) == [want]
+
+
 def test_score_argument_errors():
     fake = 1 << 40
     f32 = dt.DATTRI_F32
