@@ -505,8 +505,9 @@ __global__ __launch_bounds__(256, 2) void ghost_kernel(const GhostEntry* __restr
 // of 16 waves per output.  The blocks of every such entry are cut into runs of
 // 256 (four loads in flight per lane), and the runs, entry after entry, are
 // dealt to the waves in turn, so that one entry of a long sequence fills them
-// as well as 48 short ones; each wave finds the entries 64 at a time.  Every
-// lane adds its blocks in order, then a fixed tree over lanes and waves.
+// as well as 48 short ones.  Each wave looks the entries up 64 at a time and
+// finds its runs among them by their running count.  Every lane adds its blocks
+// in order, then a fixed tree over lanes and waves.
 constexpr int kGhRedWaves = 16, kGhRedRun = 4 * 64;
 
 __global__ __launch_bounds__(64 * kGhRedWaves) void ghost_reduce_kernel(const GhostEntry* __restrict__ entries,
@@ -531,23 +532,31 @@ __global__ __launch_bounds__(64 * kGhRedWaves) void ghost_reduce_kernel(const Gh
         first = E.part_off + (int64_t)i * rb * nbc + j * cb;
       }
     }
-    for (uint64_t m = __ballot(rb * cb > 0); m; m &= m - 1) {
-      const int src = __builtin_ctzll(m);
-      const int c = __builtin_amdgcn_readlane(cb, src), n_c = __builtin_amdgcn_readlane(nbc, src);
-      const int nblk = __builtin_amdgcn_readlane(rb, src) * c, runs = (nblk + kGhRedRun - 1) / kGhRedRun;
-      const float* p = parts + __shfl(first, src, 64);
-      for (int r = (wave - run0) & (kGhRedWaves - 1); r < runs; r += kGhRedWaves) {
-        float v[4];
+    const int nblk = rb * cb, runs = (nblk + kGhRedRun - 1) / kGhRedRun;
+    int end = runs;  // runs of the lanes up to this one
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int b = r * kGhRedRun + 64 * u + lane;
-          v[u] = b < nblk ? p[(int64_t)(b / c) * n_c + b % c] : 0.f;
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) s += v[u];
-      }
-      run0 += runs;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int below = __shfl_up(end, o, 64);
+      if (lane >= o) end += below;
     }
+    const int begin = end - runs, total = __builtin_amdgcn_readlane(end, 63);
+    const int lo = (int)(uint32_t)first, hi = (int)(first >> 32);
+    for (int u = (wave - run0) & (kGhRedWaves - 1); u < total; u += kGhRedWaves) {
+      const int src = 63 - __builtin_clzll(__ballot(begin <= u));  // the last such lane holds run u
+      const int c = __builtin_amdgcn_readlane(cb, src), n_c = __builtin_amdgcn_readlane(nbc, src);
+      const int n_b = __builtin_amdgcn_readlane(nblk, src), b0 = (u - __builtin_amdgcn_readlane(begin, src)) * kGhRedRun;
+      const float* p = parts + (((int64_t)__builtin_amdgcn_readlane(hi, src) << 32) |
+                                (uint32_t)__builtin_amdgcn_readlane(lo, src));
+      float v[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int b = b0 + 64 * q + lane;
+        v[q] = b < n_b ? p[(int64_t)(b / c) * n_c + b % c] : 0.f;
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) s += v[q];
+    }
+    run0 += total;
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
