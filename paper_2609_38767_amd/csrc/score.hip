@@ -410,16 +410,18 @@ __global__ __launch_bounds__(64 * NW) void row_inv_norms_wide_kernel(const uint8
 template <int ELT>
 static hipError_t launch_norms(const uint8_t* X, int64_t ld, int64_t rows, int64_t F, const float* d, float* inv,
                                hipStream_t s) {
-  // Waves per row.  Short rows (up to 8 KB): one, as a workgroup each costs more
-  // than it reads (2048 rows of 256 floats: 2.7 us, 16 waves 5.0).  Up to 128 KB:
-  // four, one load each in flight (512 rows of 12288 floats: 3.1 us, one wave
-  // 14.1; 2048 rows: 15.6 and 18.9).  Longer: 16 (one row of 229376 floats: 7.9
-  // us, 4 waves 14.1, one 98.9).  More than 2048 rows fill the chip with a wave
-  // each (4096 rows of 12288: 28.8 us either way).
+  // Waves per row.  Short rows (up to 4 KB): one, as a workgroup each costs more
+  // than it reads (2048 rows of 256 floats: 2.7 us, 16 waves 5.0).  Longer: four,
+  // one load each in flight (100 rows of 4096 bf16: 2.4 us, one wave 4.0; 2048
+  // rows of 12288 floats: 15.6 and 18.9), or 16 where that many have loads to
+  // make and rows are too few to fill the chip with fewer (256 rows of 12288
+  // floats, not in a cache: 5.2 us, 4 waves 8.1) or rows are very long (one of
+  // 229376 floats: 7.9 us, 4 waves 14.1, one 98.9).  More than 2048 rows fill the
+  // chip with a wave each (4096 rows of 12288: 28.8 us either way).
   const int64_t bytes = F * ELT;
-  if (rows <= 2048 && bytes > 131072) {
+  if (rows <= 2048 && (bytes > 131072 || (rows <= 512 && bytes > 16384))) {
     hipLaunchKernelGGL((row_inv_norms_wide_kernel<ELT, 16>), dim3((unsigned)rows), dim3(1024), 0, s, X, ld, F, d, inv);
-  } else if (rows <= 2048 && bytes > 8192) {
+  } else if (rows <= 2048 && bytes > 4096) {
     hipLaunchKernelGGL((row_inv_norms_wide_kernel<ELT, 4>), dim3((unsigned)rows), dim3(256), 0, s, X, ld, F, d, inv);
   } else {
     const int64_t b = (rows + 3) / 4;
