@@ -560,6 +560,12 @@ dattri_status dattri_feature_ld(int64_t F, dattri_dtype dtype, int64_t* ld);
  *              are ordered by lower training index (-0.0 equals +0.0; NaN
  *              scores are not supported).
  *   workspace: device, >= dattri_score_workspace_bytes(...), 256-byte aligned.
+ *              With less, a call whose sizes have a slower form that fits takes
+ *              that one (bf16, at most 48 queries against 512 MB of training rows
+ *              or more: 128 x 128 tiles in place of the row stream; cosines:
+ *              norms by a pass of their own); scores then differ in the last
+ *              bits, by the order of the sums.  WORKSPACE is reported when none
+ *              fits.
  * Accumulation is float32.  Errors: INVALID_ARG (including ld < F), DTYPE,
  * WORKSPACE, UNSUPPORTED (topk > 1024, misaligned rows, 256 rows of the
  * stride reaching 4 GiB), HIP. */
@@ -595,8 +601,9 @@ dattri_status dattri_score_noalloc(const void* phi_q, int64_t n_q, int64_t ld_q,
  *   S[q][j] = <q', x_j> / (|q'| |x_j|),  q' = phi_q[q] * d (d = 1 when NULL),
  * and 0 when either norm is 0; top-k ranks these cosines.  Norms are float32
  * sums of squares of the rows as given (the query scaled by d in float32).
- *   workspace: >= dattri_cosine_workspace_bytes(...) (dattri_score's plus
- *   n_q + n_train floats), 256-byte aligned.
+ *   workspace: >= dattri_cosine_workspace_bytes(...) (dattri_score's plus n_q
+ *   floats and n_train floats for every part that the features are split into),
+ *   256-byte aligned; with less as for dattri_score.
  * Errors: as dattri_score. */
 dattri_status dattri_cosine_workspace_bytes(int64_t n_q, int64_t n_train, int64_t F,
                                             dattri_dtype dtype, int32_t has_precond,

@@ -102,9 +102,10 @@ hipError_t launch_reduce(const ReduceTask* tasks, int n_tasks, int n_examples, i
 // n*T rows) slab by slab over the feature dimension d, writing float32
 // partial projections [slab][row][tile cols]; stage 2 sums the slabs and
 // contracts each example's tokens into its layer block of phi.
-// Rows per stage-1 workgroup: 4 waves of 4 row tiles on the direct-load stream
-// (aligned rows); the same on the register path (unaligned rows) up to 4 map
-// tiles, 2 row tiles at 8, where 4 would not fit the register file.
+// Rows per stage-1 workgroup: 4 waves of 4 row tiles on the bf16 direct-load
+// stream (aligned rows), of 2 on the float32 one; on the register path
+// (unaligned rows) 4 up to 4 map tiles, 2 at 8, where 4 would not fit the
+// register file.
 constexpr int split_stream_rows(int elt) { return elt == 2 ? 256 : 128; }
 constexpr int split_rt_of(int nt_inst) { return nt_inst <= 4 ? 4 : 2; }
 constexpr int split_rows_of(int nt_inst) { return 4 * split_rt_of(nt_inst) * 16; }
@@ -117,7 +118,7 @@ struct SplitOp {                    // one factor block: a group's A or a member
   int32_t out_ld;                   // floats per projected row
   int32_t once, pad0;               // no other op of the call reads X
   int32_t rows, ld;                 // n*T, row stride
-  int32_t width, pad1;              // columns of a row
+  int32_t width, pad1;              // columns of a row (scored rows may lie further apart: ld > width)
   int32_t slab_cols, n_slabs;
   int32_t nt;                       // 16-column tiles of the projected rows
   int32_t aligned;                  // 16-byte vector loads allowed

@@ -287,16 +287,6 @@ hipError_t launch_rowcov(const RowOp* ops, int n_ops, int max_items, float* part
 __device__ inline float load_elem(const void* p, int bf16, int64_t i);
 
 // ---------------------------------------------------- token-level scores
-// Workgroup (TT token positions, example, QS query rows): every layer is
-// staged as zero-padded tiles in LDS (the QS query blocks of 64 x 64, the
-// chunk's TT x 64 a~ and g~ rows), loaded into registers one layer ahead so
-// that the loads of layer l + 1 are in flight while layer l is computed.  The
-// 256 / TT threads of a token split into QS query slots of PARTS parts; a part
-// holds g~_t in registers and sums a~_t[c] (R g~_t)[c] over its share of c,
-// reading rows of R as broadcast float4.  Each part accumulates over all
-// layers in layer order and the parts are added in part order at the end
-// (deterministic).  One query row takes TT = 32 (twice the workgroups, so two
-// share a CU and hide each other's per-layer load latency).
 // Token contributions a~_t^T R g~_t on float32 MFMA (32x32x2; layouts as
 // for ekfac_kernel).  A workgroup holds kTokTokens token positions of one
 // example, 32 per wave, and QS query rows; per layer, for each query,
@@ -482,9 +472,10 @@ __device__ inline double rsqrt_near(double y) {
 // its cosine to float64 rounding with s = t c, so the rotations are orthogonal
 // to rounding.  Bound by the LDS port: 128 KiB per round of k = 64 (about 1000
 // of about 2600 cycles, the rest being the rotations' latency and two
-// barriers).  56 matrices of 64 x 64: 0.58 ms (1.17 ms with four waves,
+// barriers).  56 matrices of 64 x 64: 0.58 to 0.65 ms (1.17 ms with four waves,
 // rows and columns updated in separate phases, and division and square root
-// to full precision in each rotation).
+// to full precision in each rotation); 392 matrices, more than one per CU and
+// so two or three after another: 1.28 ms (1.53).
 constexpr int kEigThreads = 1024;
 
 __global__ __launch_bounds__(kEigThreads) void eigen_kernel(const EigTask* __restrict__ tasks,

@@ -334,7 +334,13 @@ const std::vector<dattri_route>& call_routes(const dattri_ctx* ctx, dattri_route
 
 // ---------------------------------------------------------------- planning
 // The split form serves every factored group when the fused kernel would have
-// fewer than kSplitMinFusedItems work items.
+// fewer than kSplitMinFusedItems work items.  Around the line (fused against
+// split): Llama-shaped blocks, 8 x 2048 bf16 tokens, k = 32: 768 items 2.49 and
+// 2.42 ms, 1024 items 2.84 and 3.11; Qwen-shaped, 32 x 512, k = 64: 768 items 2.92
+// and 2.89, 1024 items 3.65 and 3.81.  Narrow maps would take the fused kernel
+// earlier (Pythia-shaped, 32 x 256 bf16, k = 16: 256 items 91 and 104 us, 768
+// items 272 and 295) and float32 with wide maps later (24 Pythia-shaped blocks,
+// 8 x 512, k = 64, 768 items: 3.7 and 1.6 ms).
 constexpr int64_t kSplitMinFusedItems = 1024;
 constexpr int kCus = 256;                     // MI355X compute units
 constexpr int64_t kGProjTargetBlocks = 1024;  // G-projection workgroups aimed for

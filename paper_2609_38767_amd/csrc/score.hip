@@ -163,8 +163,8 @@ __global__ __launch_bounds__(256) void score_gemm_kernel(const uint8_t* __restri
 // splits them once and writes 16 bytes to each of the three planes of its side
 // in LDS (64 bytes per row and plane; the 16-byte chunk c of row r at c XOR
 // (r / 2) mod 4); the waves read operands from there: 24 reads for 96 MFMA per
-// stage.  A value is split once per tile and used by 128 products.  Three
-// workgroups share a CU, so one's splitting runs beside another's MFMA.  Blocks of 16
+// stage.  A value is split once per tile and used by 128 products.  Two
+// workgroups share a CU (174 registers), so one's splitting runs beside the other's MFMA.  Blocks of 16
 // query rows past n_q are not multiplied.  A wave's block with a result that
 // the split may have cost bits (split_unsafe) is computed again in float32 MFMA from memory.  Bound by the issue of MFMA and
 // splitting: the whole cosine call for 256 x 8192 x 12288 takes 0.30 ms (0.52 ms

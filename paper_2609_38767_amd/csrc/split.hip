@@ -8,8 +8,10 @@
 //
 //   stage 1  for every factor block X (a group's A, each member's B) viewed as
 //            n*T token rows: out[s][row][:] = X[row, slab s] P[slab s, :],
-//            float32, one workgroup per (block, 256-row block, slab).  Rows
-//            past an example's length are neither read nor written.
+//            float32, one workgroup per (block, 256-row block, slab; 128 rows
+//            in float32 and at 8 unaligned tiles).  The aligned stream neither
+//            reads nor writes rows past an example's length; the element loads
+//            of unaligned blocks take them along, and stage 2 ignores them.
 //   stage 2  per (layer, example, token chunk): Psi[c][r] = sum_t a~_t[c] g~_t[r]
 //            with a~_t = sum_s outA[s][t] and g~_t = sum_s outB[s][t], over
 //            the example's first T_i tokens (Eq. (4) allows T_i < T), written
