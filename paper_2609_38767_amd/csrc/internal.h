@@ -437,7 +437,8 @@ hipError_t launch_token_scores(const TokTask* tasks, int n_tasks, const void* ph
 
 // Symmetric eigendecomposition of sum / count (k x k, k <= kCurvMaxK).
 struct EigTask { int64_t sum_off, count_off, q_off, lam_off; int32_t k, pad0; };
-hipError_t launch_eigen(const EigTask* tasks, int n_tasks, uint8_t* state, hipStream_t s);
+// max_k: the largest k among the tasks.
+hipError_t launch_eigen(const EigTask* tasks, int n_tasks, int max_k, uint8_t* state, hipStream_t s);
 
 // Rotated-block kernels: per layer, the block of phi at column col and the
 // layer's fields in the state.

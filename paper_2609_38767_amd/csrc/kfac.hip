@@ -463,7 +463,8 @@ __device__ inline double rsqrt_near(double y) {
   return r * fma(-0.5 * y * r, r, 1.5);
 }
 
-// Workgroup of 16 waves per matrix.  A round is two phases: 32 threads form the
+// Workgroup of 16 waves per matrix (fewer where every matrix of the call is
+// small: 32 threads per pair).  A round is two phases: 32 threads form the
 // rotations; then thread (i, j) of the 32 x 32 grid applies both sides to the
 // 2 x 2 block of pairs i and j (A <- J^T A J in one pass) and the rotation of
 // pair j to rows i and i + 32 of V.  The tangent of a rotation comes from
@@ -475,8 +476,9 @@ __device__ inline double rsqrt_near(double y) {
 // barriers).  56 matrices of 64 x 64: 0.58 to 0.65 ms (1.17 ms with four waves,
 // rows and columns updated in separate phases, and division and square root
 // to full precision in each rotation); 392 matrices, more than one per CU and
-// so two or three after another: 1.28 ms (1.53).
-constexpr int kEigThreads = 1024;
+// so two or three after another: 1.28 ms (1.53).  2 matrices of 8 x 8: 37
+// us with two waves, 44 with 16.
+constexpr int kEigThreads = 1024;  // at most: (kCurvMaxK / 2) pairs of pairs
 
 __global__ __launch_bounds__(kEigThreads) void eigen_kernel(const EigTask* __restrict__ tasks,
                                                             uint8_t* __restrict__ state) {
@@ -486,12 +488,12 @@ __global__ __launch_bounds__(kEigThreads) void eigen_kernel(const EigTask* __res
   __shared__ double red[2][kEigThreads / 64];
   __shared__ int rank[kCurvMaxK];
   const EigTask t = tasks[blockIdx.x];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, threads = blockDim.x;
   const int k = t.k, n = k + (k & 1), m = n / 2;
   const float* sum = (const float*)(state + t.sum_off);
   const int64_t cnt = *(const int64_t*)(state + t.count_off);
   const double scale = cnt > 0 ? 1.0 / (double)cnt : 0.0;
-  for (int e = tid; e < n * n; e += kEigThreads) {
+  for (int e = tid; e < n * n; e += threads) {
     const int i = e / n, j = e - (e / n) * n;
     double v = 0.0;
     if (i < k && j < k) v = 0.5 * ((double)sum[i * k + j] + (double)sum[j * k + i]) * scale;
@@ -504,7 +506,7 @@ __global__ __launch_bounds__(kEigThreads) void eigen_kernel(const EigTask* __res
   const bool mine = bi < m && bj < m;
   for (int sweep = 0; sweep < kEigSweeps; ++sweep) {
     double off = 0.0, tot = 0.0;
-    for (int e = tid; e < n * n; e += kEigThreads) {
+    for (int e = tid; e < n * n; e += threads) {
       const int i = e / n, j = e - (e / n) * n;
       const double v = Am[i * kEigLd + j];
       tot += v * v;
@@ -518,8 +520,7 @@ __global__ __launch_bounds__(kEigThreads) void eigen_kernel(const EigTask* __res
     }
     __syncthreads();
     off = tot = 0.0;
-#pragma unroll
-    for (int w = 0; w < kEigThreads / 64; ++w) {
+    for (int w = 0; w < threads / 64; ++w) {
       off += red[0][w];
       tot += red[1][w];
     }
@@ -589,16 +590,18 @@ __global__ __launch_bounds__(kEigThreads) void eigen_kernel(const EigTask* __res
   __syncthreads();
   float* Q = (float*)(state + t.q_off);
   float* lam = (float*)(state + t.lam_off);
-  for (int e = tid; e < k * k; e += kEigThreads) {
+  for (int e = tid; e < k * k; e += threads) {
     const int row = e / k, col = e - (e / k) * k;
     Q[row * k + rank[col]] = (float)Vm[row * kEigLd + col];
   }
   if (tid < k) lam[rank[tid]] = (float)Am[tid * kEigLd + tid];
 }
 
-hipError_t launch_eigen(const EigTask* tasks, int n_tasks, uint8_t* state, hipStream_t s) {
+hipError_t launch_eigen(const EigTask* tasks, int n_tasks, int max_k, uint8_t* state, hipStream_t s) {
   if (n_tasks <= 0) return hipSuccess;
-  hipLaunchKernelGGL(eigen_kernel, dim3(n_tasks), dim3(kEigThreads), 0, s, tasks, state);
+  if (max_k < 1 || max_k > kCurvMaxK) return hipErrorInvalidValue;
+  const int pairs = (max_k + 1) / 2;
+  hipLaunchKernelGGL(eigen_kernel, dim3(n_tasks), dim3((pairs + 1) / 2 * 64), 0, s, tasks, state);
   return hipGetLastError();
 }
 

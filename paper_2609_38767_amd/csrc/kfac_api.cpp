@@ -491,6 +491,7 @@ dattri_status dattri_curvature_eigen(const dattri_ctx* ctx, void* state, void* s
   CurvLayout C;
   curv_layout(ctx, C);
   std::vector<EigTask> E;
+  int32_t max_k = 0;
   for (size_t l = 0; l < ctx->layers.size(); ++l) {
     const dattri_curvature_layout& f = C.L[l];
     EigTask a, g;
@@ -502,12 +503,13 @@ dattri_status dattri_curvature_eigen(const dattri_ctx* ctx, void* state, void* s
     g.k = ctx->layers[l].k_out;
     E.push_back(a);
     E.push_back(g);
+    max_k = std::max({max_k, a.k, g.k});
   }
   hipStream_t s = (hipStream_t)stream;
   uint8_t* base = (uint8_t*)state;
   HIP_TRY(copy_tables(ctx, base + C.off_eig, {E.data()}, {0}, {E.size() * sizeof(EigTask)},
                       E.size() * sizeof(EigTask), s));
-  HIP_TRY(launch_eigen((const EigTask*)(base + C.off_eig), (int)E.size(), base, s));
+  HIP_TRY(launch_eigen((const EigTask*)(base + C.off_eig), (int)E.size(), max_k, base, s));
   return DATTRI_OK;
 }
 

@@ -516,3 +516,25 @@ def test_curvature_full_size_sampled():
         e = rel_fro(host64(pq[0, off:off + w]).reshape(L["k_in"], L["k_out"]), ref)
         print(f"  layer {li}: K-FAC preconditioned block rel err {e:.2e}")
         assert e <= 1e-3, (li, e)
+
+
+@pytest.mark.parametrize("ks", [[(1, 1)], [(2, 3)], [(4, 8), (5, 7)], [(16, 17)], [(31, 32)], [(33, 2)]])
+def test_eigen_small_calls(ks):
+    # the workgroup has 32 threads per pair of the call's largest matrix
+    rng = np.random.default_rng(9)
+    layers, s = _eig_session(ks)
+    c = Curvature(s)
+    mats = {}
+    for li, kk in enumerate(ks):
+        for side, k in zip("ag", kk):
+            X = rng.standard_normal((k, 2 * k + 3)).astype(np.float32)
+            S = X @ X.T
+            c.field(li, "sum_" + side).copy_(torch.from_numpy(S))
+            mats[li, side] = 0.5 * (S.astype(np.float64) + S.T.astype(np.float64)) / 4
+        c.field(li, "counts").copy_(torch.tensor([4, 4, 0]))
+    c.eigen()
+    for (li, side), M in mats.items():
+        lam, Q = host64(c.field(li, "lam_" + side)), host64(c.field(li, "q_" + side))
+        lam_o, _ = ok.eigenbasis(M)
+        assert np.max(np.abs(lam - lam_o)) <= 1e-5 * np.max(lam_o) and np.all(np.diff(lam) >= 0)
+        assert rel_fro(Q.T @ Q, np.eye(len(M))) <= 1e-5 and rel_fro((Q * lam) @ Q.T, M) <= 1e-5
