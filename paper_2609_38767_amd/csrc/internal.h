@@ -417,6 +417,7 @@ struct RowOp {
   const int32_t* lengths;
   int64_t ld, partial_base;
   int32_t col0, k, T, n, ex_per_item, n_items;
+  int32_t tok_chunk, n_chunks;      // n_chunks > 1: one example per item, its tokens cut into chunks
 };
 hipError_t launch_rowcov(const RowOp* ops, int n_ops, int max_items, float* parts, hipStream_t s);
 

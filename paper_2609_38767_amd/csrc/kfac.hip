@@ -221,9 +221,11 @@ __global__ __launch_bounds__(256) void rowcov_kernel(const RowOp* __restrict__ o
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-  const int e0 = blockIdx.x * o.ex_per_item, e1 = min(o.n, e0 + o.ex_per_item);
+  const int e0 = (int)blockIdx.x / o.n_chunks * o.ex_per_item, e1 = min(o.n, e0 + o.ex_per_item);
+  const int tok0 = (int)blockIdx.x % o.n_chunks * o.tok_chunk;  // this item's tokens of each example
   auto rows_of = [&](int ex) {
-    return o.lengths ? min(max(o.lengths[ex], 0), o.T) : o.T;
+    const int len = o.lengths ? min(max(o.lengths[ex], 0), o.T) : o.T;
+    return tok0 + min(len - tok0, o.tok_chunk);  // no rows where it is at most tok0
   };
   // tiles of kRowTile rows, example by example; the next tile is loaded into
   // registers (zero past the example's rows and past column k) while the
@@ -242,10 +244,10 @@ __global__ __launch_bounds__(256) void rowcov_kernel(const RowOp* __restrict__ o
     t0 += kRowTile;
     while (ex < e1 && t0 >= rows_of(ex)) {
       ++ex;
-      t0 = 0;
+      t0 = tok0;
     }
   };
-  int ex = e0, t0 = -kRowTile;
+  int ex = e0, t0 = tok0 - kRowTile;
   next(ex, t0);
   if (ex < e1) load(ex, t0);
   while (ex < e1) {  // uniform trip count

@@ -248,6 +248,7 @@ dattri_status plan_fsum(const dattri_ctx* ctx, const CurvLayout& C, FsumPlan& P,
 // materialized route (which never form projected rows) take the separate
 // factor-sum pass.  Workspace: [projection plan][row ops, row tasks, factor-sum
 // descriptors][row partials][factor-sum partials].
+constexpr int kRowTokens = 64;               // token rows a row-covariance workgroup takes at a time
 constexpr int64_t kRowTargetItems = 2048;  // row-covariance workgroups aimed for
 
 struct FitPlan {
@@ -273,6 +274,11 @@ dattri_status plan_fit(const dattri_ctx* ctx, const CurvLayout& C, dattri_route 
   const int32_t n = ctx->layers[0].n;
   const int64_t n_ops = (int64_t)F.proj->row_srcs.size();
   const int epi = (int)std::max<int64_t>(1, cdiv((int64_t)n * n_ops, kRowTargetItems));
+  // few (example, operand) pairs: long examples in chunks of at least 128 tokens,
+  // as a workgroup's walk over its rows is a chain of 60 ns per token (one
+  // example of 2048 tokens, 768 -> 768, k = 64, projection with the factor sums:
+  // 161 -> 44 us)
+  const int64_t row_chunks = n > 0 ? std::max<int64_t>(1, kRowTargetItems / 2 / std::max<int64_t>(1, (int64_t)n * n_ops)) : 1;
   size_t parts = 0;
   for (const RowSrc& R : F.proj->row_srcs) {
     const Layer& L = ctx->layers[R.layer];
@@ -286,7 +292,10 @@ dattri_status plan_fit(const dattri_ctx* ctx, const CurvLayout& C, dattri_route 
     o.T = L.T;
     o.n = n;
     o.ex_per_item = epi;
-    o.n_items = n > 0 ? (int)cdiv(n, epi) : 0;
+    const int64_t chunks = std::min<int64_t>(row_chunks, std::max<int64_t>(1, L.T / 128));
+    o.tok_chunk = (int32_t)std::min<int64_t>(cdiv(cdiv(std::max(L.T, 1), chunks), kRowTokens) * kRowTokens, INT32_MAX);
+    o.n_chunks = std::max(1, (int)cdiv(L.T, o.tok_chunk));
+    o.n_items = n > 0 ? (int)cdiv(n, epi) * o.n_chunks : 0;
     o.partial_base = (int64_t)parts;
     parts += (size_t)o.n_items * k * k;
     StatTask t = side_task(ctx, C, R.layer, R.side, n);

@@ -538,3 +538,25 @@ def test_eigen_small_calls(ks):
         lam_o, _ = ok.eigenbasis(M)
         assert np.max(np.abs(lam - lam_o)) <= 1e-5 * np.max(lam_o) and np.all(np.diff(lam) >= 0)
         assert rel_fro(Q.T @ Q, np.eye(len(M))) <= 1e-5 and rel_fro((Q * lam) @ Q.T, M) <= 1e-5
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n,T,lens", [(1, 300, [300]), (1, 257, [130]), (3, 520, [520, 191, 0]), (2, 2050, [2050, 64])])
+def test_fit_token_chunks(dtype, n, T, lens):
+    # few examples: the kept rows' outer products are taken over chunks of an
+    # example's tokens (last chunk short, chunks past the length, empty example)
+    layers = [dict(name="t0", d_in=64, d_out=40, k_in=64, k_out=20, a_group="t0"),
+              dict(name="t1", d_in=48, d_out=72, k_in=8, k_out=64, a_group="t1")]
+    inputs = _inputs(layers, n, T, dtype, seed=67)
+    lengths = torch.tensor(lens, dtype=torch.int32, device=DEV)
+    s = _session(layers, inputs, dtype, 11, lengths)
+    c = Curvature(s)
+    c.project_and_fit(n)
+    c.project_and_fit(n)  # added to the state
+    maps = oracle_maps(11, layers, dtype)
+    for li in range(len(layers)):
+        A, B = host64(inputs[li][0]), host64(inputs[li][1])
+        SA, SG, nt, ne = ok.factor_sums(A, B, maps[li][0], maps[li][1], lens)
+        ea, eg = rel_fro(host64(c.field(li, "sum_a")), 2 * SA), rel_fro(host64(c.field(li, "sum_g")), 2 * SG)
+        assert ea <= 1e-5 and eg <= 1e-5, (li, ea, eg)
+        assert c.field(li, "counts").tolist() == [2 * nt, 2 * ne, 0]
