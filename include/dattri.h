@@ -680,7 +680,9 @@ dattri_status dattri_curvature_accumulate_factors(dattri_ctx* ctx, void* state, 
  * factored kernels also keep each layer's projected token rows a~_t, g~_t
  * (float32, in the workspace) and the sums are formed from those rows; layers
  * on the materialized route, which never form projected rows, take the
- * separate factor-sum pass.
+ * separate factor-sum pass, so AUTO factors every layer that can be (phi then
+ * differs in the last bits from dattri_project_per_example's where that
+ * materializes one).
  *   workspace: >= dattri_project_fit_workspace_bytes(ctx, route), 256-byte aligned.
  * Errors: those of dattri_project_per_example and of
  * dattri_curvature_accumulate_factors. */

@@ -560,3 +560,17 @@ def test_fit_token_chunks(dtype, n, T, lens):
         ea, eg = rel_fro(host64(c.field(li, "sum_a")), 2 * SA), rel_fro(host64(c.field(li, "sum_g")), 2 * SG)
         assert ea <= 1e-5 and eg <= 1e-5, (li, ea, eg)
         assert c.field(li, "counts").tolist() == [2 * nt, 2 * ne, 0]
+
+
+@pytest.mark.parametrize("d,k,n,T", [((768, 64), 64, 1, 1024), ((768, 768), 64, 2, 2048), ((2048, 2048), 16, 1, 64)])
+def test_fit_under_auto_keeps_rows(d, k, n, T):
+    # whatever the layer's route in a plain projection, a fit under AUTO factors
+    # it: its rows are then read once
+    layers = [dict(name="k0", d_in=d[0], d_out=d[1], k_in=k, k_out=k, a_group="k0")]
+    s = _session(layers, _inputs(layers, n, T, "bf16", seed=71), "bf16", 15)
+    fit = [dt.dattri_project_fit_workspace_bytes(s.ctx, r) for r in
+           (dt.DATTRI_ROUTE_AUTO, dt.DATTRI_ROUTE_FACTORED, dt.DATTRI_ROUTE_MATERIALIZED)]
+    assert fit[0] == fit[1] != fit[2]
+    c = Curvature(s)
+    phi = c.project_and_fit(n)
+    assert torch.equal(phi, s.project(n, route=dt.DATTRI_ROUTE_FACTORED))
