@@ -66,8 +66,9 @@ __device__ inline void store_rows(const f32x4 (&acc)[RT][NT], float* dst, int k,
     }
 }
 
-// ONCE: no two groups of the launch read the same input block.
-template <int ELT, bool AL, int RT, int NA, int NB, bool ONCE>
+// STREAM: blocks read past the caches: none (0), the output blocks (1), the input
+// blocks too (2: no two groups of the launch read the same one).
+template <int ELT, bool AL, int RT, int NA, int NB, int STREAM>
 __global__ __launch_bounds__(256, occupancy_of(ELT, AL, NA, NB)) void factored_kernel(const FactItem* __restrict__ items,
                                                           const FactGroup* __restrict__ groups,
                                                           const FactMember* __restrict__ members,
@@ -122,7 +123,7 @@ __global__ __launch_bounds__(256, occupancy_of(ELT, AL, NA, NB)) void factored_k
 #pragma unroll
       for (int t = 0; t < NA; ++t) acc_a[rt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
     if constexpr (kDma)
-      project_rows_dma<RT, NA, ONCE>(ra, r_wave, rows_valid, d_in, d_in, pin, acc_a, smem);
+      project_rows_dma<RT, NA, STREAM == 2>(ra, r_wave, rows_valid, d_in, d_in, pin, acc_a, smem);
     else
       project_rows<ELT, AL, RT, NA, NTL, PD>(ra, r_wave, rows_valid, d_in, d_in, pin, acc_a, pan);
     // projected input rows of every member that asks for them
@@ -151,7 +152,7 @@ __global__ __launch_bounds__(256, occupancy_of(ELT, AL, NA, NB)) void factored_k
 #pragma unroll
         for (int t = 0; t < NB; ++t) acc_b[rt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
       if constexpr (kDma)
-        project_rows_dma<RT, NB, true>(rb, r_wave, rows_valid, d_out, d_out, pout, acc_b, smem);
+        project_rows_dma<RT, NB, STREAM >= 1>(rb, r_wave, rows_valid, d_out, d_out, pout, acc_b, smem);
       else
         project_rows<ELT, AL, RT, NB, NTL, PD>(rb, r_wave, rows_valid, d_out, d_out, pout, acc_b, pan);
       if (M.rows_b)
@@ -234,29 +235,31 @@ void factored_instance(int elt, int na_req, int nb_req, int aligned, int* na_ins
 
 template <int ELT, bool AL, int NA, int NB>
 static hipError_t launch_one(const FactItem* items, int n, const FactGroup* g, const FactMember* m,
-                             float* part, int once, hipStream_t s) {
+                             float* part, int stream, hipStream_t s) {
   constexpr int RT = AL ? rt_of(ELT, NA, NB) : 1;
   constexpr bool kDma = dma_instance(ELT, AL, NA, NB);  // the register path has no such hint
-  if (kDma && once)
-    hipLaunchKernelGGL((factored_kernel<ELT, AL, RT, NA, NB, kDma>), dim3(n), dim3(256), 0, s, items, g, m, part);
+  if (kDma && stream == 2)
+    hipLaunchKernelGGL((factored_kernel<ELT, AL, RT, NA, NB, kDma ? 2 : 0>), dim3(n), dim3(256), 0, s, items, g, m, part);
+  else if (kDma && stream == 1)
+    hipLaunchKernelGGL((factored_kernel<ELT, AL, RT, NA, NB, kDma ? 1 : 0>), dim3(n), dim3(256), 0, s, items, g, m, part);
   else
-    hipLaunchKernelGGL((factored_kernel<ELT, AL, RT, NA, NB, false>), dim3(n), dim3(256), 0, s, items, g, m, part);
+    hipLaunchKernelGGL((factored_kernel<ELT, AL, RT, NA, NB, 0>), dim3(n), dim3(256), 0, s, items, g, m, part);
   return hipGetLastError();
 }
 
-hipError_t launch_factored(int elt, int na, int nb, int aligned, int once, const FactItem* items, int n_items,
+hipError_t launch_factored(int elt, int na, int nb, int aligned, int stream, const FactItem* items, int n_items,
                            const FactGroup* groups, const FactMember* members, float* partials,
                            hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
 #define DATTRI_FACT_CASE(E, A, B) \
-  if (elt == E && na == A && nb == B) return launch_one<E, true, A, B>(items, n_items, groups, members, partials, once, s);
+  if (elt == E && na == A && nb == B) return launch_one<E, true, A, B>(items, n_items, groups, members, partials, stream, s);
 #define DATTRI_FACT_NB(E, A) DATTRI_FACT_CASE(E, A, 1) DATTRI_FACT_CASE(E, A, 2) DATTRI_FACT_CASE(E, A, 4)
 #define DATTRI_FACT_ALL(E) \
   DATTRI_FACT_NB(E, 1) DATTRI_FACT_NB(E, 2) DATTRI_FACT_NB(E, 4) DATTRI_FACT_NB(E, 6) DATTRI_FACT_NB(E, 8)
   if (!aligned) {
     if (na != 8 || nb != 4) return hipErrorInvalidValue;
-    if (elt == 2) return launch_one<2, false, 8, 4>(items, n_items, groups, members, partials, once, s);
-    if (elt == 4) return launch_one<4, false, 8, 4>(items, n_items, groups, members, partials, once, s);
+    if (elt == 2) return launch_one<2, false, 8, 4>(items, n_items, groups, members, partials, stream, s);
+    if (elt == 4) return launch_one<4, false, 8, 4>(items, n_items, groups, members, partials, stream, s);
     return hipErrorInvalidValue;
   }
   DATTRI_FACT_ALL(2)

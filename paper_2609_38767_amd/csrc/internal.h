@@ -81,8 +81,9 @@ struct ReduceTask {
 
 // Items with example < 0 are padding (the workgroup exits at once); they keep
 // the XCD-interleaved order exact.
-// once: no two groups of the launch read the same input block.
-hipError_t launch_factored(int elt_bytes, int na, int nb, int aligned, int once, const FactItem* items,
+// stream: blocks read past the caches: none (0), the output blocks (1), the input
+// blocks too (2: no two groups of the launch read the same one).
+hipError_t launch_factored(int elt_bytes, int na, int nb, int aligned, int stream, const FactItem* items,
                            int n_items, const FactGroup* groups, const FactMember* members,
                            float* partials, hipStream_t s);
 void factored_instance(int elt_bytes, int na_req, int nb_req, int aligned, int* na_inst,
@@ -391,7 +392,8 @@ struct FsumOp {
 };
 struct FsumItem { int32_t op, unit0, n_units, part; };  // n_units 0: padding item
 // One launch per instance (elt, aligned, tiles); rows per wave from fsum_rt.
-hipError_t launch_fsum(int elt_bytes, int aligned, int nt, const FsumItem* items, int n_items,
+// once: the call's rows are more than a cache keeps (non-temporal loads).
+hipError_t launch_fsum(int elt_bytes, int aligned, int nt, int once, const FsumItem* items, int n_items,
                        const FsumOp* ops, float* partials, hipStream_t s);
 int fsum_nt_instance(int nt_req);   // tiles of the instance serving nt_req tiles
 int fsum_rows_per_wave(int nt_inst);

@@ -38,7 +38,8 @@ constexpr int fsum_rt(int nt) { return nt <= 2 ? 4 : 2; }
 // through LDS by direct loads (project_rows_dma), as the factored route does
 constexpr bool fsum_dma(int elt, bool aligned, int nt) { return elt == 2 && aligned && (nt == 2 || nt == 4); }
 
-template <int ELT, bool AL, int NT>
+// ONCE: the rows of the call are more than a cache keeps (non-temporal loads).
+template <int ELT, bool AL, int NT, bool ONCE>
 __global__ __launch_bounds__(256, 2) void fsum_kernel(const FsumItem* __restrict__ items,
                                                       const FsumOp* __restrict__ ops,
                                                       float* __restrict__ partials) {
@@ -88,7 +89,7 @@ __global__ __launch_bounds__(256, 2) void fsum_kernel(const FsumItem* __restrict
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[rt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
       if constexpr (kDma)
-        project_rows_dma<RT, NT, true>(r, r_wave, rows_valid, d, d, P, acc, smem);
+        project_rows_dma<RT, NT, ONCE>(r, r_wave, rows_valid, d, d, P, acc, smem);
       else
         project_rows<ELT, AL, RT, NT, NT, PD>(r, r_wave, rows_valid, d, d, P, acc, pan);
 #pragma unroll
@@ -124,13 +125,17 @@ __global__ __launch_bounds__(256, 2) void fsum_kernel(const FsumItem* __restrict
 int fsum_nt_instance(int nt_req) { return nt_req <= 1 ? 1 : (nt_req <= 2 ? 2 : 4); }
 int fsum_rows_per_wave(int nt_inst) { return fsum_rt(nt_inst); }
 
-hipError_t launch_fsum(int elt, int aligned, int nt, const FsumItem* items, int n_items,
+hipError_t launch_fsum(int elt, int aligned, int nt, int once, const FsumItem* items, int n_items,
                        const FsumOp* ops, float* partials, hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
-#define DATTRI_FSUM(E, A, N)                                                                   \
-  if (elt == E && (aligned != 0) == A && nt == N) {                                            \
-    hipLaunchKernelGGL((fsum_kernel<E, A, N>), dim3(n_items), dim3(256), 0, s, items, ops, partials); \
-    return hipGetLastError();                                                                  \
+#define DATTRI_FSUM(E, A, N)                                                                                  \
+  if (elt == E && (aligned != 0) == A && nt == N) {                                                           \
+    constexpr bool kDma = fsum_dma(E, A, N); /* the register path has no such hint */                         \
+    if (kDma && once)                                                                                         \
+      hipLaunchKernelGGL((fsum_kernel<E, A, N, kDma>), dim3(n_items), dim3(256), 0, s, items, ops, partials); \
+    else                                                                                                      \
+      hipLaunchKernelGGL((fsum_kernel<E, A, N, false>), dim3(n_items), dim3(256), 0, s, items, ops, partials); \
+    return hipGetLastError();                                                                                 \
   }
   DATTRI_FSUM(2, true, 1) DATTRI_FSUM(2, true, 2) DATTRI_FSUM(2, true, 4)
   DATTRI_FSUM(2, false, 1) DATTRI_FSUM(2, false, 2) DATTRI_FSUM(2, false, 4)

@@ -115,7 +115,7 @@ struct FsumPlan {
   std::vector<StatTask> tasks;
   struct Launch { int elt, aligned, nt, first, count; };
   std::vector<Launch> launches;
-  int max_out = 0;
+  int max_out = 0, once = 0;
   int32_t n = 0;
   size_t off_ops = 0, off_items = 0, off_tasks = 0, blob_bytes = 0, off_parts = 0, total = 0;
 };
@@ -165,6 +165,13 @@ dattri_status plan_fsum(const dattri_ctx* ctx, const CurvLayout& C, FsumPlan& P,
       P.ops.push_back(O);
     }
   }
+  // Rows that the last-level cache (256 MB) may still hold from their capture or
+  // an earlier pass are read as usual; more than it holds is streamed past it
+  // (Pythia-shaped layers, k = 32: 168 MB 83 us, 93 non-temporal; 1.3 GB 277 and
+  // 251; k = 64: 201 MB 125 and 141, 2.7 GB 699 and 635).
+  int64_t bytes = 0;
+  for (const FsumOp& O : P.ops) bytes += (int64_t)n * O.T * O.d * elt;
+  P.once = bytes > ((int64_t)256 << 20);
   // work items: runs of units of one op, about kFsumTargetItems in total
   const double target = std::max(1.0, total_cost / (double)kFsumTargetItems);
   std::vector<int64_t> upi(P.ops.size()), nitems(P.ops.size());
@@ -486,7 +493,7 @@ dattri_status dattri_curvature_accumulate_factors(dattri_ctx* ctx, void* state, 
   const FsumItem* d_items = (const FsumItem*)(tab + P.off_items);
   float* parts = (float*)(ws + P.off_parts);
   for (const FsumPlan::Launch& L : P.launches)
-    HIP_TRY(launch_fsum(L.elt, L.aligned, L.nt, d_items + L.first, L.count, d_ops, parts, s));
+    HIP_TRY(launch_fsum(L.elt, L.aligned, L.nt, P.once, d_items + L.first, L.count, d_ops, parts, s));
   HIP_TRY(launch_stat_reduce((const StatTask*)(tab + P.off_tasks), (int)P.tasks.size(), P.max_out, parts,
                              (uint8_t*)state, s));
   return DATTRI_OK;
@@ -667,7 +674,7 @@ dattri_status dattri_project_and_fit(dattri_ctx* ctx, void* phi, dattri_dtype ph
     const uint8_t* fd = tab + (F.off_fdesc - F.off_desc);
     float* fparts = (float*)(ws + F.off_fparts);
     for (const FsumPlan::Launch& L : F.mat.launches)
-      HIP_TRY(launch_fsum(L.elt, L.aligned, L.nt, (const FsumItem*)(fd + F.mat.off_items) + L.first, L.count,
+      HIP_TRY(launch_fsum(L.elt, L.aligned, L.nt, F.mat.once, (const FsumItem*)(fd + F.mat.off_items) + L.first, L.count,
                           (const FsumOp*)(fd + F.mat.off_ops), fparts, s));
     HIP_TRY(launch_stat_reduce((const StatTask*)(fd + F.mat.off_tasks), (int)F.mat.tasks.size(), F.mat.max_out,
                                fparts, (uint8_t*)state, s));

@@ -35,7 +35,7 @@ struct Plan {
   std::vector<ReduceTask> tasks;  // factored tasks first, then one per MatChunk
   int n_fact_tasks = 0;
   int fact_max_out = 0;            // largest k_in*k_out over the factored tasks
-  struct Launch { int elt, na, nb, aligned, once, first, count; };
+  struct Launch { int elt, na, nb, aligned, stream, first, count; };
   std::vector<Launch> launches;
   std::vector<MatChunk> mat;
   // split form of the factored route (captures with few fused work items)

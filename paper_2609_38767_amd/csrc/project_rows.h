@@ -170,9 +170,9 @@ struct DmaLds {
 
 // kOnce: rows are streamed past L2's other lines (nt): right where no other
 // workgroup of the same XCD reads them about the same time.  (The factor sums
-// set it always: layers that share an input are separate ops there, mostly on
-// different XCDs.  4 Qwen-shaped blocks with shared inputs, 32 x 512 rows: k =
-// 64 1.95 ms with, 1.96 without; k = 16 2.20 both.)
+// set it by size alone: layers that share an input are separate ops there,
+// mostly on different XCDs.  4 Qwen-shaped blocks with shared inputs, 32 x 512
+// rows: k = 64 1.95 ms with, 1.96 without; k = 16 2.20 both.)
 template <int RT, int NT, bool kOnce>
 __device__ inline void project_rows_dma(const rsrc_t r, int r_wave, int nrows, int d, int64_t ld,
                                         const FragSrc<NT>& P, f32x4 (&acc)[RT][NT], uint8_t* lds) {

@@ -389,6 +389,16 @@ dattri_status dattri::build_plan(const dattri_ctx* ctx, dattri_route forced, Pla
   if (rows && forced == DATTRI_ROUTE_AUTO)
     for (size_t l = 0; l < route.size(); ++l)
       if (route[l] == DATTRI_ROUTE_MATERIALIZED && factored_supported(ctx->layers[l])) route[l] = DATTRI_ROUTE_FACTORED;
+  // Blocks that the last-level cache (256 MB) may still hold from their capture
+  // are read as usual; of more than it holds, those that one group alone reads
+  // are streamed past it (24 bf16 layers of 4096 -> 1024, k = 16, 64 x 16 tokens,
+  // 252 MB: 174 us, 195 non-temporal; 4 Llama-shaped blocks, 9 GB: 1.69 ms, 1.55).
+  int64_t factor_bytes = 0;
+  for (size_t l = 0; l < route.size(); ++l) {
+    const Layer& L = ctx->layers[l];
+    if (route[l] == DATTRI_ROUTE_FACTORED) factor_bytes += (int64_t)n * L.T * (L.d_in + L.d_out) * elt;
+  }
+  const int streamed = factor_bytes > ((int64_t)256 << 20);
   std::vector<std::vector<int>> group_layers;
   for (size_t l = 0; l < ctx->layers.size(); ++l) {
     const Layer& L = ctx->layers[l];
@@ -579,8 +589,9 @@ dattri_status dattri::build_plan(const dattri_ctx* ctx, dattri_route forced, Pla
       units[u].push_back(g);
       unit_cost[u] += group_cost[g];
     }
-    int once = 1;  // every input block of the launch belongs to one group
-    for (const auto& u : units) once = once && u.size() == 1;
+    int stream = streamed ? 2 : 0;  // the input blocks too where each belongs to one group
+    for (const auto& u : units)
+      if (stream && u.size() != 1) stream = 1;
     std::vector<int> order(units.size());
     for (size_t u = 0; u < units.size(); ++u) order[u] = (int)u;
     if (units.size() < (size_t)4 * kXcds) {
@@ -593,7 +604,7 @@ dattri_status dattri::build_plan(const dattri_ctx* ctx, dattri_route forced, Pla
           for (int c = 0; c < H.n_chunks; ++c)
             for (int g : units[u]) P.items.push_back({g, e, c, 0});
       }
-      P.launches.push_back({elt, I.na, I.nb, I.aligned, once, first, (int)P.items.size() - first});
+      P.launches.push_back({elt, I.na, I.nb, I.aligned, stream, first, (int)P.items.size() - first});
       continue;
     }
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return unit_cost[a] > unit_cost[b]; });
@@ -613,7 +624,7 @@ dattri_status dattri::build_plan(const dattri_ctx* ctx, dattri_route forced, Pla
     for (size_t s = 0; s < len; ++s)
       for (int x = 0; x < kXcds; ++x)
         P.items.push_back(s < q[x].size() ? q[x][s] : FactItem{0, -1, 0, 0});
-    P.launches.push_back({elt, I.na, I.nb, I.aligned, once, first, (int)P.items.size() - first});
+    P.launches.push_back({elt, I.na, I.nb, I.aligned, stream, first, (int)P.items.size() - first});
   }
 
   // ---- split form: one stage-1 op per factor block (a group's A, each
@@ -860,7 +871,7 @@ dattri_status dattri::build_plan(const dattri_ctx* ctx, dattri_route forced, Pla
           if (u == units.size()) units.push_back({});
           units[u].push_back(o);
         }
-        for (const auto& u : units) P.sops[u[0]].once = u.size() == 1;
+        for (const auto& u : units) P.sops[u[0]].once = streamed && u.size() == 1;
         const int rows_wg = al ? split_stream_rows(elt) : split_rows_of(nt);
         struct Piece { size_t unit; int rb0, rb1; double cost, item; };
         std::vector<Piece> pieces;
@@ -1421,7 +1432,7 @@ dattri_status dattri::run_plan(dattri_ctx* ctx, const Plan& P, void* phi, dattri
   float* fpart = (float*)(ws + P.off_fpart);
   const int phi_bf16 = phi_dtype == DATTRI_BF16;
   for (const Plan::Launch& L : P.launches)
-    HIP_TRY(launch_factored(L.elt, L.na, L.nb, L.aligned, L.once, d_items + L.first, L.count, d_groups,
+    HIP_TRY(launch_factored(L.elt, L.na, L.nb, L.aligned, L.stream, d_items + L.first, L.count, d_groups,
                             d_members, fpart, s));
   if (P.n_fact_tasks)
     HIP_TRY(launch_reduce(d_tasks, P.n_fact_tasks, n, P.fact_max_out, fpart, phi, phi_bf16, ld_phi, s));

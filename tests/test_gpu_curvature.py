@@ -574,3 +574,24 @@ def test_fit_under_auto_keeps_rows(d, k, n, T):
     c = Curvature(s)
     phi = c.project_and_fit(n)
     assert torch.equal(phi, s.project(n, route=dt.DATTRI_ROUTE_FACTORED))
+
+
+@pytest.mark.parametrize("rows", [16384, 16392])  # 256 MB of rows, and one row of 8 more per layer
+@pytest.mark.parametrize("k", [32, 64])
+def test_streamed_and_cached_rows(rows, k):
+    # both sides of the size above which rows are loaded past the caches
+    d = 4096
+    layers = [dict(name="r0", d_in=d, d_out=d, k_in=k, k_out=k, a_group="r0")]
+    g = torch.Generator(device=DEV).manual_seed(3)
+    A, B = (torch.randn((8, rows // 8, d), generator=g, device=DEV).to(torch.bfloat16) for _ in range(2))
+    s = _session(layers, [(A, B)], "bf16", 13)
+    c = Curvature(s)
+    c.accumulate_factors()
+    phi = s.project(8, route=dt.DATTRI_ROUTE_FACTORED)
+    P_in, P_out = (torch.from_numpy(np.asarray(m, dtype=np.float64)).to(DEV) for m in oracle_maps(13, layers, "bf16")[0])
+    a, b = A.double() @ P_in, B.double() @ P_out
+    ref = torch.stack([a[i].t().contiguous() @ b[i] for i in range(8)]).reshape(8, -1)
+    assert rel_fro(host64(phi), host64(ref)) <= 1e-5
+    a, b = a.reshape(-1, k), b.reshape(-1, k)
+    assert rel_fro(host64(c.field(0, "sum_a")), host64(a.t().contiguous() @ a)) <= 1e-5
+    assert rel_fro(host64(c.field(0, "sum_g")), host64(b.t().contiguous() @ b)) <= 1e-5
