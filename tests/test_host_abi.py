@@ -487,3 +487,20 @@ def test_probe_errors():
         with pytest.raises(dt.DattriError) as e:
             fn()
         assert _status(e) == want
+
+
+@pytest.mark.parametrize("k", [8, 16, 32, 64])
+@pytest.mark.parametrize("layers", [24, 96])
+def test_few_row_slabs(k, layers):
+    # blocks of few rows are cut into as many slabs as 64 rows are: the partial
+    # rows, which are nearly all of this scratch, shrink with the rows alone
+    fake, size = 1 << 40, {}
+    for T in (16, 64):
+        c = dt.dattri_create(dt.DATTRI_BF16, 0)
+        for l in range(layers):
+            dt.dattri_register_layer(c, 1024, 4096, k, k)
+        for l in range(layers):
+            dt.dattri_capture_layer(c, l, fake + (l << 30), fake + (l << 32), 1, T)
+        size[T] = dt.dattri_workspace_bytes(c, dt.DATTRI_ROUTE_FACTORED)
+        dt.dattri_destroy(c)
+    assert 4 * size[16] >= size[64]
