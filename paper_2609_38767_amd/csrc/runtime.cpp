@@ -873,7 +873,16 @@ dattri_status dattri::build_plan(const dattri_ctx* ctx, dattri_route forced, Pla
           if (u == units.size()) units.push_back({});
           units[u].push_back(o);
         }
-        for (const auto& u : units) P.sops[u[0]].once = streamed && u.size() == 1;
+        // Few workgroups hide less of the memory's latency, so here the line lies
+        // lower.  Passes over three sets of captures in turn (what one set leaves in
+        // the cache the next may push out): 12 ragged examples of up to 25 tokens
+        // through 16 GPT-2-shaped blocks, k = 64, 118 MB, 55 us, 53 non-temporal; 14
+        // of 35 through 18, k = 16, 217 MB, 44 and 41; 3 of 67 through 6 Qwen-shaped
+        // blocks, k = 17, 217 MB, 63 and 57; but 5 of 86 through 7 Pythia-shaped, k =
+        // 48, 99 MB, 42.6 and 43.6.  Over one set again and again: 54, 57 for the
+        // Qwen blocks.
+        for (const auto& u : units)
+          P.sops[u[0]].once = factor_bytes > ((int64_t)100 << 20) && u.size() == 1;
         const int rows_wg = al ? split_stream_rows(elt) : split_rows_of(nt);
         struct Piece { size_t unit; int rb0, rb1; double cost, item; };
         std::vector<Piece> pieces;

@@ -576,10 +576,11 @@ def test_fit_under_auto_keeps_rows(d, k, n, T):
     assert torch.equal(phi, s.project(n, route=dt.DATTRI_ROUTE_FACTORED))
 
 
-@pytest.mark.parametrize("rows", [16384, 16392])  # 256 MB of rows, and one row of 8 more per layer
+@pytest.mark.parametrize("rows", [6400, 6408, 16384, 16392])  # 100 MB and 256 MB of rows, and just more
 @pytest.mark.parametrize("k", [32, 64])
 def test_streamed_and_cached_rows(rows, k):
-    # both sides of the size above which rows are loaded past the caches
+    # both sides of the sizes above which the split form, and the others, load
+    # their rows past the caches
     d = 4096
     layers = [dict(name="r0", d_in=d, d_out=d, k_in=k, k_out=k, a_group="r0")]
     g = torch.Generator(device=DEV).manual_seed(3)
