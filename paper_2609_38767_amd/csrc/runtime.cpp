@@ -723,11 +723,14 @@ dattri_status dattri::build_plan(const dattri_ctx* ctx, dattri_route forced, Pla
     // sqrt(2 c W / slots).  A block of fewer rows than its map has columns
     // streams the map for longer than its rows and is counted by those (24
     // layers of 1024 -> 4096, k = 64, 32 rows: 39 us a call with whole-width
-    // items, 27 with four slabs), and a stage is no shorter than 64 rows' however
-    // few there are, as its loads' latency then bounds it (96 such layers, k =
-    // 16, 16 rows: 45 us, 36 counted as 64).
+    // items, 27 with four slabs), and a bf16 stage is no shorter than 64 rows'
+    // however few there are, as its loads' latency then bounds it (96 such layers,
+    // k = 16, 16 rows: 45 us, 36 counted as 64).  Float32 has three workgroups per
+    // CU to hide it (40 rows through 4 Qwen-shaped blocks, k = 16: 32 us, 36
+    // counted as 64).
     double work = 0.0, fixed = 0.0;
-    auto stream_rows_of = [](const SplitOp& O, int r) { return (double)std::max({r, O.nt * 16, 64}); };
+    const int floor_rows = elt == 2 ? 64 : 1;
+    auto stream_rows_of = [=](const SplitOp& O, int r) { return (double)std::max({r, O.nt * 16, floor_rows}); };
     const int srows = split_stream_rows(elt), slots = elt == 2 ? kCus : 3 * kCus;
     for (size_t o = op0; o < P.sops.size(); ++o) {
       const SplitOp& O = P.sops[o];

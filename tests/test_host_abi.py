@@ -504,3 +504,17 @@ def test_few_row_slabs(k, layers):
         size[T] = dt.dattri_workspace_bytes(c, dt.DATTRI_ROUTE_FACTORED)
         dt.dattri_destroy(c)
     assert 4 * size[16] >= size[64]
+
+
+def test_few_row_slabs_f32():
+    # float32 blocks of few rows keep wider slabs
+    size = {}
+    for T in (16, 64):
+        c = dt.dattri_create(dt.DATTRI_F32, 0)
+        for l in range(24):
+            dt.dattri_register_layer(c, 1024, 4096, 16, 16)
+        for l in range(24):
+            dt.dattri_capture_layer(c, l, (1 << 40) + (l << 30), (1 << 40) + (l << 32), 1, T)
+        size[T] = dt.dattri_workspace_bytes(c, dt.DATTRI_ROUTE_FACTORED)
+        dt.dattri_destroy(c)
+    assert 5 * size[16] < size[64]
