@@ -117,7 +117,7 @@ struct SplitOp {                    // one factor block: a group's A or a member
   const int32_t* lengths;           // [n] or null: row i is token i % T of example i / T
   int32_t T;
   int32_t out_ld;                   // floats per projected row
-  int32_t once, pad0;               // no other op of the call reads X
+  int32_t once, pad0;               // non-temporal: no other op reads X, and the call reads over 100 MB
   int32_t rows, ld;                 // n*T, row stride
   int32_t width, pad1;              // columns of a row (scored rows may lie further apart: ld > width)
   int32_t slab_cols, n_slabs;
